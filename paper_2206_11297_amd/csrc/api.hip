@@ -524,8 +524,6 @@ static int enqueue(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_byte
   return RSZ_OK;
 }
 
-uint64_t decode_tables_bytes();
-
 // Host parse of a stream header; fills the decode plan geometry.
 static int parse_header(const uint8_t *h, uint64_t n, uint64_t in_bytes, rsz_params *p,
                         uint32_t *npeaks, DecodePlan *dp) {
@@ -608,21 +606,14 @@ static int parse_header(const uint8_t *h, uint64_t n, uint64_t in_bytes, rsz_par
     dp->off_run = end;
     dp->off_runoffs = off_runoffs;
     dp->off_runbits = off_runbits;
+    decode_geometry(*dp);
   }
   return RSZ_OK;
 }
 
-uint64_t decode_roi_tables_bytes();
-
 static uint64_t decode_ws_bytes(const DecodePlan &dp) {
-  return align_up(4ull * dp.nbins, 256) + align_up(dp.nbins + 64ull, 256) +
-         align_up(4ull * dp.nchunks, 256) + 256 +
-         align_up(decode_tables_bytes(), 256) +
-         (dp.dim == 1 ? align_up(4ull * dp.P * dp.Hb, 256) : 0) +
-         (dp.roi_coding ? align_up(4ull * dp.npeaks * dp.w * dp.w, 256) +
-                              align_up(decode_roi_tables_bytes(), 256)
-                        : 0) +
-         (dp.run_coding ? align_up(4 * ((dp.T + 31) / 32 + 2), 256) : 0);
+  DecodePlan t = dp;
+  return (uint64_t)(decode_region(t, (uint8_t *)0) - (uint8_t *)0);
 }
 
 // Results of a single-frame call live in the workspace tail.
@@ -685,32 +676,7 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
     if (dp.init_status == RSZ_OK) {
       dp.in = (const uint8_t *)it[f].in;
       dp.frame = it[f].frame;
-      dp.res = (int32_t *)w;
-      w += align_up(4ull * dp.nbins, 256);
-      dp.res8 = w;
-      w += align_up(dp.nbins + 64ull, 256);
-      dp.zcount = (uint32_t *)w;
-      w += align_up(4ull * dp.nchunks, 256);
-      dp.status = (int32_t *)w;
-      w += 256;
-      dp.tables = (uint32_t *)w;
-      w += align_up(decode_tables_bytes(), 256);
-      if (dp.dim == 1) {
-        dp.carry = (uint32_t *)w;
-        w += align_up(4ull * dp.P * dp.Hb, 256);
-      }
-      if (dp.roi_coding) {
-        dp.roi_payload = (uint32_t *)w;
-        w += align_up(4ull * dp.npeaks * dp.w * dp.w, 256);
-        dp.roi_tables = (uint32_t *)w;
-        w += align_up(decode_roi_tables_bytes(), 256);
-      }
-      // the Huffman words: in the stream, or expanded from the run section
-      dp.bits = (const uint32_t *)(dp.in + dp.off_bits);
-      if (dp.run_coding) {
-        dp.hbits = (uint32_t *)w;
-        dp.bits = dp.hbits;
-      }
+      decode_region(dp, w);
     }
     if (it[f].status) dp.status = it[f].status;
     if (!dp.status) return RSZ_ERR_ARG;   // a rejected stream needs a status word
@@ -733,7 +699,8 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
   for (int k = 0; k < kDecKernels; ++k) pre[(size_t)k * (n + 1) + n] = total_blocks[k];
   const int st = stage_to_device(ws, host.data(), head, s);
   if (st) return st;
-  DecBatch db;
+  DecBatch db = {};
+  for (uint32_t f = 0; f < n; ++f) decode_panel_shape(db, dps[f]);
   db.n = n;
   db.plans = (const DecodePlan *)ws;
   db.pre = (const uint32_t *)(ws + align_up((uint64_t)sizeof(DecodePlan) * n, 256));
@@ -1136,6 +1103,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     dp.off_chunks = g.off_chunks;
     dp.off_bits = g.off_bits;
     dp.init_status = RSZ_OK;
+    decode_geometry(dp);
     region[f] = decode_ws_bytes(dp);
     total += region[f];
     rows = std::min<uint32_t>(rows, (uint32_t)align_up(p->height, p->bin));
@@ -1172,18 +1140,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     if (vf.valid) {
       dp.in = (const uint8_t *)d[f].out;
       dp.frame = frames_out[f];
-      dp.res = (int32_t *)w;
-      w += align_up(4ull * dp.nbins, 256);
-      dp.res8 = w;
-      w += align_up(dp.nbins + 64ull, 256);
-      dp.zcount = (uint32_t *)w;
-      w += align_up(4ull * dp.nchunks, 256);
-      dp.status = (int32_t *)w;
-      w += 256;
-      dp.tables = (uint32_t *)w;
-      w += align_up(decode_tables_bytes(), 256);
-      if (dp.dim == 1) dp.carry = (uint32_t *)w;
-      dp.bits = (const uint32_t *)(dp.in + dp.off_bits);
+      decode_region(dp, w);
     } else {
       dp.status = (int32_t *)w;
     }
@@ -1215,6 +1172,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   vr->vb.frames = (const VerifyFrame *)(ws + h_dp + h_pre);
   vr->vb.wg_prefix = (const uint32_t *)(ws + h_dp + h_pre + h_vf);
   vr->vb.total_wgs = (uint32_t)wgs;
+  for (uint32_t f = 0; f < n; ++f) decode_panel_shape(vr->db, dps[f]);
   vr->db.n = n;
   vr->db.plans = (const DecodePlan *)ws;
   vr->db.pre = (const uint32_t *)(ws + h_dp);

@@ -20,18 +20,14 @@
 //                   only nonzero residuals stored); each chunk must end
 //                   exactly at the next offset.
 //   k_dec_outliers  scatter outlier residuals onto the code-0 positions.
-//   k_dec_rows      inclusive prefix sum along each bin row (wrapping int32),
-//                   four rows per wave.
-//   k_dec_carry, k_dec_rowadd  dimension 1: carries across the rows.
-//   k_dec_cols      inclusive prefix sum down each bin column -> q; for
-//                   dimension 2 it also writes every pixel float(q * 2eb)
-//                   of its bin.
-//   k_dec_panel     dimension 2 with a panel's bins in LDS (instead of
-//                   k_dec_rows and k_dec_cols): one workgroup per panel, row
-//                   sums, column sums and pixels.
-//   k_dec_panels    dimension 3: prefix sum across the panels.
-//   k_dec_expand    dimensions 1 and 3, one wave per bin row: every pixel
-//                   gets float(q * 2eb) of its bin.
+//   k_dec_panels    dimension 3: prefix sum of the residuals across the
+//                   panels, which leaves the panels' 2D residuals.
+//   k_dec_rowsum, k_dec_carry  dimension 1: sums of the bin rows, then the
+//                   carry into each row.
+//   k_dec_cols      dimensions 2 and 3: the column sums above each band of
+//                   kDecTH bin rows.
+//   k_dec_pixels    one wave per band: column sums down the band, row sums
+//                   across it -> q, and every pixel float(q * 2eb).
 //   k_dec_roi_tables, k_dec_roi_decode, k_dec_roi_unpred  coded ROI: class
 //                   tables, per-window decode, inverse prediction.
 //   k_dec_roi       ROI windows restored from the payload bits, one wave
@@ -49,23 +45,18 @@ namespace rsz {
 constexpr int kLutBits = 11;
 constexpr int32_t kMark = INT32_MIN;  // residual slot waiting for its outlier
 
-// Dimension 2 where a panel's bins fit in LDS (and a bin row in one
-// workgroup's threads): one workgroup per panel takes the row sums, the
-// column sums and the pixel writes, so the residuals make one trip from HBM.
-constexpr uint32_t kPanelBins = 19200;
-constexpr uint32_t kPanelThreads = 1024;
-__host__ __device__ inline bool panel_in_lds(const DecodePlan &dp) {
-  return dp.dim == 2 && (uint64_t)dp.Hb * dp.Wb <= kPanelBins && dp.Wb <= kPanelThreads;
-}
-
-
-// tables: [0,2048) lut (sym | len << 16, 0 = longer code), then first[33],
-// count[33], offs[33], sorted[1024], then the multi-symbol table: per 11-bit
-// window two words, (up to 3 whole codewords' symbols, 10 bits each) | count
+// tables: first[33], count[33], offs[33], sorted[1024], then the multi-symbol
+// table: per 11-bit window two words, (up to 3 whole codewords' symbols, 10 bits each) | count
 // << 30 and the bit position after each of them (4 bits each)
-constexpr int kTabLut = 0, kTabFirst = 1 << kLutBits, kTabCount = kTabFirst + 33,
+constexpr int kTabFirst = 0, kTabCount = kTabFirst + 33,
               kTabOffs = kTabCount + 33, kTabSorted = kTabOffs + 33,
               kTabMulti = kTabSorted + kNumSym, kTabWords = kTabMulti + 2 * (1 << kLutBits);
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 __device__ __forceinline__ void corrupt(int32_t *status) {
   atomicCAS(status, (int32_t)RSZ_OK, (int32_t)RSZ_ERR_CORRUPT);
@@ -82,23 +73,42 @@ __device__ __forceinline__ uint32_t rd32(const uint8_t *p, uint64_t off) {
 // A batch of streams: each kernel's workgroups are numbered across the
 // frames, kernel K's per-frame counts in the prefix pre[K * (n + 1) ...]; a
 // workgroup finds its frame (the last with prefix <= its index) and works on
-// that frame's plan with its index and count inside the frame.
+// that frame's plan with its index and count inside the frame.  Every wave
+// searches 64 places at a time (all its lanes are active here): two rounds of
+// loads for up to 4096 frames, where a binary search of 1000 frames made ten
+// dependent ones before a workgroup could start.
 __device__ __forceinline__ uint32_t dec_frame(const uint32_t *pre, uint32_t n, uint32_t b) {
-  uint32_t lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (pre[mid] <= b) lo = mid; else hi = mid;
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t lo = 0, len = n;   // the frame lies in [lo, lo + len)
+  while (len > 1) {
+    const uint32_t step = (len + 63) / 64;
+    const uint32_t k = lane * step;
+    const bool le = k < len && *gm(pre + lo + k) <= b;   // true for lane 0
+    const uint32_t c = (uint32_t)__builtin_popcountll(__ballot(le)) - 1;
+    lo += c * step;
+    len = min(step, len - c * step);
   }
   return lo;
 }
-#define RSZ_DEC_FRAME(K)                                                   \
+#define RSZ_DEC_FRAME_AT(K, BLK)                                           \
   const uint32_t *pre_ = db.pre + (size_t)(K) * (db.n + 1);                \
-  const uint32_t f_ = dec_frame(pre_, db.n, blockIdx.x);                   \
-  const uint32_t bid = blockIdx.x - pre_[f_];                              \
+  const uint32_t blk_ = (BLK);                                             \
+  const uint32_t f_ = dec_frame(pre_, db.n, blk_);                         \
+  const uint32_t bid = blk_ - pre_[f_];                                    \
   const uint32_t nblk = pre_[f_ + 1] - pre_[f_];                           \
   (void)bid;                                                               \
   (void)nblk;                                                              \
   const DecodePlan &dp = db.plans[f_]
+#define RSZ_DEC_FRAME(K) RSZ_DEC_FRAME_AT(K, blockIdx.x)
+
+// Workgroups go to the 8 XCDs in turn; each XCD takes a contiguous run of
+// them instead (the last few in order), so that its L2 holds neighbouring
+// pixels (a plain store kernel over 32000 panels of 185 x 388: 1.73 ms in
+// turn, 1.68 in runs; k_dec_panel on them 1.96 and 1.88).
+__device__ __forceinline__ uint32_t xcd_run() {
+  const uint32_t per = gridDim.x / 8;
+  return blockIdx.x < 8 * per ? (blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
+}
 
 __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
   RSZ_DEC_FRAME(0);
@@ -212,7 +222,6 @@ __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
       }
     }
     s_lut[x] = e;
-    tab[kTabLut + x] = e;
   }
   __syncthreads();
   // multi-symbol entry: the whole codewords (at most 3) that the window
@@ -298,18 +307,13 @@ struct BitWindow {
 // `inval` reports a bit pattern that is no codeword.  With `zrun` (residual
 // 0's codeword is the single bit 0), a run of z zero bits is z residual-0
 // symbols, taken at once up to lim.
-// One decoded symbol other than residual 0 into slot k: a residual, or the
-// outlier mark for code 0; with out8 (k_dec_panel's streams) a code byte,
-// and the residual in out only when the byte is 0.
+// One decoded symbol other than residual 0 into slot k: its code byte, and
+// where that is 0 the residual (or the outlier mark for code 0) in out.
 __device__ __forceinline__ void put_sym(int32_t *out, uint8_t *out8, uint32_t k, uint32_t sym) {
   const int32_t r = sym ? (int32_t)sym - kRadius : kMark;
-  if (out8) {
-    const bool small = sym && (uint32_t)(r + 127) < 255u;
-    *gm(out8 + k) = small ? (uint8_t)(r + 128) : (uint8_t)0;
-    if (!small) *gm(out + k) = r;
-  } else {
-    *gm(out + k) = r;
-  }
+  const bool small = sym && (uint32_t)(r + 127) < 255u;
+  *gm(out8 + k) = small ? (uint8_t)(r + 128) : (uint8_t)0;
+  if (!small) *gm(out + k) = r;
 }
 
 template <bool WRITE>
@@ -535,22 +539,10 @@ __global__ __launch_bounds__(256) void k_dec_chunks(DecBatch db) {
   // lanes then store only their nonzero residuals (most are 0)
   // (code bytes: 128, residual 0, in 16-byte stores; the region holds 64
   // bytes past the last chunk)
-  const bool bytes = panel_in_lds(dp);
   if (!bad) {
-    if (bytes) {
-      RSZ_G uint8_t *rc = gm(dp.res8 + g0);
-      for (uint32_t i = 16 * lane; i < nsym; i += 1024)
-        *(RSZ_G u32x4 *)(rc + i) = u32x4{0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
-    } else {
-      RSZ_G int32_t *rc = gm(dp.res + g0);
-      for (uint32_t i = 4 * lane; i < nsym; i += 256) {
-        if (i + 4 <= nsym) {
-          *(RSZ_G u32x4 *)(rc + i) = u32x4{0u, 0u, 0u, 0u};
-        } else {
-          for (uint32_t k = i; k < nsym; ++k) rc[k] = 0;
-        }
-      }
-    }
+    RSZ_G uint8_t *rc = gm(dp.res8 + g0);
+    for (uint32_t i = 16 * lane; i < nsym; i += 1024)
+      *(RSZ_G u32x4 *)(rc + i) = u32x4{0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   }
   BitWindow win;
@@ -560,14 +552,9 @@ __global__ __launch_bounds__(256) void k_dec_chunks(DecBatch db) {
   if (!bad)
     decode_run<true>(win, pos, lim, s_multi, s_first, s_count, s_offs, s_sorted, dp.res + g0 + off,
                      off < nsym ? nsym - off : 0u, zeros, inv, zrun,
-                     bytes ? dp.res8 + g0 + off : nullptr);
+                     dp.res8 + g0 + off);
   bad |= __builtin_amdgcn_uicmp((uint32_t)inv, 0u, 33 /* ne */) != 0;
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) zeros += __shfl_xor(zeros, d);
-  if (lane == 0) {
-    if (bad) corrupt(dp.status);
-    *gm(dp.zcount + c) = zeros;
-  }
+  if (lane == 0 && bad) corrupt(dp.status);
 }
 
 // The outliers into their bins' residual slots; the frame's workgroups take
@@ -585,7 +572,7 @@ __global__ __launch_bounds__(256) void k_dec_outliers(DecBatch db) {
     const int32_t r = orr[k];
     // the bin must have decoded as code 0 (its code byte 0 and the mark in res)
     if (g >= dp.nbins || (k > 0 && g <= oi[k - 1]) || (r > -kRadius && r < kRadius) ||
-        (int64_t)r <= -lim || (int64_t)r >= lim || (panel_in_lds(dp) && dp.res8[g] != 0) ||
+        (int64_t)r <= -lim || (int64_t)r >= lim || dp.res8[g] != 0 ||
         dp.res[g] != kMark) {
       corrupt(dp.status);
       return;
@@ -594,354 +581,640 @@ __global__ __launch_bounds__(256) void k_dec_outliers(DecBatch db) {
   }
 }
 
-// One wave per bin row: inclusive prefix sum along the row.
-constexpr uint32_t kDecRowsPerWave = 4;   // bin rows per wave of k_dec_rows
-__global__ __launch_bounds__(256) void k_dec_rows(DecBatch db) {
+// ------------------------------------------------- inverse Lorenzo, pixels
+
+// The residuals travel as one byte a bin (res8), and every pass below reads
+// them as such: r + 128, or 0 with the residual in res (an escape).  A panel
+// is cut into bands of kDecTH bin rows.  q of a bin is the sum of every
+// residual above and left of it, so a band needs the column sums of the rows
+// above it (k_dec_cols reads the bytes once more for them, 1 byte a bin
+// against the 4 b^2 its pixels take) and nothing of its neighbours beside:
+// one wave walks it from left to right with the rows' carries in scalar
+// registers, takes all its rows' bytes of a strip at once and writes whole
+// lines of pixels.  Panels that one workgroup covers (k_dec_panel) take the
+// column sums through LDS instead and read the bytes once.  Any panel size
+// and dimension takes these passes; int32 residuals in HBM with a pass per
+// axis took 0.86 ms where this takes 0.43 on 128 frames of 8x512x1024 at b =
+// 2, and 1.95 ms against 0.56 on 250 frames of 32x185x388 in 3D.  What bounds
+// them is the pixels' stores: 5.0 TB/s on 8x512x1024, 4.9 on 32x185x388,
+// where a kernel that only stores reaches 5.3 to 5.7 in this order.
+
+// 0x80 in each byte of x that is zero, 0 elsewhere.
+__device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {
+  return ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
+}
+
+// Words at any address (global accesses take any alignment).
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+__device__ __forceinline__ uint32_t ld_any32(const uint8_t *p) {
+  return *(const RSZ_G u32_any *)p;
+}
+__device__ __forceinline__ uint32_t ld_any16(const uint8_t *p) {
+  return *(const RSZ_G u16_any *)p;
+}
+
+// Dimension 3: the residuals' inclusive prefix sum across the panels, in
+// place, after which each panel holds its 2D residuals.  A thread takes 4
+// consecutive bins of the panel plane through every panel, kPanelsAhead
+// panels' bytes loaded before any is stored.
+constexpr uint32_t kPanelsAhead = 8;
+__global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
   RSZ_DEC_FRAME(5);
-  const uint32_t row0 = (bid * 4 + (threadIdx.x >> 6)) * kDecRowsPerWave;
-  const int lane = threadIdx.x & 63;
-  const uint32_t nrows = dp.P * dp.Hb;
-  if (row0 >= nrows || !dec_ok(dp.status)) return;
-  const uint32_t Wb = dp.Wb;
-  if (Wb <= 256) {
-    // four consecutive bins per lane, the wave's rows all loaded first; per
-    // row the lanes' prefixes and one wave scan of their totals
-    int32_t v[kDecRowsPerWave][4];
-#pragma unroll
-    for (uint32_t rr = 0; rr < kDecRowsPerWave; ++rr)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t j = 4 * lane + t;
-        v[rr][t] = row0 + rr < nrows && j < Wb ? dp.res[(size_t)(row0 + rr) * Wb + j] : 0;
-      }
-    bool bad = false;
-#pragma unroll
-    for (uint32_t rr = 0; rr < kDecRowsPerWave; ++rr) {
-      if (row0 + rr >= nrows) break;
-      uint32_t x[4], sum = 0;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        bad |= v[rr][t] == kMark;
-        sum += (uint32_t)v[rr][t];
-        x[t] = sum;
-      }
-      const uint32_t incl = wave_inclusive_sum(sum);
-      const uint32_t before = incl - sum;
-      int32_t *r = dp.res + (size_t)(row0 + rr) * Wb;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t j = 4 * lane + t;
-        if (j < Wb) r[j] = (int32_t)(x[t] + before);
-      }
-    }
-    if (bad) corrupt(dp.status);
-    return;
-  }
+  const uint32_t plane = dp.Hb * dp.Wb, P = dp.P;
+  const uint32_t c = (bid * 256 + threadIdx.x) * 4;
+  if (c >= plane || !dec_ok(dp.status)) return;
+  const uint32_t n = min(4u, plane - c);
+  uint8_t *src = dp.res8 + c;
+  int32_t *res = dp.res + c;
+  uint32_t run[4] = {0u, 0u, 0u, 0u};
   bool bad = false;
-  for (uint32_t row = row0; row < min(row0 + kDecRowsPerWave, nrows); ++row) {
-    int32_t *r = dp.res + (size_t)row * Wb;
-    uint32_t carry = 0;
-    for (uint32_t j0 = 0; j0 < Wb; j0 += 64) {
-      const uint32_t j = j0 + lane;
-      uint32_t x = 0;
-      if (j < Wb) {
-        const int32_t v = r[j];
-        bad |= v == kMark;
-        x = (uint32_t)v;
+  for (uint32_t p0 = 0; p0 < P; p0 += kPanelsAhead) {
+    uint32_t w[kPanelsAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kPanelsAhead; ++k)
+      w[k] = ld_any32(src + (size_t)min(p0 + k, P - 1) * plane);
+#pragma unroll
+    for (uint32_t k = 0; k < kPanelsAhead; ++k) {
+      if (p0 + k >= P) break;
+      const size_t o = (size_t)(p0 + k) * plane;
+      uint32_t y = 0;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+        const uint32_t by = (w[k] >> (8 * t)) & 0xFFu;
+        int32_t r = (int32_t)by - 128;
+        if (by == 0 && t < n) {
+          r = *gm(res + o + t);
+          bad |= r == kMark;
+        }
+        run[t] += (uint32_t)r;
+        const bool small = run[t] + 127u < 255u;
+        y |= (small ? run[t] + 128u : 0u) << (8 * t);
+        if (!small && t < n) *gm(res + o + t) = (int32_t)run[t];
       }
-      x = wave_inclusive_sum(x) + carry;
-      if (j < Wb) r[j] = (int32_t)x;
-      carry = __builtin_amdgcn_readlane(x, 63);
+      if (n == 4) {
+        *(RSZ_G u32_any *)(src + o) = y;
+      } else {   // the plane's last bins: the bytes after them are another's
+        for (uint32_t t = 0; t < n; ++t) *gm(src + o + t) = (uint8_t)(y >> (8 * t));
+      }
     }
   }
   if (bad) corrupt(dp.status);
 }
 
-// One lane per bin column: inclusive prefix sum down the column.
-// The pixels of bin (I, J) of a panel whose first pixel is out get v:
-// rows [I*b, min(I*b + b, H)), columns [J*b, min(J*b + b, W)).  For b = 2 or 4
-// with W a multiple of b a bin's pixels of one row are an aligned float2 /
-// float4 (the frame is 16-byte aligned).
-__device__ __forceinline__ void fill_bin(float *out_, uint32_t H, uint32_t W, uint32_t b,
-                                         uint32_t I, uint32_t J, float v) {
-  RSZ_G float *out = gm(out_);
-  const uint32_t i0 = I * b, i1 = min(i0 + b, H), j0 = J * b;
-  if (b == 2 && W % 2 == 0) {
-    for (uint32_t i = i0; i < i1; ++i) *(RSZ_G f32x2 *)(out + (size_t)i * W + j0) = f32x2{v, v};
-  } else if (b == 4 && W % 4 == 0) {
-    for (uint32_t i = i0; i < i1; ++i)
-      *(RSZ_G f32x4 *)(out + (size_t)i * W + j0) = f32x4{v, v, v, v};
-  } else {
-    const uint32_t j1 = min(j0 + b, W);
-    for (uint32_t i = i0; i < i1; ++i)
-      for (uint32_t j = j0; j < j1; ++j) out[(size_t)i * W + j] = v;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_dec_cols(DecBatch db) {
-  RSZ_DEC_FRAME(8);
-  const uint32_t col = bid * 256 + threadIdx.x;
-  if (col >= dp.P * dp.Wb || !dec_ok(dp.status)) return;
-  const uint32_t p = col / dp.Wb, J = col - p * dp.Wb;
-  int32_t *r = dp.res + (size_t)p * dp.Hb * dp.Wb + J;
-  const size_t Wb = dp.Wb;
-  // dimension 2: q is final here, so its pixels are written at once (no
-  // expansion pass re-reads the residuals); dimension 3 stores q for the
-  // sum across the panels
-  const bool fill = dp.dim == 2;
-  float *out = dp.frame + (size_t)p * dp.H * dp.W;
-  const uint32_t H = dp.H, W = dp.W, b = dp.b;
-  const double step = dp.step;
-  auto put = [&](uint32_t I, uint32_t acc) {
-    if (fill) fill_bin(out, H, W, b, I, J, (float)((double)(int32_t)acc * step));
-    else r[I * Wb] = (int32_t)acc;
-  };
-  uint32_t acc = 0;
-  uint32_t I = 0;
-  // eight rows loaded before any is stored (a store would otherwise hold
-  // back the next load: the compiler cannot reorder them)
-  for (; I + 8 <= dp.Hb; I += 8) {
-    uint32_t v[8];
+// Dimension 1: the sum of each bin row (kDecRowsPerWave rows a wave).
+constexpr uint32_t kDecRowsPerWave = 4;
+__global__ __launch_bounds__(256) void k_dec_rowsum(DecBatch db) {
+  RSZ_DEC_FRAME(6);
+  const uint32_t row0 = (bid * 4 + (threadIdx.x >> 6)) * kDecRowsPerWave;
+  const int lane = threadIdx.x & 63;
+  const uint32_t nrows = dp.P * dp.Hb, Wb = dp.Wb;
+  if (row0 >= nrows || !dec_ok(dp.status)) return;
+  uint32_t sum[kDecRowsPerWave];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = (uint32_t)r[(I + k) * Wb];
+  for (uint32_t k = 0; k < kDecRowsPerWave; ++k) sum[k] = 0;
+  for (uint32_t j0 = 0; j0 < Wb; j0 += 256) {
+    const uint32_t j = j0 + 4 * lane, jc = min(j, Wb - 1);
+    const uint32_t n = j < Wb ? min(4u, Wb - j) : 0u;   // this lane's bins of the row
+    const uint32_t keep = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+    uint32_t w[kDecRowsPerWave];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      acc += v[k];
-      put(I + k, acc);
+    for (uint32_t k = 0; k < kDecRowsPerWave; ++k)
+      w[k] = ld_any32(dp.res8 + (size_t)min(row0 + k, nrows - 1) * Wb + jc);
+#pragma unroll
+    for (uint32_t k = 0; k < kDecRowsPerWave; ++k) {
+      const uint32_t x = w[k] & keep;
+      sum[k] = __builtin_amdgcn_sad_u8(x, 0u, sum[k]) - 128u * n;
+      for (uint32_t z = zero_bytes(x) & keep; z; z &= z - 1) {   // escapes
+        const uint32_t t = (uint32_t)__builtin_ctz(z) >> 3;
+        sum[k] += 128u + (uint32_t)*gm(dp.res + (size_t)min(row0 + k, nrows - 1) * Wb + j + t);
+      }
     }
   }
-  for (; I < dp.Hb; ++I) {
-    acc += (uint32_t)r[I * Wb];
-    put(I, acc);
+#pragma unroll
+  for (uint32_t k = 0; k < kDecRowsPerWave; ++k) {
+    const uint32_t tot = wave_inclusive_sum(sum[k]);
+    if (lane == 63 && row0 + k < nrows) *gm(dp.carry + row0 + k) = tot;
   }
 }
 
 // Dimension 1: the raster sequence continues across rows, so each row adds
-// the sum of every row before it.  One workgroup scans the row totals (the
-// last element of each row-scanned row) into exclusive carries.
+// the sum of every row before it.  One workgroup scans the row sums into
+// exclusive carries.
 __global__ __launch_bounds__(256) void k_dec_carry(DecBatch db) {
-  RSZ_DEC_FRAME(6);
+  RSZ_DEC_FRAME(7);
   __shared__ uint32_t s_w[4];
-  if (!dec_ok(dp.status)) return;
+  __shared__ int s_ok;
+  if (threadIdx.x == 0) s_ok = dec_ok(dp.status);
+  __syncthreads();
+  if (!s_ok) return;
   const uint32_t rows = dp.P * dp.Hb;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   uint32_t run = 0;
-  for (uint32_t r0 = 0; r0 < rows; r0 += 256) {
-    const uint32_t row = r0 + threadIdx.x;
-    uint32_t x = row < rows ? (uint32_t)dp.res[(size_t)row * dp.Wb + dp.Wb - 1] : 0u;
-    const uint32_t v = x;
+  for (uint32_t r0 = 0; r0 < rows; r0 += 1024) {
+    const uint32_t row = r0 + 4 * threadIdx.x;
+    uint32_t v[4], sum = 0;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d);
-      if (lane >= d) x += y;
-    }
+    for (uint32_t k = 0; k < 4; ++k) v[k] = row + k < rows ? *gm(dp.carry + row + k) : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) sum += v[k];
+    const uint32_t x = wave_inclusive_sum(sum);
     if (lane == 63) s_w[wv] = x;
     __syncthreads();
-    uint32_t before = run;
+    uint32_t before = run + x - sum;
     for (int i = 0; i < wv; ++i) before += s_w[i];
-    if (row < rows) dp.carry[row] = before + x - v;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      if (row + k < rows) *gm(dp.carry + row + k) = before;
+      before += v[k];
+    }
     run += s_w[0] + s_w[1] + s_w[2] + s_w[3];
     __syncthreads();
   }
 }
 
-// Dimension 1: adds each row's carry (one lane per bin).
-__global__ __launch_bounds__(256) void k_dec_rowadd(DecBatch db) {
-  RSZ_DEC_FRAME(7);
-  if (!dec_ok(dp.status)) return;
-  const uint64_t stride = (uint64_t)nblk * 256;
-  for (uint64_t g = (uint64_t)bid * 256 + threadIdx.x; g < dp.nbins; g += stride)
-    dp.res[g] = (int32_t)((uint32_t)dp.res[g] + dp.carry[g / dp.Wb]);
-}
-
-// Dimension 3: inclusive prefix sum across the panels (one lane per bin
-// position of the panel plane), after the 2D sums of each panel.
-__global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
-  RSZ_DEC_FRAME(9);
-  const uint32_t plane = dp.Hb * dp.Wb;
-  const uint32_t c = bid * 256 + threadIdx.x;
-  if (c >= plane || !dec_ok(dp.status)) return;
-  int32_t *r = dp.res + c;
-  uint32_t acc = 0;
-  for (uint32_t p = 0; p < dp.P; ++p) {
-    acc += (uint32_t)r[(size_t)p * plane];
-    r[(size_t)p * plane] = (int32_t)acc;
-  }
-}
-
-// One wave per bin row: each lane takes a bin, computes its value once and
-// writes it to the bin's b x b pixels (clipped at the panel edges), a raw
-// row at a time, so the wave's stores of a row are contiguous.
-__global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
-  RSZ_DEC_FRAME(16);
-  // s_v[lead + i]: residual i of the panel, lead = the panel's byte offset
-  // in its 16-byte line (the loads below are whole aligned lines)
-  __shared__ __align__(16) uint32_t s_v[kPanelBins + 32];
-  __shared__ uint32_t s_part[kPanelThreads];
-  __shared__ int s_ok, s_bad;
-  const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  // one read of the status for the whole workgroup (another panel may
-  // change it meanwhile), so every thread takes the same branch
-  if (t == 0) {
-    s_ok = dec_ok(dp.status);
-    s_bad = 0;
-  }
-  __syncthreads();
-  if (!s_ok) return;
-  const uint32_t Hb = dp.Hb, Wb = dp.Wb, n = Hb * Wb;
-  const RSZ_G int32_t *r = gm(dp.res + (size_t)bid * n);
-  // The panel's code bytes into LDS as residuals: aligned 16-byte loads, all
-  // of a thread's in flight at once (res8 is 256-byte aligned with 64 bytes
-  // to spare past the last bin, so the lines cover the panel and stay in
-  // the buffer).  A byte 0 (its residual in res) is marked and filled in a
-  // second pass, so that no load waits on another.
-  const uint8_t *p8 = dp.res8 + (size_t)bid * n;
-  const uint8_t *a8 = (const uint8_t *)((uintptr_t)p8 & ~(uintptr_t)15);
-  const uint32_t lead = (uint32_t)(p8 - a8), nw = (lead + n + 15) / 16;
-  uint32_t *sv = s_v + lead;
-  bool bad = false;
-  for (uint32_t w0 = 0; w0 < nw; w0 += 2 * kPanelThreads) {
-    uint4 v[2];
+// The column sums above each band, within its segment of bands, and the sums
+// of whole segments: one thread per segment and 4 bin columns, walking the
+// segment's rows a band at a time (its kDecTH loads in flight together).
+__global__ __launch_bounds__(256) void k_dec_cols(DecBatch db) {
+  RSZ_DEC_FRAME(8);
+  const uint32_t Wb = dp.Wb, Hb = dp.Hb, nq = (Wb + 3) / 4;
+  const uint32_t t = bid * 256 + threadIdx.x;
+  if (t >= dp.P * dp.nsegs * nq || !dec_ok(dp.status)) return;
+  const uint32_t ps = t / nq, J = (t - ps * nq) * 4;
+  const uint32_t p = ps / dp.nsegs, seg = ps - p * dp.nsegs;
+  const uint32_t n = min(4u, Wb - J), keep = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+  const uint32_t b0 = seg * dp.seg_bands, b1 = min(b0 + dp.seg_bands, dp.nbands);
+  const size_t row0 = (size_t)p * Hb;
+  const uint8_t *src = dp.res8 + row0 * Wb + J;
+  const int32_t *res = dp.res + row0 * Wb + J;
+  uint32_t run[4] = {0u, 0u, 0u, 0u};
+  auto put = [&](uint32_t *to) {
+    if (n == 4) *(RSZ_G u32x4a *)to = u32x4a{run[0], run[1], run[2], run[3]};
+    else
+      for (uint32_t k = 0; k < n; ++k) *gm(to + k) = run[k];
+  };
+  for (uint32_t band = b0; band < b1; ++band) {
+    if (band > b0) put(dp.colbase + ((size_t)p * dp.nbands + band) * Wb + J);
+    if (band + 1 == dp.nbands) return;   // nothing lies below the last band
+    uint32_t w[kDecTH], lo = 0, hi = 0, z = 0;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const uint32_t w = w0 + k * kPanelThreads + t;
-      v[k] = w < nw ? ld16(a8 + 16 * (size_t)w) : make_uint4(0x80808080u, 0x80808080u,
-                                                               0x80808080u, 0x80808080u);
+    for (uint32_t i = 0; i < kDecTH; ++i)
+      w[i] = ld_any32(src + (size_t)(band * kDecTH + i) * Wb);
+#pragma unroll
+    for (uint32_t i = 0; i < kDecTH; ++i) {   // bytes 0, 2 and 1, 3 in 16-bit fields
+      lo += w[i] & 0x00FF00FFu;
+      hi += (w[i] >> 8) & 0x00FF00FFu;
+      z |= zero_bytes(w[i]);
     }
+    run[0] += (lo & 0xFFFFu) - 128u * kDecTH;
+    run[1] += (hi & 0xFFFFu) - 128u * kDecTH;
+    run[2] += (lo >> 16) - 128u * kDecTH;
+    run[3] += (hi >> 16) - 128u * kDecTH;
+    if (z & keep) {   // escapes, counted as -128 above
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const uint32_t w = w0 + k * kPanelThreads + t;
-      if (w < nw) {
-        // bytes of this line inside the panel: [lo, hi)
-        const int32_t lo = max((int32_t)lead - (int32_t)(16 * w), 0);
-        const int32_t hi = min((int32_t)(lead + n) - (int32_t)(16 * w), 16);
-        const uint32_t inr = hi > lo ? ((hi == 16 ? 0xFFFFu : (1u << hi) - 1u) & ~((1u << lo) - 1u))
-                                     : 0u;
-        const uint32_t e[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-        uint32_t zm = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint32_t o[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t by = (e[q] >> (8 * j)) & 0xFFu;
-            zm |= (by == 0 ? 1u : 0u) << (4 * q + j);
-            o[j] = by ? (uint32_t)((int32_t)by - 128) : (uint32_t)kMark;
+      for (uint32_t i = 0; i < kDecTH; ++i)
+        for (uint32_t k = 0; k < n; ++k)
+          if (((w[i] >> (8 * k)) & 0xFFu) == 0) {
+            const uint32_t x = 128u + (uint32_t)*gm(res + (size_t)(band * kDecTH + i) * Wb + k);
+            run[0] += k == 0 ? x : 0u;
+            run[1] += k == 1 ? x : 0u;
+            run[2] += k == 2 ? x : 0u;
+            run[3] += k == 3 ? x : 0u;
           }
-          *(uint4 *)(s_v + 16 * w + 4 * q) = make_uint4(o[0], o[1], o[2], o[3]);
-        }
-        // escapes (byte 0): the residual (or the outlier mark) from res,
-        // by the thread that holds the byte (rare; no other thread reads
-        // these entries before the barrier below)
-        for (uint32_t zb = zm & inr; zb; zb &= zb - 1) {
-          const uint32_t e16 = (uint32_t)__builtin_ctz(zb);
-          const int32_t x = r[16 * w + e16 - lead];
-          bad |= x == kMark;
-          s_v[16 * w + e16] = (uint32_t)x;
-        }
+    }
+  }
+  put(dp.segtot + ((size_t)p * dp.nsegs + seg) * Wb + J);
+}
+
+// n pixels of value v from a pixel row's address.
+__device__ __forceinline__ void fill_px(RSZ_G float *o, uint32_t n, float v) {
+  uint32_t k = 0;
+  for (; k + 4 <= n; k += 4) *(RSZ_G f32x4a *)(o + k) = f32x4a{v, v, v, v};
+  if (n & 2) {
+    *(RSZ_G f32x2a *)(o + k) = f32x2a{v, v};
+    k += 2;
+  }
+  if (n & 1) o[k] = v;
+}
+
+// A wave's band, in registers: the bytes of kDecTH rows of S strips.  A lane
+// takes V consecutive bins of a strip of 64 V, so that its pixels of a row
+// are 16 bytes for b = 1, 2 and 4.  B: the bin factor, 0 for any other.
+template <int B>
+struct Band {
+  static constexpr int V = B == 1 ? 4 : (B == 2 ? 2 : 1);
+  static constexpr int S = B == 1 ? 2 : 4;
+  static constexpr int R = (int)kDecTH;
+  static constexpr int C = 4 / V;                 // rows packed in a word
+  static constexpr uint32_t kCols = 64 * V * S;   // bin columns of the strips
+  // signed bytes: the residuals, kEsc (code byte 0) an escape
+  uint32_t w[S][R / C];
+  bool esc;   // some byte of the wave is an escape (wave-uniform)
+  static constexpr int kEsc = -128;
+  // rows [0, nr) of the code bytes from src (row stride Wb), columns from j0,
+  // NS strips (0: ns); rows past nr and columns past the row hold residual 0
+  template <int NS>
+  __device__ __forceinline__ void load(const uint8_t *src, uint32_t Wb, uint32_t j0, int ns,
+                                       uint32_t nr, int lane) {
+    uint32_t z = 0;
+    // the strips in pairs, their loads in flight together
+#pragma unroll
+    for (int s = 0; s < (NS ? NS : S); ++s) {
+      if (!NS && s >= ns) continue;
+      const uint32_t J = j0 + (uint32_t)((64 * s + lane) * V), Jc = min(J, Wb - 1);
+      uint32_t keep = 0;   // the lane's bytes inside the row
+#pragma unroll
+      for (int v = 0; v < V; ++v) keep |= J + v < Wb ? 0xFFu << (8 * v) : 0u;
+      if constexpr (V == 1) keep |= keep << 8;
+      if constexpr (V <= 2) keep |= keep << 16;
+      uint32_t x[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const uint8_t *a = src + min((uint32_t)i, nr - 1) * Wb;
+        if constexpr (V == 4) x[i] = ld_any32(a + Jc);
+        else if constexpr (V == 2) x[i] = ld_any16(a + Jc);
+        else x[i] = *gm(a + Jc);
+      }
+#pragma unroll
+      for (int k = 0; k < R / C; ++k) {
+        uint32_t y = 0;
+#pragma unroll
+        for (int t = 0; t < C; ++t)
+          y |= ((uint32_t)(k * C + t) < nr ? x[k * C + t] : 0x80808080u >> (32 - 8 * V)) << (8 * V * t);
+        w[s][k] = (y ^ 0x80808080u) & keep;
+        z |= zero_bytes(w[s][k] ^ 0x80808080u);
+      }
+    }
+    esc = __ballot(z != 0) != 0;
+  }
+  __device__ __forceinline__ int32_t residual(int s, int i, int v) const {
+    return (int8_t)(w[s][i / C] >> (8 * ((i % C) * V + v)));
+  }
+};
+
+// Column sums of the band's strips into sum.
+template <int B, int NS>
+__device__ __forceinline__ void band_sums(const Band<B> &bd, const int32_t *res, uint32_t Wb,
+                                          int ns, int lane,
+                                          uint32_t (&sum)[Band<B>::S][Band<B>::V]) {
+  using D = Band<B>;
+#pragma unroll
+  for (int s = 0; s < (NS ? NS : D::S); ++s) {
+#pragma unroll
+    for (int v = 0; v < D::V; ++v) sum[s][v] = 0u;
+    if (!NS && s >= ns) continue;
+#pragma unroll
+    for (int i = 0; i < D::R; ++i)
+#pragma unroll
+      for (int v = 0; v < D::V; ++v) sum[s][v] += (uint32_t)bd.residual(s, i, v);
+    if (bd.esc) {   // escapes, counted as -128 above
+      const uint32_t J = (uint32_t)((64 * s + lane) * D::V);
+#pragma unroll
+      for (int i = 0; i < D::R; ++i)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          if (bd.residual(s, i, v) == D::kEsc)
+            sum[s][v] += 128u + (uint32_t)*gm(res + (size_t)i * Wb + J + v);
+    }
+  }
+}
+
+// What the row loop needs of the plan, in registers before it starts.
+struct EmitPlan {
+  uint32_t b, Wb, H, W;
+  double step;
+  const uint8_t *src;   // the band's first bin
+  const int32_t *res;
+  float *out;           // and its first pixel
+  uint32_t I0, nr;
+};
+
+// One row's q of the band's strips: r the residuals, acc the column sums
+// above (advanced past the row), carry the row's q left of the strips
+// (advanced past them).
+template <int B, int NS, bool D1>
+__device__ __forceinline__ void row_q(double step, int ns,
+                                      const int32_t (&r)[NS ? NS : Band<B>::S][Band<B>::V],
+                                      uint32_t (&acc)[Band<B>::S][Band<B>::V], uint32_t &carry,
+                                      float (&q)[NS ? NS : Band<B>::S][Band<B>::V]) {
+  using D = Band<B>;
+#pragma unroll
+  for (int s = 0; s < (NS ? NS : D::S); ++s) {
+    if (!NS && s >= ns) continue;
+    uint32_t x[D::V], sum = 0;
+#pragma unroll
+    for (int v = 0; v < D::V; ++v) {
+      acc[s][v] = D1 ? (uint32_t)r[s][v] : acc[s][v] + (uint32_t)r[s][v];
+      sum += acc[s][v];
+      x[v] = sum;
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    const uint32_t before = incl - sum + carry;
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+#pragma unroll
+    for (int v = 0; v < D::V; ++v) q[s][v] = (float)((double)(int32_t)(before + x[v]) * step);
+  }
+}
+
+// The pixels of bin row I (the panel's) from prow.  They leave in consecutive
+// stores, which complete each other's lines (a panel row is seldom whole
+// lines; strip by strip over a band, the pieces of a line left the L2 one by
+// one).
+template <int B, int NS>
+__device__ __forceinline__ void row_pixels(const EmitPlan &ep, uint32_t I, float *prow,
+                                           uint32_t j0, int ns, int lane,
+                                           const float (&q)[NS ? NS : Band<B>::S][Band<B>::V]) {
+  using D = Band<B>;
+  const uint32_t b = B ? (uint32_t)B : ep.b;
+  const uint32_t Wb = ep.Wb, W = ep.W;
+  const bool ragged = Wb % D::V != 0 || W % b != 0;   // some lane's pixels are cut by the edge
+  const uint32_t nrow = min(b, ep.H - I * b);
+  for (uint32_t d = 0; d < nrow; ++d, prow += W) {
+#pragma unroll
+    for (int s = 0; s < (NS ? NS : D::S); ++s) {
+      if (!NS && s >= ns) continue;
+      const uint32_t J = j0 + (uint32_t)((64 * s + lane) * D::V);
+      const float *e = q[s];
+      RSZ_G float *o = gm(prow) + J * b;
+      if ((J + D::V) * b <= W) {   // all of its bins' pixels lie in the panel
+        if constexpr (B == 1) *(RSZ_G f32x4a *)o = f32x4a{e[0], e[1], e[2], e[3]};
+        else if constexpr (B == 2) *(RSZ_G f32x4a *)o = f32x4a{e[0], e[0], e[1], e[1]};
+        else if constexpr (B == 3) *(RSZ_G f32x3a *)o = f32x3a{e[0], e[0], e[0]};
+        else if constexpr (B == 4) *(RSZ_G f32x4a *)o = f32x4a{e[0], e[0], e[0], e[0]};
+        else fill_px(o, b, e[0]);
+      }
+      if (ragged && s + 1 == (NS ? NS : ns) && (J + D::V) * b > W) {
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          if (J + v < Wb) fill_px(o + v * b, min(b, W - (J + v) * b), e[v]);
       }
     }
   }
-  if (bad) s_bad = 1;
-  __syncthreads();
-  if (s_bad) {
-    if (t == 0) corrupt(dp.status);
-    return;
+}
+
+// The q and the pixels of a band without escapes.  carry: lane i holds row
+// i's.  The loop loads nothing: loads and stores share one wait counter, so
+// a load's wait would wait for every store before it too, and the pixels of
+// a row would leave only when the row before had reached memory.
+template <int B, int NS, bool D1>
+__device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd, uint32_t j0,
+                                          int ns, int lane,
+                                          uint32_t (&acc)[Band<B>::S][Band<B>::V],
+                                          uint32_t &carry) {
+  using D = Band<B>;
+  constexpr int N = NS ? NS : D::S;
+  const uint32_t b = B ? (uint32_t)B : ep.b;
+#pragma unroll
+  for (int i = 0; i < D::R; ++i) {
+    if ((uint32_t)i >= ep.nr) continue;
+    int32_t r[N][D::V];
+    float q[N][D::V];
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+#pragma unroll
+      for (int v = 0; v < D::V; ++v) r[s][v] = bd.residual(s, i, v);
+    uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)carry, i);
+    row_q<B, NS, D1>(ep.step, ns, r, acc, c, q);
+    carry = lane == i ? c : carry;
+    row_pixels<B, NS>(ep, ep.I0 + i, ep.out + (size_t)i * b * ep.W, j0, ns, lane, q);
   }
-  // row sums: wave w takes rows w, w + 16, ...
-  for (uint32_t I = wave; I < Hb; I += kPanelThreads / 64) {
-    uint32_t carry = 0;
-    for (uint32_t j0 = 0; j0 < Wb; j0 += 64) {
-      const uint32_t j = j0 + lane;
-      uint32_t x = j < Wb ? sv[I * Wb + j] : 0u;
-      x = wave_inclusive_sum(x) + carry;
-      if (j < Wb) sv[I * Wb + j] = x;
-      carry = __builtin_amdgcn_readlane(x, 63);
-    }
-  }
-  __syncthreads();
-  // column sums: thread (g, J) = (t / Wb, t % Wb) takes bin column J over
-  // the g-th block of rows; the blocks' totals give each its carry
-  const uint32_t G = min(kPanelThreads / Wb, Hb), per = (Hb + G - 1) / G;
-  const uint32_t g = t / Wb, J = t - g * Wb;
-  const uint32_t I0 = min(g * per, Hb), I1 = min(I0 + per, Hb);
-  uint32_t part = 0;
-  if (g < G)
-    for (uint32_t I = I0; I < I1; ++I) part += sv[I * Wb + J];
-  s_part[t] = part;
-  __syncthreads();
-  float *out = dp.frame + (size_t)bid * dp.H * dp.W;
-  const uint32_t H = dp.H, W = dp.W, b = dp.b;
-  const double step = dp.step;
-  // Linear output (b = 1, 2 or 4 with rows of whole 16-byte groups and the
-  // frame 16-byte aligned, so the panel is a run of aligned float4): the
-  // bins' values go back into LDS, then the workgroup writes the panel's
-  // pixels in order, one float4 per thread and step, so that every store
-  // of a wave fills whole cache lines (stores by bin leave a line's pieces
-  // to different waves and times).  Otherwise each thread writes its bins'
-  // pixels.
-  const bool lin = (b == 1 || b == 2 || b == 4) && W % 4 == 0 && ((uintptr_t)out & 15) == 0;
-  if (g < G) {
-    uint32_t acc = 0;
-    for (uint32_t h = 0; h < g; ++h) acc += s_part[h * Wb + J];
-    for (uint32_t I = I0; I < I1; ++I) {
-      acc += sv[I * Wb + J];
-      const float v = (float)((double)(int32_t)acc * step);
-      if (lin) sv[I * Wb + J] = __float_as_uint(v);
-      else fill_bin(out, H, W, b, I, J, v);
-    }
-  }
-  if (!lin) return;
-  __syncthreads();
-  const uint32_t sh = b == 1 ? 0u : (b == 2 ? 1u : 2u), W4 = W / 4;
-  RSZ_G f32x4 *o4 = gm((f32x4 *)out);
-  auto pix4 = [&](const uint32_t *rowv) {
-    f32x4 v;
-    if (b == 4) {
-      v.x = v.y = v.z = v.w = __uint_as_float(rowv[0]);
-    } else if (b == 2) {
-      v.x = v.y = __uint_as_float(rowv[0]);
-      v.z = v.w = __uint_as_float(rowv[1]);
-    } else {
-      v = f32x4{__uint_as_float(rowv[0]), __uint_as_float(rowv[1]), __uint_as_float(rowv[2]),
-                __uint_as_float(rowv[3])};
-    }
-    return v;
+}
+
+// The same for a band with escapes (rare): row by row, the bytes read again
+// (one row ahead) and the residuals of the bytes 0 from res.  Returns
+// whether an outlier's mark is left.
+template <int B, bool D1>
+__device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, int ns, int lane,
+                                              uint32_t (&acc)[Band<B>::S][Band<B>::V],
+                                              uint32_t &carry) {
+  using D = Band<B>;
+  const uint32_t b = B ? (uint32_t)B : ep.b, Wb = ep.Wb;
+  uint32_t next[D::S];
+  auto load = [&](uint32_t i) {
+#pragma unroll
+    for (int s = 0; s < D::S; ++s)
+      if (s < ns) {
+        const uint32_t J = j0 + (uint32_t)((64 * s + lane) * D::V);
+        const uint8_t *a = ep.src + (size_t)min(i, ep.nr - 1) * Wb + min(J, Wb - 1);
+        if constexpr (D::V == 4) next[s] = ld_any32(a);
+        else if constexpr (D::V == 2) next[s] = ld_any16(a);
+        else next[s] = *gm(a);
+      }
   };
-  // A pass covers R whole pixel rows (R a multiple of b), thread t the
-  // float4 (t mod W4) of row t / W4: from pass to pass its LDS bin row and
-  // its output move by fixed steps, with no division per store.
-  uint32_t R = kPanelThreads / W4;
-  R -= R % b;
-  if (R > 0) {
-    const uint32_t r0 = t / W4, c4 = t - r0 * W4;
-    if (r0 < R) {
-      const uint32_t dv = (R >> sh) * Wb;
-      const size_t dO = (size_t)R * W4;
-      const uint32_t *rowv = sv + (r0 >> sh) * Wb + ((4 * c4) >> sh);
-      RSZ_G f32x4 *o = o4 + (size_t)r0 * W4 + c4;
-      for (uint32_t i = r0; i < H; i += R, rowv += dv, o += dO) *o = pix4(rowv);
+  bool bad = false;
+  load(0);
+#pragma unroll 1
+  for (uint32_t i = 0; i < ep.nr; ++i) {
+    int32_t r[D::S][D::V];
+    float q[D::S][D::V];
+#pragma unroll
+    for (int s = 0; s < D::S; ++s)
+      if (s < ns)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v) {
+          const uint32_t J = j0 + (uint32_t)((64 * s + lane) * D::V) + v;
+          r[s][v] = J < Wb ? (int32_t)((next[s] >> (8 * v)) & 0xFFu) - 128 : 0;
+          if (r[s][v] == D::kEsc) r[s][v] = *gm(ep.res + (size_t)i * Wb + J);
+        }
+    load(i + 1);
+#pragma unroll
+    for (int s = 0; s < D::S; ++s)
+      if (s < ns)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v) bad |= r[s][v] == kMark;
+    uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)carry, (int)i);
+    row_q<B, 0, D1>(ep.step, ns, r, acc, c, q);
+    carry = (uint32_t)lane == i ? c : carry;
+    row_pixels<B, 0>(ep, ep.I0 + i, ep.out + (size_t)i * b * ep.W, j0, ns, lane, q);
+  }
+  return bad;
+}
+
+__device__ __forceinline__ EmitPlan emit_plan(const DecodePlan &dp, uint32_t p, uint32_t I0,
+                                              uint32_t nr) {
+  EmitPlan ep;
+  ep.b = dp.b;
+  ep.Wb = dp.Wb;
+  ep.H = dp.H;
+  ep.W = dp.W;
+  ep.step = dp.step;
+  ep.src = dp.res8 + ((size_t)p * dp.Hb + I0) * dp.Wb;
+  ep.res = dp.res + ((size_t)p * dp.Hb + I0) * dp.Wb;
+  ep.out = dp.frame + ((size_t)p * dp.H + (size_t)I0 * dp.b) * dp.W;
+  ep.I0 = I0;
+  ep.nr = nr;
+  return ep;
+}
+
+// One wave's band of a panel of any size: strips group by group from left to
+// right, the column sums above from k_dec_cols.  D1: Lorenzo dimension 1
+// (each row continues the one before: only row sums, from the row's carry).
+template <int B, bool D1>
+__device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint32_t band,
+                                         int lane) {
+  using D = Band<B>;
+  const uint32_t Hb = dp.Hb, Wb = dp.Wb;
+  const uint32_t I0 = band * kDecTH, nr = min(kDecTH, Hb - I0);
+  const EmitPlan ep = emit_plan(dp, p, I0, nr);
+  const uint32_t seg = band / dp.seg_bands, nsegs = dp.nsegs;
+  const uint32_t *cb = D1 || band == seg * dp.seg_bands
+                           ? nullptr : dp.colbase + ((size_t)p * dp.nbands + band) * Wb;
+  const uint32_t *st = D1 ? nullptr : dp.segtot + (size_t)p * nsegs * Wb;
+  const bool marks = dp.dim != 3;   // (dimension 3: k_dec_panels looked)
+  int32_t *status = dp.status;
+  uint32_t carry = D1 ? *gm(dp.carry + (size_t)p * Hb + I0 + min((uint32_t)lane, nr - 1)) : 0u;
+  bool bad = false;
+  for (uint32_t j0 = 0; j0 < Wb; j0 += D::kCols) {
+    const int ns = (int)min((uint32_t)D::S, (Wb - j0 + 64 * D::V - 1) / (64 * D::V));
+    D bd;
+    bd.template load<0>(ep.src, Wb, j0, ns, nr, lane);
+    uint32_t acc[D::S][D::V];
+#pragma unroll
+    for (int s = 0; s < D::S; ++s) {
+#pragma unroll
+      for (int v = 0; v < D::V; ++v) acc[s][v] = 0;
+      if (D1 || s >= ns) continue;
+      const uint32_t J = j0 + (uint32_t)((64 * s + lane) * D::V);
+      for (uint32_t g = 0; g < seg; ++g)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          if (J + v < Wb) acc[s][v] += *gm(st + (size_t)g * Wb + J + v);
+      if (cb) {
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          if (J + v < Wb) acc[s][v] += *gm(cb + J + v);
+      }
+    }
+    if (bd.esc) bad |= band_emit_esc<B, D1>(ep, j0, ns, lane, acc, carry);
+    else if (!D1 && ns == D::S) band_emit<B, D::S, D1>(ep, bd, j0, ns, lane, acc, carry);
+    else band_emit<B, 0, D1>(ep, bd, j0, ns, lane, acc, carry);
+  }
+  if (bad && marks) corrupt(status);
+}
+
+__global__ __launch_bounds__(256) void k_dec_pixels(DecBatch db) {
+  RSZ_DEC_FRAME_AT(9, xcd_run());
+  const uint32_t it = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (it >= dp.P * dp.nbands || !dec_ok(dp.status)) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t p = it / dp.nbands, band = it - p * dp.nbands;
+  if (dp.dim == 1) {
+    switch (dp.b) {
+      case 1: dec_band<1, true>(dp, p, band, lane); break;
+      case 2: dec_band<2, true>(dp, p, band, lane); break;
+      case 3: dec_band<3, true>(dp, p, band, lane); break;
+      case 4: dec_band<4, true>(dp, p, band, lane); break;
+      default: dec_band<0, true>(dp, p, band, lane); break;
     }
   } else {
-    const FastDiv fW = fast_div(W);
-    for (uint32_t c = t; c < H * W4; c += kPanelThreads) {
-      const uint32_t i = fdiv(fW, 4 * c), j = 4 * c - i * W;
-      o4[c] = pix4(sv + (i >> sh) * Wb + (j >> sh));
+    switch (dp.b) {
+      case 1: dec_band<1, false>(dp, p, band, lane); break;
+      case 2: dec_band<2, false>(dp, p, band, lane); break;
+      case 3: dec_band<3, false>(dp, p, band, lane); break;
+      case 4: dec_band<4, false>(dp, p, band, lane); break;
+      default: dec_band<0, false>(dp, p, band, lane); break;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_dec_expand(DecBatch db) {
-  RSZ_DEC_FRAME(10);
-  const uint32_t brow = bid * 4 + (threadIdx.x >> 6);
-  if (brow >= dp.P * dp.Hb || !dec_ok(dp.status)) return;
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t p = brow / dp.Hb, I = brow - p * dp.Hb;
-  const int32_t *rb = dp.res + (size_t)brow * dp.Wb;
-  float *out = dp.frame + (size_t)p * dp.H * dp.W;
-  const double step = dp.step;
-  for (uint32_t J = lane; J < dp.Wb; J += 64)
-    fill_bin(out, dp.H, dp.W, dp.b, I, J, (float)((double)rb[J] * step));
+// Panels whose bands are at most the waves of a workgroup and whose rows one
+// group of strips holds (panel_fits): one workgroup per panel and a wave per
+// band, so the column sums above a band come through LDS and the bytes are
+// read once.
+__host__ __device__ inline bool panel_fits(const DecodePlan &dp) {
+  const uint32_t cols = dp.b == 1 ? Band<1>::kCols : (dp.b == 2 ? Band<2>::kCols : Band<0>::kCols);
+  return dp.dim != 1 && dp.nbands <= kDecPanelWaves && dp.Wb <= cols;
+}
+
+// Wave wv's band of panel p; every wave of the workgroup calls it (mine: the
+// panel has the band).  Returns whether the band holds escapes, its pixels
+// then left to the caller (acc: the column sums above).
+template <int B, int NS>
+__device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint32_t wv,
+                                             uint32_t *s_col, int lane,
+                                             uint32_t (&acc)[Band<B>::S][Band<B>::V]) {
+  using D = Band<B>;
+  const uint32_t Wb = ep.Wb;
+  D bd;
+  if (mine) {
+    bd.template load<NS>(ep.src, Wb, 0, NS, ep.nr, lane);
+    band_sums<B, NS>(bd, ep.res, Wb, NS, lane, acc);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int v = 0; v < D::V; ++v) {
+        const uint32_t J = (uint32_t)((64 * s + lane) * D::V + v);
+        if (J < Wb) s_col[wv * Wb + J] = acc[s][v];
+      }
+  }
+  __syncthreads();
+  if (!mine) return false;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int v = 0; v < D::V; ++v) acc[s][v] = 0;
+  for (uint32_t k = 0; k < wv; ++k)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int v = 0; v < D::V; ++v)
+        acc[s][v] += s_col[k * Wb + min((uint32_t)((64 * s + lane) * D::V + v), Wb - 1)];
+  // lanes past the row add nothing to its sums
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int v = 0; v < D::V; ++v)
+      if ((uint32_t)((64 * s + lane) * D::V + v) >= Wb) acc[s][v] = 0;
+  if (bd.esc) return true;
+  uint32_t carry = 0;
+  band_emit<B, NS, false>(ep, bd, 0, NS, lane, acc, carry);
+  return false;
+}
+
+template <int B>
+__device__ __forceinline__ void dec_panel(const DecodePlan &dp, uint32_t p, uint32_t wv,
+                                          uint32_t *s_col, int lane) {
+  using D = Band<B>;
+  const bool mine = wv < dp.nbands;
+  const uint32_t I0 = mine ? wv * kDecTH : 0u;
+  const EmitPlan ep = emit_plan(dp, p, I0, min(kDecTH, dp.Hb - I0));
+  const bool marks = dp.dim != 3;   // (dimension 3: k_dec_panels looked)
+  int32_t *status = dp.status;
+  const int ns = (int)((ep.Wb + 64 * D::V - 1) / (64 * D::V));
+  uint32_t acc[D::S][D::V];
+  bool esc = false;
+  switch (ns) {
+    case 1: esc = dec_panel_ns<B, 1>(ep, mine, wv, s_col, lane, acc); break;
+    case 2: esc = dec_panel_ns<B, 2>(ep, mine, wv, s_col, lane, acc); break;
+    case 3: if constexpr (D::S >= 3) esc = dec_panel_ns<B, 3>(ep, mine, wv, s_col, lane, acc); break;
+    default: if constexpr (D::S >= 4) esc = dec_panel_ns<B, 4>(ep, mine, wv, s_col, lane, acc); break;
+  }
+  if (esc) {
+    uint32_t carry = 0;
+    if (band_emit_esc<B, false>(ep, 0, ns, lane, acc, carry) && marks) corrupt(status);
+  }
+}
+
+// LDS: the bands' column sums.
+__global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
+  RSZ_DEC_FRAME_AT(10, xcd_run());
+  extern __shared__ __align__(16) uint32_t s_col[];
+  __shared__ int s_ok;
+  // one read of the status for the whole workgroup (another panel may
+  // change it meanwhile), so every thread takes the same branch
+  if (threadIdx.x == 0) s_ok = dec_ok(dp.status);
+  __syncthreads();
+  if (!s_ok) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  switch (dp.b) {
+    case 1: dec_panel<1>(dp, bid, wv, s_col, lane); break;
+    case 2: dec_panel<2>(dp, bid, wv, s_col, lane); break;
+    case 3: dec_panel<3>(dp, bid, wv, s_col, lane); break;
+    case 4: dec_panel<4>(dp, bid, wv, s_col, lane); break;
+    default: dec_panel<0>(dp, bid, wv, s_col, lane); break;
+  }
 }
 
 // ------------------------------------------------------- coded ROI windows
@@ -1171,19 +1444,16 @@ void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
   nb[3] = (dp.nchunks + 3) / 4;
   nb[4] = (dp.n_out + 255) / 256;
   // inverse Lorenzo: prefix sums along each axis the predictor spans
-  if (panel_in_lds(dp)) {
-    nb[16] = dp.P;   // k_dec_panel: rows, columns and pixels
-  } else {
-    nb[5] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
-    if (dp.dim == 1) {
-      nb[6] = 1;
-      nb[7] = std::min<uint32_t>((dp.nbins + 255) / 256, 1u << 16);
-    } else {
-      nb[8] = (dp.P * dp.Wb + 255) / 256;
-      if (dp.dim == 3) nb[9] = (dp.Hb * dp.Wb + 255) / 256;
-    }
+  if (dp.dim == 3) nb[5] = (dp.Hb * dp.Wb + 1023) / 1024;
+  if (panel_fits(dp)) {
+    nb[10] = dp.P;
+  } else if (dp.dim == 1) {
+    nb[6] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
+    nb[7] = 1;
+  } else if (dp.nbands > 1) {
+    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nsegs * ((dp.Wb + 3) / 4) + 255) / 256);
   }
-  if (dp.dim != 2) nb[10] = (dp.P * dp.Hb + 3) / 4;   // dimension 2: k_dec_cols
+  if (!nb[10]) nb[9] = (uint32_t)(((uint64_t)dp.P * dp.nbands + 3) / 4);
   if (dp.roi_coding) {
     nb[11] = 1;
     nb[12] = (dp.npeaks + 255) / 256;
@@ -1192,16 +1462,17 @@ void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
   nb[14] = nb[15] = (dp.npeaks + 3) / 4;   // a wave per window
 }
 
-#define RSZ_DLAUNCH(k, name, kern, block)                              \
+#define RSZ_DLAUNCH_S(k, name, kern, block, lds)                       \
   do {                                                                 \
     if (total[k]) {                                                    \
       prof_begin(name, s);                                             \
-      hipLaunchKernelGGL(kern, dim3(total[k]), dim3(block), 0, s, db); \
+      hipLaunchKernelGGL(kern, dim3(total[k]), dim3(block), lds, s, db); \
       prof_end(s);                                                     \
       hipError_t e_ = hipGetLastError();                               \
       if (e_ != hipSuccess) return e_;                                 \
     }                                                                  \
   } while (0)
+#define RSZ_DLAUNCH(k, name, kern, block) RSZ_DLAUNCH_S(k, name, kern, block, 0)
 
 hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStream_t s) {
   RSZ_DLAUNCH(0, "k_dec_tables", k_dec_tables, 256);
@@ -1209,13 +1480,12 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
   RSZ_DLAUNCH(2, "k_dec_runs", k_dec_runs, 256);
   RSZ_DLAUNCH(3, "k_dec_chunks", k_dec_chunks, 256);
   RSZ_DLAUNCH(4, "k_dec_outliers", k_dec_outliers, 256);
-  RSZ_DLAUNCH(5, "k_dec_rows", k_dec_rows, 256);
-  RSZ_DLAUNCH(6, "k_dec_carry", k_dec_carry, 256);
-  RSZ_DLAUNCH(7, "k_dec_rowadd", k_dec_rowadd, 256);
+  RSZ_DLAUNCH(5, "k_dec_panels", k_dec_panels, 256);
+  RSZ_DLAUNCH(6, "k_dec_rowsum", k_dec_rowsum, 256);
+  RSZ_DLAUNCH(7, "k_dec_carry", k_dec_carry, 256);
   RSZ_DLAUNCH(8, "k_dec_cols", k_dec_cols, 256);
-  RSZ_DLAUNCH(9, "k_dec_panels", k_dec_panels, 256);
-  RSZ_DLAUNCH(10, "k_dec_expand", k_dec_expand, 256);
-  RSZ_DLAUNCH(16, "k_dec_panel", k_dec_panel, 1024);
+  RSZ_DLAUNCH(9, "k_dec_pixels", k_dec_pixels, 256);
+  RSZ_DLAUNCH_S(10, "k_dec_panel", k_dec_panel, 64 * db.panel_waves, 4 * db.panel_lds);
   RSZ_DLAUNCH(11, "k_dec_roi_tables", k_dec_roi_tables, 64);
   RSZ_DLAUNCH(12, "k_dec_roi_decode", k_dec_roi_decode, 256);
   RSZ_DLAUNCH(13, "k_dec_roi_unpred", k_dec_roi_unpred, 256);
@@ -1224,7 +1494,53 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
   return hipSuccess;
 }
 
-uint64_t decode_tables_bytes() { return 4ull * kTabWords; }
-uint64_t decode_roi_tables_bytes() { return 4ull * kRoiTabWords; }
+// The bands of kDecTH bin rows and the segments of bands that k_dec_cols
+// walks.  Every segment of a panel is summed by threads of its own and a band
+// adds the segments above it, so a tall panel is split (8 bands, 128 rows, a
+// segment) but into at most 16, which bounds what a band adds.
+void decode_geometry(DecodePlan &dp) {
+  dp.nbands = (dp.Hb + kDecTH - 1) / kDecTH;
+  dp.seg_bands = std::max(8u, (dp.nbands + 15) / 16);
+  dp.nsegs = (dp.nbands + dp.seg_bands - 1) / dp.seg_bands;
+}
+
+// k_dec_panel's waves and LDS words: the most that a panel of the batch takes.
+void decode_panel_shape(DecBatch &db, const DecodePlan &dp) {
+  if (dp.init_status != RSZ_OK || !panel_fits(dp)) return;
+  db.panel_waves = std::max(db.panel_waves, dp.nbands);
+  db.panel_cols = std::max(db.panel_cols, dp.Wb);
+  db.panel_lds = db.panel_waves * db.panel_cols;
+}
+
+// A stream's workspace region from w (its buffers one after the other, each
+// on a 256-byte boundary; dp's pointers into it are set); returns its end.
+uint8_t *decode_region(DecodePlan &dp, uint8_t *w) {
+  auto take = [&](uint64_t bytes) {
+    uint8_t *at = w;
+    w += align_up(bytes, 256);
+    return at;
+  };
+  dp.res = (int32_t *)take(4ull * dp.nbins);
+  dp.res8 = take(dp.nbins + 64ull);
+  dp.status = (int32_t *)take(4);
+  dp.tables = (uint32_t *)take(4ull * kTabWords);
+  if (dp.dim == 1) {
+    dp.carry = (uint32_t *)take(4ull * dp.P * dp.Hb);
+  } else if (dp.nbands > 1 && !panel_fits(dp)) {
+    dp.colbase = (uint32_t *)take(4ull * dp.P * dp.nbands * dp.Wb);
+    dp.segtot = (uint32_t *)take(4ull * dp.P * dp.nsegs * dp.Wb);
+  }
+  if (dp.roi_coding) {
+    dp.roi_payload = (uint32_t *)take(4ull * dp.npeaks * dp.w * dp.w);
+    dp.roi_tables = (uint32_t *)take(4ull * kRoiTabWords);
+  }
+  // the Huffman words: in the stream, or expanded from the run section
+  dp.bits = (const uint32_t *)(dp.in + dp.off_bits);
+  if (dp.run_coding) {
+    dp.hbits = (uint32_t *)take(4 * ((dp.T + 31) / 32 + 2));
+    dp.bits = dp.hbits;
+  }
+  return w;
+}
 
 }  // namespace rsz

@@ -51,6 +51,11 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same at 4-byte aligned addresses (global accesses need no more).
+typedef float f32x2a __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x3a __attribute__((ext_vector_type(3), aligned(4)));
+typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ uint4 ld16(const void *p) {
   const u32x4 v = *gm((const u32x4 *)p);
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -231,12 +236,15 @@ struct DecodePlan {
   uint64_t off_peaks, off_roi, off_lens, off_oidx, off_ores, off_chunks, off_bits;
   const uint8_t *in;
   float *frame;
-  int32_t *res;         // nbins: residuals; for k_dec_panel's streams only those
-                        // whose code byte (res8) is 0
-  uint8_t *res8;        // nbins (+64): k_dec_panel's streams, r + 128 for
-                        // |r| <= 127, else 0 with r (or the outlier mark) in res
-  uint32_t *zcount;     // nchunks code-0 counts
-  uint32_t *carry;      // dim 1: P*Hb row carries
+  int32_t *res;         // nbins: the residuals whose code byte (res8) is 0
+  uint8_t *res8;        // nbins (+64): r + 128 for |r| <= 127, else 0 with r (or
+                        // the outlier mark) in res
+  uint32_t *carry;      // dim 1: P*Hb row sums, then the carries into the rows
+  uint32_t nbands, seg_bands, nsegs;   // bands of kDecTH bin rows of a panel, bands
+                                       // of a k_dec_cols segment, segments
+  uint32_t *colbase;    // dims 2, 3 (nbands > 1): per panel and band, the column
+                        // sums of its segment's rows above it (Wb a band)
+  uint32_t *segtot;     // and per panel and segment, the segment's column sums
   int32_t *status;      // one word
   uint32_t *tables;     // decode tables
   int32_t init_status;  // RSZ_OK, or the host's verdict on the stream (no other work)
@@ -245,12 +253,20 @@ struct DecodePlan {
 // Streams decoded together: every decoder kernel is launched once for all of
 // them, its workgroups numbered across the frames.  pre holds kDecKernels
 // prefix arrays of n + 1 entries, kernel K's per-frame workgroup counts.
-constexpr int kDecKernels = 17;
+constexpr int kDecKernels = 16;
+constexpr uint32_t kDecTH = 16;   // bin rows of a band (one wave)
+constexpr uint32_t kDecPanelWaves = 16;   // most waves of a k_dec_panel workgroup
 struct DecBatch {
   uint32_t n;
   const DecodePlan *plans;
   const uint32_t *pre;
+  uint32_t panel_waves, panel_cols, panel_lds;   // k_dec_panel's workgroups: waves, bin
+                                                 // columns, LDS words
 };
+void decode_panel_shape(DecBatch &db, const DecodePlan &dp);
+// Bands and segments of a plan whose bin geometry is set; its workspace region.
+void decode_geometry(DecodePlan &dp);
+uint8_t *decode_region(DecodePlan &dp, uint8_t *w);
 // Workgroups of each decoder kernel for one frame (0: not launched for it).
 void decode_blocks(const DecodePlan &dp, uint32_t *nb);
 // Launches the kernels with total[K] workgroups (the prefixes' last entries).
