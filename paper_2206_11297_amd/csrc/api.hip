@@ -1106,7 +1106,8 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     decode_geometry(dp);
     region[f] = decode_ws_bytes(dp);
     total += region[f];
-    rows = std::min<uint32_t>(rows, (uint32_t)align_up(p->height, p->bin));
+    rows = std::min<uint32_t>({rows, (uint32_t)align_up(p->height, p->bin),
+                               std::max(p->bin, kVerifyRows / p->bin * p->bin)});
     vf.x = d[f].frame;
     vf.y = frames_out ? frames_out[f] : nullptr;
     vf.peaks = (const int32_t *)d[f].peaks;
@@ -1132,6 +1133,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   uint64_t off = head;
   uint32_t dec_total[kDecKernels] = {0};
   uint64_t wgs = 0;
+  uint32_t mask_words = 0;
   for (uint32_t f = 0; f < n; ++f) {
     DecodePlan &dp = dps[f];
     VerifyFrame &vf = vfs[f];
@@ -1158,7 +1160,10 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
       dec_total[k] += nb[k];
     }
     vpre[f] = (uint32_t)wgs;
-    if (vf.valid) wgs += (uint64_t)vf.P * vf.chunks;
+    if (vf.valid) {
+      wgs += (uint64_t)vf.P * vf.chunks;
+      mask_words = std::max(mask_words, vf.rows * ((vf.W + 31) / 32));
+    }
     if (wgs > 0x7FFFFFFFull) return RSZ_ERR_ARG;
   }
   for (int k = 0; k < kDecKernels; ++k) pre[(size_t)k * (n + 1) + n] = dec_total[k];
@@ -1172,6 +1177,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   vr->vb.frames = (const VerifyFrame *)(ws + h_dp + h_pre);
   vr->vb.wg_prefix = (const uint32_t *)(ws + h_dp + h_pre + h_vf);
   vr->vb.total_wgs = (uint32_t)wgs;
+  vr->vb.mask_words = mask_words;
   for (uint32_t f = 0; f < n; ++f) decode_panel_shape(vr->db, dps[f]);
   vr->db.n = n;
   vr->db.plans = (const DecodePlan *)ws;

@@ -276,7 +276,8 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
 // streams decoded by the decoder kernels (their plans completed on the
 // device from the compression's totals), then every pixel checked against
 // the frame it came from.
-constexpr uint32_t kVerifyMaskWords = 8192;   // LDS ROI bitmap of a workgroup's rows
+constexpr uint32_t kVerifyMaskWords = 8192;   // most words of a workgroup's LDS ROI bitmap
+constexpr uint32_t kVerifyRows = 32;          // raw rows of a workgroup, where they fit
 constexpr uint32_t kVerifyOutlierBlocks = 16; // k_dec_outliers workgroups per frame
 struct VerifyFrame {
   const float *x;           // the frame
@@ -296,6 +297,7 @@ struct VerifyBatch {
   const VerifyFrame *frames;  // device
   const uint32_t *wg_prefix;  // device, n + 1: k_verify workgroups per frame
   uint32_t total_wgs;
+  uint32_t mask_words;        // most LDS words of a workgroup's ROI bitmap
 };
 hipError_t launch_verify_plan(const VerifyBatch &vb, hipStream_t s);
 hipError_t launch_verify_check(const VerifyBatch &vb, hipStream_t s);

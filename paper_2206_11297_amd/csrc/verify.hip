@@ -41,16 +41,129 @@ __global__ __launch_bounds__(256) void k_vplan(VerifyBatch vb) {
   dp->init_status = RSZ_OK;
 }
 
+// The mean of a bin's n included pixels.  S / n for n a power of two is S
+// times its reciprocal, bit for bit.
+__device__ __forceinline__ double bin_mean(double S, uint32_t n) {
+  if (n == 0) return 0.0;
+  if ((n & (n - 1)) == 0) return S * (1.0 / (double)n);
+  return S / (double)n;
+}
+
+// Whether pixel y of a bin (x: the frame's) fails its check.
+__device__ __forceinline__ bool pixel_fails(float x, float y, bool roi, double mean, double eb) {
+  const double yv = (double)y;
+  const double tol = eb + fabs(yv) * 0x1p-23 + fabs(mean) * 0x1p-40;
+  return roi ? __float_as_uint(y) != __float_as_uint(x) : !(fabs(yv - mean) <= tol);
+}
+
+struct VerifyRows {
+  const float *x, *y;        // the panel
+  const uint32_t *mask;      // the block's ROI bitmap, wpr words a row from row r0
+  uint32_t H, W, wpr, r0, mode;
+  double eb;
+};
+
+// Bin rows [Ia, Ib) in steps of 4 of a panel whose rows are whole aligned
+// 16-byte groups, b = 1, 2 or 4: a lane takes 4 columns of a bin row's b raw
+// rows, so its 4 / b bins are whole, kVerifyAhead such groups' loads in
+// flight together.  Failing pixels of this lane.
+constexpr int kVerifyAhead = 2;
+template <int B>
+__device__ __forceinline__ uint32_t verify_vec(const VerifyRows &v, uint32_t Ia, uint32_t Ib,
+                                               uint32_t lane) {
+  const uint32_t W4 = v.W / 4;
+  uint32_t bad = 0;
+  for (uint32_t I = Ia; I < Ib; I += 4) {
+    const uint32_t nrow = min((uint32_t)B, v.H - I * B);
+    for (uint32_t c0 = 0; c0 < W4; c0 += 64 * kVerifyAhead) {
+      f32x4 xv[kVerifyAhead][B], yv[kVerifyAhead][B];
+#pragma unroll
+      for (int u = 0; u < kVerifyAhead; ++u)
+#pragma unroll
+        for (int d = 0; d < B; ++d) {
+          const size_t g = (size_t)(I * B + min((uint32_t)d, nrow - 1)) * W4 +
+                           min(c0 + 64 * u + lane, W4 - 1);
+          xv[u][d] = *(gm((const f32x4 *)v.x) + g);
+          yv[u][d] = *(gm((const f32x4 *)v.y) + g);
+        }
+#pragma unroll
+      for (int u = 0; u < kVerifyAhead; ++u) {
+        const uint32_t c = c0 + 64 * u + lane;
+        if (c >= W4) continue;
+        uint32_t roi[B];
+#pragma unroll
+        for (int d = 0; d < B; ++d)
+          roi[d] = v.mask[(I * B + min((uint32_t)d, nrow - 1) - v.r0) * v.wpr + (c >> 3)] >>
+                   (4 * (c & 7));
+#pragma unroll
+        for (int e = 0; e < 4 / B; ++e) {
+          double S = 0.0;
+          uint32_t n = 0;
+#pragma unroll
+          for (int d = 0; d < B; ++d)
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+              const bool in = (uint32_t)d < nrow && (v.mode || !((roi[d] >> (e * B + k)) & 1u));
+              const double t = S + (double)xv[u][d][e * B + k];
+              S = in ? t : S;
+              n += in ? 1u : 0u;
+            }
+          const double mean = bin_mean(S, n);
+#pragma unroll
+          for (int d = 0; d < B; ++d)
+#pragma unroll
+            for (int k = 0; k < B; ++k)
+              bad += (uint32_t)d < nrow &&
+                     pixel_fails(xv[u][d][e * B + k], yv[u][d][e * B + k],
+                                 (roi[d] >> (e * B + k)) & 1u, mean, v.eb);
+        }
+      }
+    }
+  }
+  return bad;
+}
+
+// The same for any b and width, a lane on a bin.
+__device__ __forceinline__ uint32_t verify_any(const VerifyRows &v, uint32_t b, uint32_t Ia,
+                                               uint32_t Ib, uint32_t lane) {
+  const uint32_t Wb = (v.W + b - 1) / b;
+  uint32_t bad = 0;
+  for (uint32_t I = Ia; I < Ib; I += 4)
+    for (uint32_t J = lane; J < Wb; J += 64) {
+      const uint32_t ia = I * b, ie = min(ia + b, v.H), ja = J * b, je = min(ja + b, v.W);
+      double S = 0.0;
+      uint32_t n = 0;
+      for (uint32_t r = ia; r < ie; ++r)
+        for (uint32_t c = ja; c < je; ++c) {
+          const bool roi = (v.mask[(r - v.r0) * v.wpr + c / 32] >> (c & 31)) & 1u;
+          if (v.mode || !roi) {
+            S += (double)*gm(v.x + (size_t)r * v.W + c);
+            ++n;
+          }
+        }
+      const double mean = bin_mean(S, n);
+      for (uint32_t r = ia; r < ie; ++r)
+        for (uint32_t c = ja; c < je; ++c) {
+          const size_t g = (size_t)r * v.W + c;
+          const bool roi = (v.mask[(r - v.r0) * v.wpr + c / 32] >> (c & 31)) & 1u;
+          bad += pixel_fails(*gm(v.x + g), *gm(v.y + g), roi, mean, v.eb);
+        }
+    }
+  return bad;
+}
+
 // One workgroup per block of `rows` raw rows of a panel: the block's ROI
 // bitmap in LDS from the frame's peaks (the windows of Sec. IV, clipped to
-// the panel), then one thread per bin: the mean of the bin's pixels that
-// enter it (all of them, or those outside every window) in fp64, and each
-// pixel's check.  A background pixel passes when |y - mean| <= eb + |y|
-// 2^-23 + |mean| 2^-40: the bound, plus the float32 rounding of the stored
-// value and the rounding of the fp64 sums (taken here in another order than
-// the compressor's).
+// the panel), then its bin rows, a wave on every fourth: the mean of the
+// bin's pixels that enter it (all of them, or those outside every window) in
+// fp64, and each pixel's check.  A background pixel passes when |y - mean| <=
+// eb + |y| 2^-23 + |mean| 2^-40: the bound, plus the float32 rounding of the
+// stored value and the rounding of the fp64 sums (taken here in another
+// order than the compressor's).  Both frames are read once and HBM bounds it:
+// 48 frames of 8x512x1024 at b = 2 take 0.35 ms, 4.6 TB/s; one load a pixel
+// in blocks of 256 rows, which left 12 waves a CU, took 1.10 ms.
 __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
-  __shared__ uint32_t s_mask[kVerifyMaskWords];
+  extern __shared__ uint32_t s_mask[];
   __shared__ uint32_t s_f;
   if (threadIdx.x == 0) {
     uint32_t lo = 0, hi = vb.n;
@@ -87,37 +200,25 @@ __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
       }
   }
   __syncthreads();
-  const uint32_t Wb = (W + b - 1) / b, Ib0 = r0 / b, Ib1 = (r1 + b - 1) / b;
-  const float *x = vf.x + (size_t)p * H * W, *y = vf.y + (size_t)p * H * W;
-  const double eb = vf.eb;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t Ia = r0 / b + wv, Ib = (r1 + b - 1) / b;
+  VerifyRows v;
+  v.x = vf.x + (size_t)p * H * W;
+  v.y = vf.y + (size_t)p * H * W;
+  v.mask = s_mask;
+  v.H = H;
+  v.W = W;
+  v.wpr = wpr;
+  v.r0 = r0;
+  v.mode = vf.mode;
+  v.eb = vf.eb;
+  const bool vec = W % 4 == 0 && (((uintptr_t)v.x | (uintptr_t)v.y) & 15) == 0;
   uint32_t bad = 0;
-  for (uint32_t i = threadIdx.x; i < (Ib1 - Ib0) * Wb; i += 256) {
-    const uint32_t I = Ib0 + i / Wb, J = i % Wb;
-    const uint32_t ia = I * b, ie = min(ia + b, H), ja = J * b, je = min(ja + b, W);
-    double S = 0.0;
-    uint32_t n = 0;
-    for (uint32_t r = ia; r < ie; ++r)
-      for (uint32_t c = ja; c < je; ++c) {
-        const bool roi = (s_mask[(r - r0) * wpr + c / 32] >> (c & 31)) & 1u;
-        if (vf.mode || !roi) {
-          S += (double)x[(size_t)r * W + c];
-          ++n;
-        }
-      }
-    const double mean = n ? S / (double)n : 0.0;
-    for (uint32_t r = ia; r < ie; ++r)
-      for (uint32_t c = ja; c < je; ++c) {
-        const size_t g = (size_t)r * W + c;
-        const bool roi = (s_mask[(r - r0) * wpr + c / 32] >> (c & 31)) & 1u;
-        if (roi) {
-          bad += __float_as_uint(y[g]) != __float_as_uint(x[g]);
-        } else {
-          const double yv = (double)y[g];
-          const double tol = eb + fabs(yv) * 0x1p-23 + fabs(mean) * 0x1p-40;
-          bad += !(fabs(yv - mean) <= tol);
-        }
-      }
-  }
+  if (vec && b == 1) bad = verify_vec<1>(v, Ia, Ib, lane);
+  else if (vec && b == 2) bad = verify_vec<2>(v, Ia, Ib, lane);
+  else if (vec && b == 4) bad = verify_vec<4>(v, Ia, Ib, lane);
+  else bad = verify_any(v, b, Ia, Ib, lane);
   if (bad) atomicAdd(vf.bad, bad);
 }
 
@@ -140,7 +241,7 @@ hipError_t launch_verify_plan(const VerifyBatch &vb, hipStream_t s) {
 hipError_t launch_verify_check(const VerifyBatch &vb, hipStream_t s) {
   if (vb.total_wgs) {
     prof_begin("k_verify", s);
-    hipLaunchKernelGGL(k_verify, dim3(vb.total_wgs), dim3(256), 0, s, vb);
+    hipLaunchKernelGGL(k_verify, dim3(vb.total_wgs), dim3(256), 4 * vb.mask_words, s, vb);
     prof_end(s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
