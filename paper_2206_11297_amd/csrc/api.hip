@@ -1153,7 +1153,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     decode_blocks(dp, nb);
     // the outliers: a fixed number of workgroups (their count is known only
     // on the device), each striding over them
-    if (vf.valid) nb[4] = std::min<uint32_t>(kVerifyOutlierBlocks, (dp.nbins + 255) / 256);
+    if (vf.valid) nb[kDecOutliers] = std::min<uint32_t>(kVerifyOutlierBlocks, (dp.nbins + 255) / 256);
     for (int k = 0; k < kDecKernels; ++k) {
       pre[(size_t)k * (n + 1) + f] = dec_total[k];
       if ((uint64_t)dec_total[k] + nb[k] > 0x7FFFFFFFull) return RSZ_ERR_ARG;

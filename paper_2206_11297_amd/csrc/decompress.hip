@@ -8,11 +8,10 @@
 //                   canonical decode tables (11-bit single- and multi-symbol
 //                   lookup tables + per-length first codes); write the
 //                   status of a stream the host rejected.
-//   k_dec_run_zero  runs coded: clear the words the runs expand into.
-//   k_dec_runs      runs coded: one thread per chunk expands its Rice-coded
-//                   zero runs back into the Huffman bits (a word at a time),
-//                   checking parameters, offsets and that every one bit stays
-//                   inside its chunk.
+//   k_dec_runs      runs coded: one wave per chunk expands its Rice-coded
+//                   zero runs back into the Huffman bits, checking
+//                   parameters, offsets and that every one bit stays inside
+//                   its chunk.
 //   k_dec_chunks    one wave per 4096-symbol chunk, lanes on slices of its
 //                   bits (self-synchronising starts): Huffman decode to
 //                   residuals (runs of the one-bit residual-0 codeword 32 at
@@ -28,8 +27,9 @@
 //                   kDecTH bin rows.
 //   k_dec_pixels    one wave per band: column sums down the band, row sums
 //                   across it -> q, and every pixel float(q * 2eb).
-//   k_dec_roi_tables, k_dec_roi_decode, k_dec_roi_unpred  coded ROI: class
-//                   tables, per-window decode, inverse prediction.
+//   k_dec_roi_decode  coded ROI: class tables, then per window its values
+//                   and their inverse prediction (k_dec_roi_unpred for
+//                   windows larger than LDS holds).
 //   k_dec_roi       ROI windows restored from the payload bits, one wave
 //                   per window.
 //   k_dec_roi_check overlapping windows must agree on their shared pixels
@@ -155,7 +155,10 @@ __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
   for (uint32_t c = threadIdx.x; c < dp.nchunks; c += 256) {
     const uint32_t o = co[c];
     if (o > dp.T || (c == 0 && o != 0) || (c > 0 && o < co[c - 1])) s_bad = 1;
+    // the words that two chunks share, cleared for k_dec_runs
+    else if (dp.run_coding) dp.hbits[o >> 5] = 0u;
   }
+  if (dp.run_coding && threadIdx.x == 0) dp.hbits[dp.T >> 5] = 0u;
   __syncthreads();
   const bool complete = s_kraft == (1ull << kMaxLen);
   const bool single = s_used == 1 && s_kraft == (1ull << (kMaxLen - 1));
@@ -373,100 +376,170 @@ __device__ __forceinline__ uint32_t decode_run(BitWindow &win, uint64_t &pos, ui
 
 constexpr uint32_t kRunKMax = 20;
 
-__global__ __launch_bounds__(256) void k_dec_run_zero(DecBatch db) {
-  RSZ_DEC_FRAME(1);
-  const uint64_t n = (dp.T + 31) / 32 + 2;
-  for (uint64_t i = bid * 256ull + threadIdx.x; i < n; i += nblk * 256ull)
-    dp.hbits[i] = 0u;
-}
-
 // The 32 bits of words (n of them, zero beyond) from bit pos, MSB-first.
-__device__ __forceinline__ uint32_t peek_bits(const uint32_t *w, uint64_t n, uint64_t pos) {
-  const uint64_t i = pos >> 5;
-  const uint32_t s = (uint32_t)(pos & 31);
-  const uint32_t hi = i < n ? w[i] : 0u, lo = i + 1 < n ? w[i + 1] : 0u;
-  return s ? (hi << s) | (lo >> (32 - s)) : hi;
+__device__ __forceinline__ uint32_t peek_bits(const uint32_t *w, uint32_t n, uint32_t pos) {
+  const uint32_t i = pos >> 5, s = pos & 31;
+  const uint32_t hi = i < n ? *gm(w + i) : 0u, lo = i + 1 < n ? *gm(w + i + 1) : 0u;
+  return (uint32_t)((((uint64_t)hi << 32 | lo) << s) >> 32);
 }
 
-// Chunk c's codes occupy run bits [runoffs[c], runoffs[c + 1]): each is a
-// unary quotient q (ones closed by a zero) and k low bits, giving the zero
-// run before the chunk's next one bit.  A valid section has parameters <= 20
-// (zero padding), offsets from 0 that never decrease, a last offset whose
-// words end the stream exactly, codes that end exactly at the next offset,
-// and every one bit inside its chunk [chunk_off[c], chunk_off[c + 1]).
-// Reads stay inside the section once its size is checked; the loop ends
-// after at most one step per run bit.
+// A wave's words of run bits and of expanded Huffman bits in LDS; a chunk
+// with more works in global memory.
+constexpr uint32_t kRunIn = 512, kRunOut = 1024;
+
+// A wave's stretch of a bit section: staged (words from w0 in LDS, zero words
+// after them) or in the stream.
+struct BitSrc {
+  const uint32_t *lds, *words;
+  uint32_t w0, n;
+  bool staged;
+  __device__ __forceinline__ uint32_t peek(uint32_t pos) const {
+    if (!staged) return peek_bits(words, n, pos);
+    const uint32_t i = (pos >> 5) - w0;
+    return (uint32_t)((((uint64_t)lds[i] << 32 | lds[i + 1]) << (pos & 31)) >> 32);
+  }
+};
+
+// Run codes from pos while pos < lim: each is a unary quotient q (ones closed
+// by a zero) and k low bits, the zero run before the next one bit.  Leaves
+// pos at the first boundary >= lim and returns the Huffman bits they stand
+// for; inval when a code runs past rend.  Calls f(run) for each.
+template <class F>
+__device__ __forceinline__ uint64_t rice_codes(const BitSrc &src, uint32_t &pos, uint32_t lim,
+                                               uint32_t rend, uint32_t k, bool &inval, F f) {
+  uint64_t adv = 0;
+  while (pos < lim) {
+    uint64_t q = 0;
+    uint32_t x = src.peek(pos), n = ~x ? (uint32_t)__builtin_clz(~x) : 32u;
+    while (n == 32 && rend - pos > 32) {   // 32 ones and more to come
+      q += 32;
+      pos += 32;
+      x = src.peek(pos);
+      n = ~x ? (uint32_t)__builtin_clz(~x) : 32u;
+    }
+    // no closing zero, or no room for the low bits, before the chunk's end
+    if (n + 1 + k > rend - pos || n == 32) {
+      inval = true;
+      break;
+    }
+    q += n;
+    uint32_t low = 0;
+    if (k) low = n + 1 + k <= 32 ? (x << (n + 1)) >> (32 - k) : src.peek(pos + n + 1) >> (32 - k);
+    pos += n + 1 + k;
+    const uint64_t run = (q << k) | low;
+    f(run);
+    adv += run + 1;
+  }
+  return adv;
+}
+
+// One wave per chunk.  Chunk c's codes occupy run bits [runoffs[c],
+// runoffs[c + 1]), cut into 64 slices and decoded as k_dec_chunks decodes its
+// own (self-synchronising starts); a scan of the Huffman bits that the lanes'
+// codes stand for places their one bits, which are ORed into the chunk's
+// words in LDS and leave as whole words (the two that the chunks beside may
+// share by atomics, on words that k_dec_tables cleared).  One thread a chunk,
+// as before, waited for its own loads bit by bit: 0.55 against %%RUNS%% ms on
+// 250 CSPAD frames.  A valid section has parameters <= 20 (zero padding),
+// offsets from 0 that never decrease, a last offset whose words end the
+// stream exactly, codes that end exactly at the next offset, and every one
+// bit inside its chunk [chunk_off[c], chunk_off[c + 1]).  Reads stay inside
+// the section once its size is checked; every loop ends after at most one
+// step per run bit.
 __global__ __launch_bounds__(256) void k_dec_runs(DecBatch db) {
-  RSZ_DEC_FRAME(2);
-  const uint32_t c = bid * 256 + threadIdx.x;
+  RSZ_DEC_FRAME(1);
+  __shared__ uint32_t s_in[4][kRunIn + 2], s_out[4][kRunOut];
+  const int lane = threadIdx.x & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t c = bid * 4 + wv;
   if (c >= dp.nchunks || !dec_ok(dp.status)) return;
-  const uint8_t *kpar = dp.in + dp.off_run;
-  const uint32_t *ro = (const uint32_t *)(dp.in + dp.off_runoffs);
-  const uint64_t Trun = ro[dp.nchunks];
-  const uint64_t nrw = (Trun + 31) / 32;
-  bool bad = dp.off_runbits + 4 * nrw != dp.total || ro[0] != 0 || kpar[c] > kRunKMax;
+  const RSZ_G uint8_t *kpar = gm(dp.in + dp.off_run);
+  const RSZ_G uint32_t *ro = gm((const uint32_t *)(dp.in + dp.off_runoffs));
+  const RSZ_G uint32_t *co = gm((const uint32_t *)(dp.in + dp.off_chunks));
+  const uint32_t Trun = ro[dp.nchunks], r0 = ro[0];
+  const uint32_t k = kpar[c], rs = ro[c], rend = ro[c + 1];
+  const uint32_t start = co[c];
+  const uint32_t end = c + 1 < dp.nchunks ? co[c + 1] : (uint32_t)dp.T;   // T < 2^32
+  const uint64_t nrw = ((uint64_t)Trun + 31) / 32;
+  bool bad = dp.off_runbits + 4 * nrw != dp.total || r0 != 0 || k > kRunKMax;
   if (c + 1 == dp.nchunks)   // padding of the parameters
     for (uint64_t t = dp.nchunks; t < align_up(dp.nchunks, 4); ++t) bad |= kpar[t] != 0;
-  const uint32_t *co = (const uint32_t *)(dp.in + dp.off_chunks);
-  const uint64_t start = co[c], end = c + 1 < dp.nchunks ? co[c + 1] : dp.T;
-  uint64_t pos = ro[c];
-  const uint64_t rend = ro[c + 1];
-  bad |= start > end || end > dp.T || rend < pos || rend > Trun;
+  bad |= start > end || end > dp.T || rend < rs || rend > Trun;
   if (bad) {
-    corrupt(dp.status);
+    if (lane == 0) corrupt(dp.status);
     return;
   }
-  const uint32_t *rw = (const uint32_t *)(dp.in + dp.off_runbits);
-  const uint32_t k = kpar[c];
-  uint64_t b = start;   // next Huffman bit position
-  // the one bits of the current word gather in acc; a word wholly inside
-  // the chunk is this thread's alone (a plain store), the two it may share
-  // with the chunks beside it take an atomic OR
-  uint64_t cw = 0;
-  uint32_t acc = 0;
+  BitSrc src;
+  src.words = (const uint32_t *)(dp.in + dp.off_runbits);
+  src.n = (uint32_t)nrw;
+  src.lds = s_in[wv];
+  src.w0 = rs >> 5;
+  const uint32_t nin = (uint32_t)(((uint64_t)rend + 31) / 32) - src.w0;
+  src.staged = nin <= kRunIn;
+  if (src.staged)
+    for (uint32_t i = lane; i < nin + 2; i += 64)
+      s_in[wv][i] = i < nin ? *gm(src.words + src.w0 + i) : 0u;
+  const uint32_t ow0 = start >> 5;
+  const uint32_t nout = (uint32_t)(((uint64_t)end + 31) / 32) - ow0;
+  const bool sout = nout <= kRunOut;
+  if (sout)
+    for (uint32_t i = lane; i < nout; i += 64) s_out[wv][i] = 0u;
+  wave_sync();
+  const uint64_t len = rend - rs;
+  const uint32_t lim = lane == 63 ? rend : rs + (uint32_t)(len * (uint64_t)(lane + 1) / 64);
+  uint32_t from = rs + (uint32_t)(len * (uint64_t)lane / 64), pos = from;
+  uint64_t adv = 0;
+  bool converged = false, inv = false, last_ok = false;
+  for (int round = 0; round <= 64 && !converged; ++round) {
+    pos = from;
+    inv = false;
+    adv = rice_codes(src, pos, lim, rend, k, inv, [](uint64_t) {});
+    // a lane stuck on no code hands on no boundary (its next lane's slice)
+    const uint32_t stop = inv ? lim : pos;
+    const uint32_t prev = __shfl_up(stop, 1);
+    const bool changed = lane > 0 && prev != from;
+    converged = __ballot(changed) == 0;
+    if (!converged && lane > 0) from = prev;
+  }
+  last_ok = __shfl((int)(pos == rend), 63) != 0;
+  uint64_t tot;
+  const uint64_t ex = wave_exclusive_scan_u64(adv, tot);
+  bad = !converged || __ballot(inv) != 0 || !last_ok || tot > (uint64_t)(end - start);
+  if (bad) {
+    if (lane == 0) corrupt(dp.status);
+    return;
+  }
+  if (!sout) {   // the chunk's own words, cleared before any bit is set
+    for (uint32_t i = lane; i < nout; i += 64)
+      if ((i > 0 || !(start & 31)) && (i + 1 < nout || !(end & 31))) *gm(dp.hbits + ow0 + i) = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  }
+  uint32_t b = start + (uint32_t)ex;   // next Huffman bit
+  uint32_t cw = b >> 5, acc = 0;       // the one bits of word cw so far
   auto flush = [&]() {
     if (!acc) return;
-    if (cw * 32 >= start && cw * 32 + 32 <= end) dp.hbits[cw] = acc;
-    else atomicOr(&dp.hbits[cw], acc);
+    if (sout) atomicOr(&s_out[wv][cw - ow0], acc);
+    else atomicOr(dp.hbits + cw, acc);
   };
-  while (pos < rend) {
-    uint64_t q = 0;
-    for (;;) {   // the unary part, up to 32 bits a step
-      const uint32_t x = peek_bits(rw, nrw, pos);
-      const uint64_t avail = min<uint64_t>(32, rend - pos);
-      const uint64_t n = ~x ? (uint64_t)__builtin_clz(~x) : 32;   // leading ones
-      if (n < avail) {
-        q += n;
-        pos += n + 1;   // and the closing zero
-        break;
-      }
-      q += avail;
-      pos += avail;
-      // no closing zero before the chunk's end, or a run past the chunk
-      if (pos >= rend || b + (q << k) >= end) bad = true;
-      if (bad) break;
-    }
-    if (bad || pos + k > rend) {
-      bad = true;
-      break;
-    }
-    const uint64_t low = k ? peek_bits(rw, nrw, pos) >> (32 - k) : 0;
-    pos += k;
-    b += (q << k) | low;
-    if (b >= end) {
-      bad = true;
-      break;
-    }
+  pos = from;
+  rice_codes(src, pos, lim, rend, k, inv, [&](uint64_t run) {
+    b += (uint32_t)run;
     if ((b >> 5) != cw) {
       flush();
       cw = b >> 5;
       acc = 0;
     }
     acc |= 0x80000000u >> (b & 31);
-    b++;
+    ++b;
+  });
+  flush();
+  if (!sout) return;
+  wave_sync();
+  for (uint32_t i = lane; i < nout; i += 64) {
+    const uint32_t v = s_out[wv][i];
+    if ((i > 0 || !(start & 31)) && (i + 1 < nout || !(end & 31))) *gm(dp.hbits + ow0 + i) = v;
+    else if (v) atomicOr(dp.hbits + ow0 + i, v);
   }
-  if (bad) corrupt(dp.status);
-  else flush();
 }
 
 // One wave per chunk.  The chunk's bits split into 64 equal slices; lane i
@@ -480,7 +553,7 @@ __global__ __launch_bounds__(256) void k_dec_runs(DecBatch db) {
 // a last pass writes them.  A valid chunk decodes to exactly its symbol count
 // and ends exactly at the next chunk offset.
 __global__ __launch_bounds__(256) void k_dec_chunks(DecBatch db) {
-  RSZ_DEC_FRAME(3);
+  RSZ_DEC_FRAME(2);
   __shared__ uint2 s_multi[1 << kLutBits];
   __shared__ uint32_t s_first[kMaxLen + 1], s_count[kMaxLen + 1], s_offs[kMaxLen + 1];
   __shared__ uint16_t s_sorted[kNumSym];
@@ -561,7 +634,7 @@ __global__ __launch_bounds__(256) void k_dec_chunks(DecBatch db) {
 // every nblk-th block of 256 (a verification plan launches a fixed number
 // per frame, the outlier count being known only on the device).
 __global__ __launch_bounds__(256) void k_dec_outliers(DecBatch db) {
-  RSZ_DEC_FRAME(4);
+  RSZ_DEC_FRAME(3);
   if (!dec_ok(dp.status)) return;
   const uint32_t *oi = (const uint32_t *)(dp.in + dp.off_oidx);
   const int32_t *orr = (const int32_t *)(dp.in + dp.off_ores);
@@ -620,7 +693,7 @@ __device__ __forceinline__ uint32_t ld_any16(const uint8_t *p) {
 // panels' bytes loaded before any is stored.
 constexpr uint32_t kPanelsAhead = 8;
 __global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
-  RSZ_DEC_FRAME(5);
+  RSZ_DEC_FRAME(4);
   const uint32_t plane = dp.Hb * dp.Wb, P = dp.P;
   const uint32_t c = (bid * 256 + threadIdx.x) * 4;
   if (c >= plane || !dec_ok(dp.status)) return;
@@ -665,7 +738,7 @@ __global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
 // Dimension 1: the sum of each bin row (kDecRowsPerWave rows a wave).
 constexpr uint32_t kDecRowsPerWave = 4;
 __global__ __launch_bounds__(256) void k_dec_rowsum(DecBatch db) {
-  RSZ_DEC_FRAME(6);
+  RSZ_DEC_FRAME(5);
   const uint32_t row0 = (bid * 4 + (threadIdx.x >> 6)) * kDecRowsPerWave;
   const int lane = threadIdx.x & 63;
   const uint32_t nrows = dp.P * dp.Hb, Wb = dp.Wb;
@@ -702,7 +775,7 @@ __global__ __launch_bounds__(256) void k_dec_rowsum(DecBatch db) {
 // the sum of every row before it.  One workgroup scans the row sums into
 // exclusive carries.
 __global__ __launch_bounds__(256) void k_dec_carry(DecBatch db) {
-  RSZ_DEC_FRAME(7);
+  RSZ_DEC_FRAME(6);
   __shared__ uint32_t s_w[4];
   __shared__ int s_ok;
   if (threadIdx.x == 0) s_ok = dec_ok(dp.status);
@@ -737,7 +810,7 @@ __global__ __launch_bounds__(256) void k_dec_carry(DecBatch db) {
 // of whole segments: one thread per segment and 4 bin columns, walking the
 // segment's rows a band at a time (its kDecTH loads in flight together).
 __global__ __launch_bounds__(256) void k_dec_cols(DecBatch db) {
-  RSZ_DEC_FRAME(8);
+  RSZ_DEC_FRAME(7);
   const uint32_t Wb = dp.Wb, Hb = dp.Hb, nq = (Wb + 3) / 4;
   const uint32_t t = bid * 256 + threadIdx.x;
   if (t >= dp.P * dp.nsegs * nq || !dec_ok(dp.status)) return;
@@ -1094,7 +1167,7 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
 }
 
 __global__ __launch_bounds__(256) void k_dec_pixels(DecBatch db) {
-  RSZ_DEC_FRAME_AT(9, xcd_run());
+  RSZ_DEC_FRAME_AT(8, xcd_run());
   const uint32_t it = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (it >= dp.P * dp.nbands || !dec_ok(dp.status)) return;
   const int lane = threadIdx.x & 63;
@@ -1198,7 +1271,7 @@ __device__ __forceinline__ void dec_panel(const DecodePlan &dp, uint32_t p, uint
 
 // LDS: the bands' column sums.
 __global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
-  RSZ_DEC_FRAME_AT(10, xcd_run());
+  RSZ_DEC_FRAME_AT(9, xcd_run());
   extern __shared__ __align__(16) uint32_t s_col[];
   __shared__ int s_ok;
   // one read of the status for the whole workgroup (another panel may
@@ -1221,64 +1294,85 @@ __global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
 
 // Tables of the ROI class code: per length L the first canonical code, the
 // number of classes and where they start in the (length, class) order, then
-// that order.  The lengths must be a complete prefix code (or one class of
-// length 1), padding zero; no class at all when there is no window.
+// that order.
 constexpr int kRoiTabFirst = 0, kRoiTabCount = 33, kRoiTabBase = 66, kRoiTabSym = 99;
 constexpr int kRoiTabWords = 132;
 constexpr int kRoiLutBits = 10;   // k_dec_roi_decode: codes this short by one lookup
 
-__global__ __launch_bounds__(64) void k_dec_roi_tables(DecBatch db) {
-  RSZ_DEC_FRAME(11);
-  if (threadIdx.x != 0 || !dec_ok(dp.status)) return;
-  const uint8_t *lens = dp.in + dp.off_rsec;
-  uint32_t *t = dp.roi_tables;
+// Builds the tables in LDS by one wave (lane c holds class c's length).  The
+// lengths must be a complete prefix code (or one class of length 1), padding
+// zero; no class at all when there is no window.  Returns whether they are.
+__device__ __forceinline__ bool roi_tables(const DecodePlan &dp, uint32_t *t, int lane) {
+  const uint32_t L = lane < (int)kRoiLens ? *gm(dp.in + dp.off_rsec + lane) : 0u;
+  const bool cls = lane < kRoiClasses;
+  const bool wrong = cls ? L > (uint32_t)kMaxLen : L != 0;
+  if (__ballot(wrong)) return false;
+  uint32_t code = 0, n = 0, prev = 0;
   uint64_t kraft = 0;
-  int used = 0;
-  bool bad = false;
-  for (int c = 0; c < (int)kRoiLens; ++c) {
-    const uint32_t L = lens[c];
-    if (c >= kRoiClasses ? L != 0 : L > (uint32_t)kMaxLen) bad = true;
-    if (c < kRoiClasses && L && L <= (uint32_t)kMaxLen) {
-      kraft += 1ull << (kMaxLen - L);
-      used++;
+#pragma unroll 1
+  for (uint32_t l = 1; l <= (uint32_t)kMaxLen; ++l) {
+    const uint64_t m = __ballot(cls && L == l);
+    const uint32_t cnt = (uint32_t)__builtin_popcountll(m);
+    code = (code + prev) << 1;
+    if (lane == 0) {
+      t[kRoiTabFirst + l - 1] = code;
+      t[kRoiTabCount + l - 1] = cnt;
+      t[kRoiTabBase + l - 1] = n;
     }
-  }
-  if (dp.npeaks == 0) bad |= used != 0;
-  else bad |= !(kraft == (1ull << kMaxLen) || (used == 1 && kraft == (1ull << (kMaxLen - 1))));
-  if (bad) {
-    corrupt(dp.status);
-    return;
-  }
-  uint32_t code = 0, n = 0, prev_count = 0;
-  for (int L = 1; L <= kMaxLen; ++L) {
-    code = (code + prev_count) << 1;
-    uint32_t cnt = 0;
-    t[kRoiTabBase + L - 1] = n;
-    for (int c = 0; c < kRoiClasses; ++c)
-      if (lens[c] == L) t[kRoiTabSym + n + cnt++] = (uint32_t)c;
-    t[kRoiTabFirst + L - 1] = code;
-    t[kRoiTabCount + L - 1] = cnt;
+    if ((m >> lane) & 1u)
+      t[kRoiTabSym + n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1))] = (uint32_t)lane;
+    kraft += (uint64_t)cnt << (kMaxLen - l);
     n += cnt;
-    prev_count = cnt;
+    prev = cnt;
   }
+  if (dp.npeaks == 0) return n == 0;
+  return kraft == (1ull << kMaxLen) || (n == 1 && kraft == (1ull << (kMaxLen - 1)));
 }
 
-// One lane per window: decode its classes and raw bits into the zigzag
-// residuals, written as r (mod 2^32) to roi_payload.  A window must start at
-// its offset (the first at 0) and end exactly at the next offset, the last
-// at Troi.
+// Windows decoded by one wave, a lane each, into its LDS slice (w <= 48), or
+// into roi_payload, its prediction left to k_dec_roi_unpred.  Few lanes a
+// wave on purpose: a lane's values follow one another, so the windows want
+// waves of their own, and the more lanes share one the more often all wait
+// for one lane's next words.
+constexpr uint32_t kRoiWins = 8, kRoiSlice = 2368;
+constexpr uint32_t kRoiIn = 2368;   // words of a wave's windows' bits in LDS
+__host__ __device__ inline uint32_t roi_wins(uint32_t w) {
+  const uint32_t ww = w * w;
+  return ww <= kRoiSlice ? (kRoiSlice / ww < kRoiWins ? kRoiSlice / ww : kRoiWins) : kRoiWins;
+}
+__host__ __device__ inline bool roi_in_lds(uint32_t w) { return w * w <= kRoiSlice; }
+
+// The windows of a frame: classes and raw bits into the zigzag residuals r
+// (mod 2^32), then the prediction undone.  A window must start at its offset
+// (the first at 0) and end exactly at the next offset, the last at Troi.
+// With D = M - 2^31 (zero outside the window), D(u, v) = r + D(u-1, v) +
+// D(u, v-1) - D(u-1, v-1), so D is the 2D prefix sum of r: a wave scan along
+// each row plus the column sums kept per lane; M = D + 2^31 maps back to the
+// float bits.  The residuals stay in LDS on the way: stored to HBM value by
+// value, the loop's loads waited for its stores (0.32 ms + 0.03 for the
+// prediction + 0.09 for tables by one thread on 250 CSPAD frames, against
+// %%ROI%% together here).
 __global__ __launch_bounds__(256) void k_dec_roi_decode(DecBatch db) {
-  RSZ_DEC_FRAME(12);
-  // the frame's class tables in LDS, and a lookup of every code of at most
+  RSZ_DEC_FRAME(10);
+  // the frame's class tables, and a lookup of every code of at most
   // kRoiLutBits bits by the stream's next kRoiLutBits bits: class | L << 8
   // (0: a longer code, or none)
   __shared__ uint32_t s_t[kRoiTabWords];
   __shared__ uint16_t s_lut[1 << kRoiLutBits];
+  __shared__ uint32_t s_r[4][kRoiSlice], s_in[4][kRoiIn + 2];
   __shared__ int s_ok;
+  const int lane = threadIdx.x & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // one read of the status for the workgroup (a window may set it
   // meanwhile), so that every thread takes the same branch
-  if (threadIdx.x == 0) s_ok = dec_ok(dp.status);
-  for (uint32_t x = threadIdx.x; x < (uint32_t)kRoiTabWords; x += 256) s_t[x] = dp.roi_tables[x];
+  if (wv == 0) {
+    bool ok = dec_ok(dp.status);
+    if (ok && !roi_tables(dp, s_t, lane)) {
+      if (lane == 0) corrupt(dp.status);
+      ok = false;
+    }
+    if (lane == 0) s_ok = ok;
+  }
   __syncthreads();
   if (!s_ok) return;
   for (uint32_t x = threadIdx.x; x < (1u << kRoiLutBits); x += 256) {
@@ -1294,65 +1388,97 @@ __global__ __launch_bounds__(256) void k_dec_roi_decode(DecBatch db) {
     s_lut[x] = e;
   }
   __syncthreads();
-  const uint32_t k = bid * 256 + threadIdx.x;
-  if (k >= dp.npeaks) return;
-  const uint32_t *offs = (const uint32_t *)(dp.in + dp.off_roffs);
-  const uint32_t *words = (const uint32_t *)(dp.in + dp.off_rbits);
-  const uint64_t nwords = (dp.Troi + 31) / 32;
-  const uint64_t start = offs[k], end = k + 1 < dp.npeaks ? offs[k + 1] : dp.Troi;
-  if ((k == 0 && start != 0) || end < start || end > dp.Troi) {
-    corrupt(dp.status);
-    return;
-  }
-  const uint64_t ww = (uint64_t)dp.w * dp.w;
-  uint32_t *out = dp.roi_payload + k * ww;
-  uint64_t pos = start;
-  BitWindow win;   // the window's bits through registers, 4 words a load
-  win.init(words, nwords, start);
-  for (uint64_t e = 0; e < ww; ++e) {
-    const uint32_t peek = win.peek(pos);
-    const uint32_t hit = s_lut[peek >> (32 - kRoiLutBits)];
-    int cls = -1, L = 1;
-    if (hit) {
-      cls = (int)(hit & 0xFFu);
-      L = (int)(hit >> 8);
-    } else {
-      for (L = kRoiLutBits + 1; L <= kMaxLen; ++L) {
-        const uint32_t code = peek >> (32 - L);
-        const uint32_t cnt = s_t[kRoiTabCount + L - 1], first = s_t[kRoiTabFirst + L - 1];
-        if (cnt && code - first < cnt) {
-          cls = (int)s_t[kRoiTabSym + s_t[kRoiTabBase + L - 1] + (code - first)];
+  const uint32_t w = dp.w, ww = w * w, wins = roi_wins(w);
+  const bool lds = roi_in_lds(w);
+  const uint32_t k0 = (bid * 4 + wv) * wins;
+  const uint32_t k = k0 + (uint32_t)lane, kn = min(k0 + wins, dp.npeaks);
+  if (k0 >= kn) return;
+  // the wave's windows' bits lie one after the other: [first, last)
+  const RSZ_G uint32_t *offs = gm((const uint32_t *)(dp.in + dp.off_roffs));
+  const uint32_t Troi = (uint32_t)dp.Troi;   // <= 63 * 2^26
+  const uint32_t first = offs[k0], last = kn < dp.npeaks ? offs[kn] : Troi;
+  const bool sane = first <= last && last <= Troi;
+  BitSrc src;
+  src.words = (const uint32_t *)(dp.in + dp.off_rbits);
+  src.n = (uint32_t)(((uint64_t)Troi + 31) / 32);
+  src.lds = s_in[wv];
+  src.w0 = first >> 5;
+  const uint32_t nin = sane ? (uint32_t)(((uint64_t)last + 31) / 32) - src.w0 : 0u;
+  src.staged = nin <= kRoiIn;
+  if (src.staged)
+    for (uint32_t i = lane; i < nin + 2; i += 64)
+      s_in[wv][i] = i < nin ? *gm(src.words + src.w0 + i) : 0u;
+  wave_sync();
+  if (k < kn) {
+    const uint32_t start = offs[k], end = k + 1 < dp.npeaks ? offs[k + 1] : Troi;
+    bool bad = !sane || (k == 0 && start != 0) || start < first || end < start || end > last;
+    uint32_t *out = dp.roi_payload + (uint64_t)k * ww;
+    uint32_t *sl = s_r[wv] + (uint32_t)lane * ww;
+    if (!bad) {
+      uint32_t pos = start;
+      for (uint32_t e = 0; e < ww; ++e) {
+        if (pos >= end) {   // every value takes a bit at least
+          bad = true;
           break;
         }
+        const uint32_t peek = src.peek(pos);
+        const uint32_t hit = s_lut[peek >> (32 - kRoiLutBits)];
+        int cls = -1, L = 1;
+        if (hit) {
+          cls = (int)(hit & 0xFFu);
+          L = (int)(hit >> 8);
+        } else {
+          for (L = kRoiLutBits + 1; L <= kMaxLen; ++L) {
+            const uint32_t code = peek >> (32 - L);
+            const uint32_t cnt = s_t[kRoiTabCount + L - 1], first = s_t[kRoiTabFirst + L - 1];
+            if (cnt && code - first < cnt) {
+              cls = (int)s_t[kRoiTabSym + s_t[kRoiTabBase + L - 1] + (code - first)];
+              break;
+            }
+          }
+        }
+        const uint32_t extra = cls >= 2 ? (uint32_t)cls - 1 : 0u;
+        if (cls < 0 || (uint32_t)L + extra > end - pos) {
+          bad = true;
+          break;
+        }
+        pos += L;
+        uint32_t z = cls == 0 ? 0u : 1u;
+        if (extra) {
+          // the raw bits, from the same 32 bits where they reach
+          const uint32_t raw = L + extra <= 32 ? peek << L : src.peek(pos);
+          z = (1u << extra) | (raw >> (32 - extra));
+          pos += extra;
+        }
+        const uint32_t r = (z >> 1) ^ (0u - (z & 1u));
+        if (lds) sl[e] = r;
+        else *gm(out + e) = r;
       }
+      bad |= pos != end;
     }
-    if (cls < 0 || pos + L > end) {
-      corrupt(dp.status);
-      return;
-    }
-    pos += L;
-    uint32_t z = cls == 0 ? 0u : 1u;
-    if (cls >= 2) {
-      const uint32_t extra = (uint32_t)cls - 1;
-      if (pos + extra > end) {
-        corrupt(dp.status);
-        return;
-      }
-      z = (1u << extra) | (win.peek(pos) >> (32 - extra));
-      pos += extra;
-    }
-    out[e] = (z >> 1) ^ (0u - (z & 1u));
+    if (bad) corrupt(dp.status);
   }
-  if (pos != end) corrupt(dp.status);
+  if (!lds) return;
+  wave_sync();
+  for (uint32_t i = 0; k0 + i < kn; ++i) {
+    uint32_t *out = dp.roi_payload + (uint64_t)(k0 + i) * ww;
+    const uint32_t *sl = s_r[wv] + i * ww;
+    uint32_t col = 0;
+    for (uint32_t u = 0; u < w; ++u) {
+      const uint32_t x = (uint32_t)lane < w ? sl[u * w + lane] : 0u;
+      col += wave_inclusive_sum(x);   // D(u, v) = row prefix of row u + D(u - 1, v)
+      const uint32_t m = col + 0x80000000u;
+      if ((uint32_t)lane < w)
+        *gm(out + u * w + lane) = (m & 0x80000000u) ? (m & 0x7FFFFFFFu) : ~m;
+    }
+  }
 }
 
-// One wave per window: undo the prediction.  With D = M - 2^31 (zero outside
-// the window), D(u, v) = r + D(u-1, v) + D(u, v-1) - D(u-1, v-1), so D is the
-// 2D prefix sum of r: a wave scan along each row plus the column sums kept
-// per lane.  Then M = D + 2^31 maps back to the float bits.
+// The same for windows too large for LDS, whose residuals k_dec_roi_decode
+// left in roi_payload: one wave per window.
 constexpr int kRoiMaxChunks = 16;   // w <= 1023: 16 chunks of 64 columns
 __global__ __launch_bounds__(256) void k_dec_roi_unpred(DecBatch db) {
-  RSZ_DEC_FRAME(13);
+  RSZ_DEC_FRAME(11);
   const uint32_t k = bid * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
@@ -1421,13 +1547,13 @@ __device__ __forceinline__ bool roi_window(const DecodePlan &dp, uint32_t k, uin
 }
 
 __global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
-  RSZ_DEC_FRAME(14);
+  RSZ_DEC_FRAME(12);
   const uint32_t k = bid * 4 + (threadIdx.x >> 6);
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
   roi_window<false>(dp, k, threadIdx.x & 63);
 }
 __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
-  RSZ_DEC_FRAME(15);
+  RSZ_DEC_FRAME(13);
   const uint32_t k = bid * 4 + (threadIdx.x >> 6);
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
   if (roi_window<true>(dp, k, threadIdx.x & 63)) corrupt(dp.status);
@@ -1437,29 +1563,28 @@ void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
   for (int k = 0; k < kDecKernels; ++k) nb[k] = 0;
   nb[0] = 1;   // k_dec_tables writes every frame's status
   if (dp.init_status != RSZ_OK) return;
-  if (dp.run_coding) {
-    nb[1] = (uint32_t)std::min<uint64_t>(((dp.T + 31) / 32 + 2 + 255) / 256, 1u << 16);
-    nb[2] = (dp.nchunks + 255) / 256;
-  }
-  nb[3] = (dp.nchunks + 3) / 4;
-  nb[4] = (dp.n_out + 255) / 256;
+  if (dp.run_coding) nb[1] = (dp.nchunks + 3) / 4;
+  nb[2] = (dp.nchunks + 3) / 4;
+  nb[kDecOutliers] = (dp.n_out + 255) / 256;
   // inverse Lorenzo: prefix sums along each axis the predictor spans
-  if (dp.dim == 3) nb[5] = (dp.Hb * dp.Wb + 1023) / 1024;
+  if (dp.dim == 3) nb[4] = (dp.Hb * dp.Wb + 1023) / 1024;
   if (panel_fits(dp)) {
-    nb[10] = dp.P;
-  } else if (dp.dim == 1) {
-    nb[6] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
-    nb[7] = 1;
-  } else if (dp.nbands > 1) {
-    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nsegs * ((dp.Wb + 3) / 4) + 255) / 256);
+    nb[9] = dp.P;
+  } else {
+    if (dp.dim == 1) {
+      nb[5] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
+      nb[6] = 1;
+    } else if (dp.nbands > 1) {
+      nb[7] = (uint32_t)(((uint64_t)dp.P * dp.nsegs * ((dp.Wb + 3) / 4) + 255) / 256);
+    }
+    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nbands + 3) / 4);
   }
-  if (!nb[10]) nb[9] = (uint32_t)(((uint64_t)dp.P * dp.nbands + 3) / 4);
   if (dp.roi_coding) {
-    nb[11] = 1;
-    nb[12] = (dp.npeaks + 255) / 256;
-    nb[13] = (dp.npeaks + 3) / 4;
+    const uint32_t wins = 4 * roi_wins(dp.w);
+    nb[10] = std::max(1u, (dp.npeaks + wins - 1) / wins);   // (no window: the lengths' check)
+    if (!roi_in_lds(dp.w)) nb[11] = (dp.npeaks + 3) / 4;
   }
-  nb[14] = nb[15] = (dp.npeaks + 3) / 4;   // a wave per window
+  nb[12] = nb[13] = (dp.npeaks + 3) / 4;   // a wave per window
 }
 
 #define RSZ_DLAUNCH_S(k, name, kern, block, lds)                       \
@@ -1476,21 +1601,19 @@ void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
 
 hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStream_t s) {
   RSZ_DLAUNCH(0, "k_dec_tables", k_dec_tables, 256);
-  RSZ_DLAUNCH(1, "k_dec_run_zero", k_dec_run_zero, 256);
-  RSZ_DLAUNCH(2, "k_dec_runs", k_dec_runs, 256);
-  RSZ_DLAUNCH(3, "k_dec_chunks", k_dec_chunks, 256);
-  RSZ_DLAUNCH(4, "k_dec_outliers", k_dec_outliers, 256);
-  RSZ_DLAUNCH(5, "k_dec_panels", k_dec_panels, 256);
-  RSZ_DLAUNCH(6, "k_dec_rowsum", k_dec_rowsum, 256);
-  RSZ_DLAUNCH(7, "k_dec_carry", k_dec_carry, 256);
-  RSZ_DLAUNCH(8, "k_dec_cols", k_dec_cols, 256);
-  RSZ_DLAUNCH(9, "k_dec_pixels", k_dec_pixels, 256);
-  RSZ_DLAUNCH_S(10, "k_dec_panel", k_dec_panel, 64 * db.panel_waves, 4 * db.panel_lds);
-  RSZ_DLAUNCH(11, "k_dec_roi_tables", k_dec_roi_tables, 64);
-  RSZ_DLAUNCH(12, "k_dec_roi_decode", k_dec_roi_decode, 256);
-  RSZ_DLAUNCH(13, "k_dec_roi_unpred", k_dec_roi_unpred, 256);
-  RSZ_DLAUNCH(14, "k_dec_roi", k_dec_roi, 256);
-  RSZ_DLAUNCH(15, "k_dec_roi_check", k_dec_roi_check, 256);
+  RSZ_DLAUNCH(1, "k_dec_runs", k_dec_runs, 256);
+  RSZ_DLAUNCH(2, "k_dec_chunks", k_dec_chunks, 256);
+  RSZ_DLAUNCH(kDecOutliers, "k_dec_outliers", k_dec_outliers, 256);
+  RSZ_DLAUNCH(4, "k_dec_panels", k_dec_panels, 256);
+  RSZ_DLAUNCH(5, "k_dec_rowsum", k_dec_rowsum, 256);
+  RSZ_DLAUNCH(6, "k_dec_carry", k_dec_carry, 256);
+  RSZ_DLAUNCH(7, "k_dec_cols", k_dec_cols, 256);
+  RSZ_DLAUNCH(8, "k_dec_pixels", k_dec_pixels, 256);
+  RSZ_DLAUNCH_S(9, "k_dec_panel", k_dec_panel, 64 * db.panel_waves, 4 * db.panel_lds);
+  RSZ_DLAUNCH(10, "k_dec_roi_decode", k_dec_roi_decode, 256);
+  RSZ_DLAUNCH(11, "k_dec_roi_unpred", k_dec_roi_unpred, 256);
+  RSZ_DLAUNCH(12, "k_dec_roi", k_dec_roi, 256);
+  RSZ_DLAUNCH(13, "k_dec_roi_check", k_dec_roi_check, 256);
   return hipSuccess;
 }
 
@@ -1530,10 +1653,7 @@ uint8_t *decode_region(DecodePlan &dp, uint8_t *w) {
     dp.colbase = (uint32_t *)take(4ull * dp.P * dp.nbands * dp.Wb);
     dp.segtot = (uint32_t *)take(4ull * dp.P * dp.nsegs * dp.Wb);
   }
-  if (dp.roi_coding) {
-    dp.roi_payload = (uint32_t *)take(4ull * dp.npeaks * dp.w * dp.w);
-    dp.roi_tables = (uint32_t *)take(4ull * kRoiTabWords);
-  }
+  if (dp.roi_coding) dp.roi_payload = (uint32_t *)take(4ull * dp.npeaks * dp.w * dp.w);
   // the Huffman words: in the stream, or expanded from the run section
   dp.bits = (const uint32_t *)(dp.in + dp.off_bits);
   if (dp.run_coding) {

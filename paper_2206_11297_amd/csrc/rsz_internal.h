@@ -225,7 +225,6 @@ struct DecodePlan {
   uint64_t Troi;
   uint64_t off_rsec, off_roffs, off_rbits;   // coded ROI section
   uint32_t *roi_payload;                      // coded ROI: npeaks*w*w decoded words
-  uint32_t *roi_tables;                       // coded ROI: decode tables
   uint32_t run_coding;                        // run section instead of the bitstream:
   uint64_t off_run, off_runoffs, off_runbits; // parameters, offsets, run bits
   const uint32_t *bits;                       // the Huffman words (stream or hbits)
@@ -253,7 +252,7 @@ struct DecodePlan {
 // Streams decoded together: every decoder kernel is launched once for all of
 // them, its workgroups numbered across the frames.  pre holds kDecKernels
 // prefix arrays of n + 1 entries, kernel K's per-frame workgroup counts.
-constexpr int kDecKernels = 16;
+constexpr int kDecKernels = 14, kDecOutliers = 3;
 constexpr uint32_t kDecTH = 16;   // bin rows of a band (one wave)
 constexpr uint32_t kDecPanelWaves = 16;   // most waves of a k_dec_panel workgroup
 struct DecBatch {

@@ -1,0 +1,86 @@
+"""GPU parity of the run and ROI decoders at the sizes where they change
+course, bit for bit against the oracle: chunks of few and many Huffman and run
+bits (past the words a wave keeps in LDS), residuals 0 alone (no run code at
+all) and long zero runs (quotients of many words), a partial last chunk;
+windows around the largest that LDS holds (48), one lane's worth of windows
+and one more, and no window."""
+import numpy as np
+import pytest
+
+from oracle import rsz_oracle as O
+from paper_2206_11297_amd import rsz, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _decode(host):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a ROCm GPU")
+    D = rsz.DecodeBatch([torch.from_numpy(s).cuda() for s in host])
+    D.run()
+    torch.cuda.synchronize()
+    status = D.status.cpu().tolist()
+    for k, s in enumerate(host):
+        st, y = O.decompress(s)
+        assert status[k] == st, k
+        if st == 0:
+            np.testing.assert_array_equal(D.frames[k].cpu().numpy().view(np.uint32),
+                                          y.view(np.uint32), err_msg=str(k))
+
+
+def _spread(shape, codes, seed):
+    """A frame at b = 1, eb = 0.5 whose residuals take about `codes` values."""
+    rng = np.random.default_rng(seed)
+    f = np.zeros(shape, np.float32)
+    f[:, :, ::2] = rng.integers(-codes // 2, codes // 2 + 1, f[:, :, ::2].shape)
+    return f
+
+
+def _run_streams():
+    frames = [np.zeros((1, 64, 128), np.float32), np.zeros((1, 64, 64), np.float32)]
+    frames[1][0, 40, 3] = 9.0                      # one run of thousands of zeros
+    lone = np.zeros((1, 300, 100), np.float32)     # long runs, k = 0 and larger
+    lone[0, ::37, ::31] = 4.0
+    frames.append(lone)
+    frames += [_spread((1, 65, 64), 2, 1), _spread((2, 64, 96), 30, 2),
+               _spread((1, 128, 97), 900, 3), _spread((1, 90, 91), 100000, 4)]
+    out = []
+    for f in frames:
+        for dim in (1, 2, 3):
+            st, s, _ = O.compress(O.params(*f.shape, 3, 1, 0.5, 0, dim, 0, 1), f,
+                                  np.zeros((0, 3), np.int32))
+            assert st == O.OK
+            out.append(s)
+    return out
+
+
+def test_run_chunks():
+    _decode(_run_streams())
+
+
+def test_run_chunks_corrupt():
+    rng = np.random.default_rng(17)
+    host = []
+    for s in _run_streams():
+        for t in range(4):
+            c = s.copy()
+            for _ in range(1 + t):
+                c[int(rng.integers(80, c.size))] ^= np.uint8(1 << int(rng.integers(0, 8)))
+            host.append(c)
+    _decode(host)
+
+
+@pytest.mark.parametrize("w,n", [(1, 40), (17, 0), (17, 8), (17, 33), (25, 5), (31, 3), (33, 9),
+                                 (48, 2), (49, 2), (70, 9)])
+def test_roi_windows(w, n):
+    f, pk = synth.tiny_case(900 + w + n, (2, 90, 120), n, "normal", scale=50.0)
+    st, s, _ = O.compress(O.params(2, 90, 120, w, 2, 1.0, 0, 2, 1, 0), f, pk)
+    assert st == O.OK
+    host = [s]
+    rng = np.random.default_rng(w * 100 + n)
+    for t in range(6):
+        c = s.copy()
+        c[int(rng.integers(80, c.size))] ^= np.uint8(1 << int(rng.integers(0, 8)))
+        host.append(c)
+    _decode(host)
