@@ -439,7 +439,7 @@ __device__ __forceinline__ uint64_t rice_codes(const BitSrc &src, uint32_t &pos,
 // codes stand for places their one bits, which are ORed into the chunk's
 // words in LDS and leave as whole words (the two that the chunks beside may
 // share by atomics, on words that k_dec_tables cleared).  One thread a chunk,
-// as before, waited for its own loads bit by bit: 0.55 against %%RUNS%% ms on
+// as before, waited for its own loads bit by bit: 0.55 against 0.09 ms on
 // 250 CSPAD frames.  A valid section has parameters <= 20 (zero padding),
 // offsets from 0 that never decrease, a last offset whose words end the
 // stream exactly, codes that end exactly at the next offset, and every one
@@ -1351,7 +1351,7 @@ __host__ __device__ inline bool roi_in_lds(uint32_t w) { return w * w <= kRoiSli
 // float bits.  The residuals stay in LDS on the way: stored to HBM value by
 // value, the loop's loads waited for its stores (0.32 ms + 0.03 for the
 // prediction + 0.09 for tables by one thread on 250 CSPAD frames, against
-// %%ROI%% together here).
+// 0.12 together here).
 __global__ __launch_bounds__(256) void k_dec_roi_decode(DecBatch db) {
   RSZ_DEC_FRAME(10);
   // the frame's class tables, and a lookup of every code of at most
@@ -1414,7 +1414,43 @@ __global__ __launch_bounds__(256) void k_dec_roi_decode(DecBatch db) {
     bool bad = !sane || (k == 0 && start != 0) || start < first || end < start || end > last;
     uint32_t *out = dp.roi_payload + (uint64_t)k * ww;
     uint32_t *sl = s_r[wv] + (uint32_t)lane * ww;
-    if (!bad) {
+    // the class code at the top of the bits: class | length << 8, 0 for none
+    auto long_code = [&](uint32_t peek) {
+      for (uint32_t L = kRoiLutBits + 1; L <= (uint32_t)kMaxLen; ++L) {
+        const uint32_t code = peek >> (32 - L);
+        const uint32_t cnt = s_t[kRoiTabCount + L - 1], first_code = s_t[kRoiTabFirst + L - 1];
+        if (cnt && code - first_code < cnt)
+          return s_t[kRoiTabSym + s_t[kRoiTabBase + L - 1] + (code - first_code)] | L << 8;
+      }
+      return 0u;
+    };
+    if (!bad && src.staged && lds) {
+      // every value's step is straight code: the word index is clamped to the
+      // staged words, and a window whose values overrun its end ends past it
+      // (no value takes 0 bits), so one comparison after the loop finds it
+      uint32_t pos = start;
+      const uint32_t *in = s_in[wv];
+      for (uint32_t e = 0; e < ww; ++e) {
+        const uint32_t i = min((pos >> 5) - src.w0, nin);
+        const uint64_t x = ((uint64_t)in[i] << 32 | in[i + 1]) << (pos & 31);
+        uint32_t hit = s_lut[(uint32_t)(x >> (64 - kRoiLutBits))];
+        if (!hit) {
+          hit = long_code((uint32_t)(x >> 32));
+          bad |= !hit;
+          hit = max(hit, 1u << 8);
+        }
+        const uint32_t cls = hit & 0xFFu, L = hit >> 8, extra = max(cls, 1u) - 1u;
+        uint32_t raw = (uint32_t)((x << L) >> 32);   // the 32 bits after the code,
+        if (L + extra > 33) {                        // some past the two words (at least 33 hold)
+          const uint32_t q = pos + L, j = min((q >> 5) - src.w0, nin);
+          raw = (uint32_t)((((uint64_t)in[j] << 32 | in[j + 1]) << (q & 31)) >> 32);
+        }
+        const uint32_t z = cls ? (uint32_t)(((1ull << 32) | raw) >> (32 - extra)) : 0u;
+        sl[e] = (z >> 1) ^ (0u - (z & 1u));
+        pos += L + extra;
+      }
+      bad |= pos != end;
+    } else if (!bad) {
       uint32_t pos = start;
       for (uint32_t e = 0; e < ww; ++e) {
         if (pos >= end) {   // every value takes a bit at least
@@ -1422,34 +1458,16 @@ __global__ __launch_bounds__(256) void k_dec_roi_decode(DecBatch db) {
           break;
         }
         const uint32_t peek = src.peek(pos);
-        const uint32_t hit = s_lut[peek >> (32 - kRoiLutBits)];
-        int cls = -1, L = 1;
-        if (hit) {
-          cls = (int)(hit & 0xFFu);
-          L = (int)(hit >> 8);
-        } else {
-          for (L = kRoiLutBits + 1; L <= kMaxLen; ++L) {
-            const uint32_t code = peek >> (32 - L);
-            const uint32_t cnt = s_t[kRoiTabCount + L - 1], first = s_t[kRoiTabFirst + L - 1];
-            if (cnt && code - first < cnt) {
-              cls = (int)s_t[kRoiTabSym + s_t[kRoiTabBase + L - 1] + (code - first)];
-              break;
-            }
-          }
-        }
-        const uint32_t extra = cls >= 2 ? (uint32_t)cls - 1 : 0u;
-        if (cls < 0 || (uint32_t)L + extra > end - pos) {
+        uint32_t hit = s_lut[peek >> (32 - kRoiLutBits)];
+        if (!hit) hit = long_code(peek);
+        const uint32_t cls = hit & 0xFFu, L = hit >> 8, extra = max(cls, 1u) - 1u;
+        if (!hit || L + extra > end - pos) {
           bad = true;
           break;
         }
-        pos += L;
-        uint32_t z = cls == 0 ? 0u : 1u;
-        if (extra) {
-          // the raw bits, from the same 32 bits where they reach
-          const uint32_t raw = L + extra <= 32 ? peek << L : src.peek(pos);
-          z = (1u << extra) | (raw >> (32 - extra));
-          pos += extra;
-        }
+        uint32_t z = cls ? 1u : 0u;
+        if (extra) z = (1u << extra) | (src.peek(pos + L) >> (32 - extra));
+        pos += L + extra;
         const uint32_t r = (z >> 1) ^ (0u - (z & 1u));
         if (lds) sl[e] = r;
         else *gm(out + e) = r;
