@@ -687,9 +687,12 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
   memcpy(host.data(), dps.data(), sizeof(DecodePlan) * n);
   uint32_t *pre = (uint32_t *)(host.data() + align_up((uint64_t)sizeof(DecodePlan) * n, 256));
   uint32_t total_blocks[kDecKernels] = {0};
+  uint64_t all_chunks = 0;
+  for (uint32_t f = 0; f < n; ++f) all_chunks += dps[f].nchunks;
+  const uint32_t reps = decode_chunk_reps(all_chunks);
   for (uint32_t f = 0; f < n; ++f) {
     uint32_t nb[kDecKernels];
-    decode_blocks(dps[f], nb);
+    decode_blocks(dps[f], reps, nb);
     for (int k = 0; k < kDecKernels; ++k) {
       pre[(size_t)k * (n + 1) + f] = total_blocks[k];
       if ((uint64_t)total_blocks[k] + nb[k] > 0x7FFFFFFFull) return RSZ_ERR_ARG;
@@ -700,6 +703,7 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
   const int st = stage_to_device(ws, host.data(), head, s);
   if (st) return st;
   DecBatch db = {};
+  db.chunk_reps = reps;
   for (uint32_t f = 0; f < n; ++f) decode_panel_shape(db, dps[f]);
   db.n = n;
   db.plans = (const DecodePlan *)ws;
@@ -1132,6 +1136,9 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   uint32_t *vpre = (uint32_t *)(host.data() + h_dp + h_pre + h_vf);
   uint64_t off = head;
   uint32_t dec_total[kDecKernels] = {0};
+  uint64_t all_chunks = 0;
+  for (uint32_t f = 0; f < n; ++f) all_chunks += dps[f].nchunks;
+  const uint32_t reps = decode_chunk_reps(all_chunks);
   uint64_t wgs = 0;
   uint32_t mask_words = 0;
   for (uint32_t f = 0; f < n; ++f) {
@@ -1150,7 +1157,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     vf.dplan = (DecodePlan *)ws + f;
     vf.bad = d_bad + f;
     uint32_t nb[kDecKernels];
-    decode_blocks(dp, nb);
+    decode_blocks(dp, reps, nb);
     // the outliers: a fixed number of workgroups (their count is known only
     // on the device), each striding over them
     if (vf.valid) nb[kDecOutliers] = std::min<uint32_t>(kVerifyOutlierBlocks, (dp.nbins + 255) / 256);
@@ -1178,6 +1185,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   vr->vb.wg_prefix = (const uint32_t *)(ws + h_dp + h_pre + h_vf);
   vr->vb.total_wgs = (uint32_t)wgs;
   vr->vb.mask_words = mask_words;
+  vr->db.chunk_reps = reps;
   for (uint32_t f = 0; f < n; ++f) decode_panel_shape(vr->db, dps[f]);
   vr->db.n = n;
   vr->db.plans = (const DecodePlan *)ws;

@@ -13,11 +13,8 @@
 //                   parameters, offsets and that every one bit stays inside
 //                   its chunk.
 //   k_dec_chunks    one wave per 4096-symbol chunk, lanes on slices of its
-//                   bits (self-synchronising starts): Huffman decode to
-//                   residuals (runs of the one-bit residual-0 codeword 32 at
-//                   a time; the chunk zeroed with whole-row stores first, then
-//                   only nonzero residuals stored); each chunk must end
-//                   exactly at the next offset.
+//                   bits (self-synchronising starts): Huffman decode to code
+//                   bytes; each chunk must end exactly at the next offset.
 //   k_dec_outliers  scatter outlier residuals onto the code-0 positions.
 //   k_dec_panels    dimension 3: prefix sum of the residuals across the
 //                   panels, which leaves the panels' 2D residuals.
@@ -46,8 +43,9 @@ constexpr int kLutBits = 11;
 constexpr int32_t kMark = INT32_MIN;  // residual slot waiting for its outlier
 
 // tables: first[33], count[33], offs[33], sorted[1024], then the multi-symbol
-// table: per 11-bit window two words, (up to 3 whole codewords' symbols, 10 bits each) | count
-// << 30 and the bit position after each of them (4 bits each)
+// table: per 11-bit window two words, up to 4 whole codewords' residuals (a
+// signed byte each), and their start bits (bit k: one starts at bit k) | the
+// bit after the last << 16 | their count << 24
 constexpr int kTabFirst = 0, kTabCount = kTabFirst + 33,
               kTabOffs = kTabCount + 33, kTabSorted = kTabOffs + 33,
               kTabMulti = kTabSorted + kNumSym, kTabWords = kTabMulti + 2 * (1 << kLutBits);
@@ -227,33 +225,23 @@ __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
     s_lut[x] = e;
   }
   __syncthreads();
-  // multi-symbol entry: the whole codewords (at most 3) that the window
-  // holds one after the other
+  // multi-symbol entry: the whole codewords (at most 4) that the window
+  // holds one after the other, while their residuals fit a byte
   for (uint32_t x = threadIdx.x; x < (1u << kLutBits); x += 256) {
-    uint32_t syms = 0, n = 0, pos = 0, ends = 0;
-    while (n < 3) {
+    uint32_t bytes = 0, n = 0, pos = 0, starts = 0;
+    while (n < 4) {
       const uint32_t e = s_lut[(x << pos) & ((1u << kLutBits) - 1)];
       const uint32_t L = e >> 16;
-      if (!e || pos + L > (uint32_t)kLutBits) break;
-      syms |= (e & 0x3FFu) << (10 * n);
+      const int32_t r = (int32_t)(e & 0x3FFu) - kRadius;
+      if (!e || pos + L > (uint32_t)kLutBits || r < -127 || r > 127) break;
+      bytes |= (uint32_t)(uint8_t)r << (8 * n);
+      starts |= 1u << pos;
       pos += L;
-      ends |= pos << (4 * n);
       ++n;
     }
-    tab[kTabMulti + 2 * x] = syms | n << 30;
-    tab[kTabMulti + 2 * x + 1] = ends;
+    tab[kTabMulti + 2 * x] = bytes;
+    tab[kTabMulti + 2 * x + 1] = starts | pos << 16 | n << 24;
   }
-}
-
-// Four stream words from word index w (0 past the stream's end).
-__device__ __forceinline__ uint4 ld4(const uint32_t *bw_, uint64_t nwords, uint64_t w) {
-  const RSZ_G uint32_t *bw = gm(bw_);
-  uint4 r;
-  r.x = w < nwords ? bw[w] : 0u;
-  r.y = w + 1 < nwords ? bw[w + 1] : 0u;
-  r.z = w + 2 < nwords ? bw[w + 2] : 0u;
-  r.w = w + 3 < nwords ? bw[w + 3] : 0u;
-  return r;
 }
 
 // Exclusive prefix sum of v over the lanes of a wave; total of all lanes.
@@ -269,123 +257,12 @@ __device__ __forceinline__ uint64_t wave_exclusive_scan_u64(uint64_t v, uint64_t
   return x - v;
 }
 
-__device__ __forceinline__ uint32_t pick8(const uint4 &a, const uint4 &b, uint32_t i) {
-  const uint32_t lo = (i & 3) == 0 ? a.x : (i & 3) == 1 ? a.y : (i & 3) == 2 ? a.z : a.w;
-  const uint32_t hi = (i & 3) == 0 ? b.x : (i & 3) == 1 ? b.y : (i & 3) == 2 ? b.z : b.w;
-  return i < 4 ? lo : hi;
-}
-
-// Decoder state of one lane: its stream bits come through a window of three
-// 4-word blocks (the third loading while the first two are decoded).
-struct BitWindow {
-  const uint32_t *bw;
-  uint64_t nwords, wb;   // wb: word index of block A
-  uint4 A, B, C;
-  __device__ void init(const uint32_t *words, uint64_t n, uint64_t pos) {
-    bw = words;
-    nwords = n;
-    wb = pos >> 5;
-    A = ld4(bw, nwords, wb);
-    B = ld4(bw, nwords, wb + 4);
-    C = ld4(bw, nwords, wb + 8);
-  }
-  // the 32 stream bits from bit `pos` (pos never moves back)
-  __device__ uint32_t peek(uint64_t pos) {
-    uint32_t r = (uint32_t)((pos >> 5) - wb);
-    while (r >= 4) {
-      A = B;
-      B = C;
-      wb += 4;
-      C = ld4(bw, nwords, wb + 8);
-      r -= 4;
-    }
-    const uint64_t two = ((uint64_t)pick8(A, B, r) << 32) | pick8(A, B, r + 1);
-    return (uint32_t)((two << (pos & 31)) >> 32);
-  }
-};
-
-// Decodes codewords from `pos` while pos < lim: returns the count and leaves
-// pos at the first boundary >= lim; with WRITE, writes each nonzero residual
-// (kMark for code 0) at out[k] for k < cap (out holds zeros already).
-// `inval` reports a bit pattern that is no codeword.  With `zrun` (residual
-// 0's codeword is the single bit 0), a run of z zero bits is z residual-0
-// symbols, taken at once up to lim.
-// One decoded symbol other than residual 0 into slot k: its code byte, and
-// where that is 0 the residual (or the outlier mark for code 0) in out.
-__device__ __forceinline__ void put_sym(int32_t *out, uint8_t *out8, uint32_t k, uint32_t sym) {
-  const int32_t r = sym ? (int32_t)sym - kRadius : kMark;
-  const bool small = sym && (uint32_t)(r + 127) < 255u;
-  *gm(out8 + k) = small ? (uint8_t)(r + 128) : (uint8_t)0;
-  if (!small) *gm(out + k) = r;
-}
-
-template <bool WRITE>
-__device__ __forceinline__ uint32_t decode_run(BitWindow &win, uint64_t &pos, uint64_t lim,
-                                               const uint2 *s_multi, const uint32_t *s_first,
-                                               const uint32_t *s_count, const uint32_t *s_offs,
-                                               const uint16_t *s_sorted, int32_t *out,
-                                               uint32_t cap, uint32_t &zeros, bool &inval,
-                                               bool zrun, uint8_t *out8 = nullptr) {
-  uint32_t m = 0;
-  while (pos < lim) {
-    const uint32_t v = win.peek(pos);
-    if (zrun && !(v >> 31)) {
-      const uint32_t z = v ? (uint32_t)__builtin_clz(v) : 32u;
-      const uint32_t take = (uint32_t)min<uint64_t>(z, lim - pos);
-      pos += take;
-      m += take;
-      continue;
-    }
-    const uint2 e = s_multi[v >> (32 - kLutBits)];
-    const uint32_t n = e.x >> 30;
-    if (n) {
-      // up to n symbols, stopping after the first that reaches lim
-      uint32_t take = 1;
-      while (take < n && pos + ((e.y >> (4 * (take - 1))) & 0xFu) < lim) ++take;
-      for (uint32_t j = 0; j < take; ++j) {
-        const uint32_t sym = (e.x >> (10 * j)) & 0x3FFu;
-        zeros += sym == 0;
-        if (WRITE && m + j < cap && sym != kRadius) put_sym(out, out8, m + j, sym);
-      }
-      pos += (e.y >> (4 * (take - 1))) & 0xFu;
-      m += take;
-    } else {
-      uint32_t L = 0, sym = 0;
-      for (uint32_t l = kLutBits + 1; l <= (uint32_t)kMaxLen; ++l) {
-        const uint32_t cd = v >> (32 - l);
-        if (s_count[l] && cd >= s_first[l] && cd - s_first[l] < s_count[l]) {
-          L = l;
-          sym = s_sorted[s_offs[l] + cd - s_first[l]];
-          break;
-        }
-      }
-      if (L == 0) {
-        inval = true;
-        break;
-      }
-      zeros += sym == 0;
-      if (WRITE && m < cap && sym != kRadius) put_sym(out, out8, m, sym);
-      pos += L;
-      ++m;
-    }
-  }
-  return m;
-}
-
-// ------------------------------------------------------------ run stage
-
-constexpr uint32_t kRunKMax = 20;
-
 // The 32 bits of words (n of them, zero beyond) from bit pos, MSB-first.
 __device__ __forceinline__ uint32_t peek_bits(const uint32_t *w, uint32_t n, uint32_t pos) {
   const uint32_t i = pos >> 5, s = pos & 31;
   const uint32_t hi = i < n ? *gm(w + i) : 0u, lo = i + 1 < n ? *gm(w + i + 1) : 0u;
   return (uint32_t)((((uint64_t)hi << 32 | lo) << s) >> 32);
 }
-
-// A wave's words of run bits and of expanded Huffman bits in LDS; a chunk
-// with more works in global memory.
-constexpr uint32_t kRunIn = 512, kRunOut = 1024;
 
 // A wave's stretch of a bit section: staged (words from w0 in LDS, zero words
 // after them) or in the stream.
@@ -399,6 +276,14 @@ struct BitSrc {
     return (uint32_t)((((uint64_t)lds[i] << 32 | lds[i + 1]) << (pos & 31)) >> 32);
   }
 };
+
+// ------------------------------------------------------------ run stage
+
+constexpr uint32_t kRunKMax = 20;
+
+// A wave's words of run bits and of expanded Huffman bits in LDS; a chunk
+// with more works in global memory.
+constexpr uint32_t kRunIn = 512, kRunOut = 1024;
 
 // Run codes from pos while pos < lim: each is a unary quotient q (ones closed
 // by a zero) and k low bits, the zero run before the next one bit.  Leaves
@@ -542,92 +427,232 @@ __global__ __launch_bounds__(256) void k_dec_runs(DecBatch db) {
   }
 }
 
+// The chunk decoder's tables in LDS.
+struct CodeTables {
+  uint2 multi[1 << kLutBits];
+  uint32_t first[kMaxLen + 1], count[kMaxLen + 1], offs[kMaxLen + 1];
+  uint16_t sorted[kNumSym];
+};
+
+// The codeword at the top of v by its length class, for those that have no
+// multi-symbol entry: its symbol, L its length (0: no codeword).
+__device__ __forceinline__ uint32_t long_codeword(const CodeTables &t, uint32_t v, uint32_t &L) {
+#pragma unroll 1
+  for (L = 1; L <= (uint32_t)kMaxLen; ++L) {
+    const uint32_t n = t.count[L], cd = (v >> (32 - L)) - t.first[L];
+    if (n && cd < n) return t.sorted[t.offs[L] + cd];
+  }
+  L = 0;
+  return 0;
+}
+
+// One step of the decoder at pos (< lim): up to n symbols that start before
+// lim.  n: how many (0: no codeword), adv: their bits, starts: the start bits
+// of the first 32 of them, bytes: their residuals (signed bytes; run: a run of
+// residuals 0, whose bytes are 0).  esc: the one symbol's byte is kEscByte and
+// sym its symbol.  With `zrun` (residual 0's codeword is the single bit 0) a
+// window of zero bits is a run of residuals 0, taken at once up to lim.
+constexpr uint32_t kEscByte = 0x80u;
+struct Step {
+  uint32_t n, adv, starts, bytes, sym;
+  bool esc;
+};
+__device__ __forceinline__ Step code_step(const CodeTables &t, uint32_t v, uint32_t room,
+                                          bool zrun) {
+  Step s;
+  s.esc = false;
+  if (zrun && !(v >> (32 - kLutBits))) {
+    s.n = s.adv = min(v ? (uint32_t)__builtin_clz(v) : 32u, room);
+    s.starts = s.n == 32 ? ~0u : (1u << s.n) - 1u;
+    s.bytes = 0;
+    return s;
+  }
+  const uint2 e = t.multi[v >> (32 - kLutBits)];
+  s.n = e.y >> 24;
+  if (s.n) {
+    const uint32_t all = e.y & 0xFFFFu, in = all & ((1u << min(room, 16u)) - 1u);
+    s.adv = (e.y >> 16) & 0xFFu;
+    s.starts = in;
+    s.bytes = e.x;
+    if (in != all) {   // the first start at or past the limit ends the step
+      s.n = __builtin_popcount(in);
+      s.adv = (uint32_t)__builtin_ctz(all & ~in);
+      s.bytes &= (1u << (8 * s.n)) - 1u;   // n < 4 here
+    }
+    return s;
+  }
+  uint32_t L;
+  s.sym = long_codeword(t, v, L);
+  s.n = L ? 1u : 0u;
+  s.adv = L;
+  s.starts = 1;
+  const int32_t r = (int32_t)s.sym - kRadius;
+  s.esc = r < -127 || r > 127;
+  s.bytes = s.esc ? kEscByte : (uint32_t)(uint8_t)r;
+  return s;
+}
+
 // One wave per chunk.  The chunk's bits split into 64 equal slices; lane i
 // decodes from a start s_i until the first codeword boundary at or past the
 // next slice.  Lane 0 starts at the chunk offset, a true boundary; every
-// other lane starts at its slice's first bit, then again at the boundary the
-// lane before it stopped at, until no start changes: then every start is a
-// true boundary (by induction from lane 0).  Huffman decoding
-// resynchronises within a few codewords, so this takes one or two rounds
-// (64 at most).  A scan of the lanes' symbol counts places their outputs, and
-// a last pass writes them.  A valid chunk decodes to exactly its symbol count
+// other lane starts at its slice's first bit, and keeps where in the slice's
+// first 64 bits its codewords started.  Then it starts again at the boundary
+// the lane before it stopped at, until no start changes: then every start is
+// a true boundary (by induction from lane 0).  Huffman decoding
+// resynchronises within a few codewords: once the second decode meets a start
+// of the first, the rest is the first's, so a restart takes a few symbols and
+// not the slice.  A scan of the lanes' symbol counts places their outputs,
+// and a last pass ORs their bytes into the chunk's in LDS, which leave as
+// whole 16-byte stores.  A valid chunk decodes to exactly its symbol count
 // and ends exactly at the next chunk offset.
-__global__ __launch_bounds__(256) void k_dec_chunks(DecBatch db) {
+//
+// The LDS lookups of a lane follow one another and bound it (the bits come
+// from LDS too, when the chunk has at most kChunkIn words of them), at 16
+// waves a CU: 8 share the tables' 18 KB (4 a workgroup 0.39 ms, 16 0.35, 8
+// 0.34 on 1000 CSPAD streams). With the bits by global loads, three whole
+// decodes a slice and byte stores straight to HBM it took 0.40 ms there and
+// 0.48 against 0.28 on 128 dense streams of 8x512x1024.
+constexpr uint32_t kChunkIn = 640;
+constexpr uint32_t kChunkWaves = 8;
+__global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
   RSZ_DEC_FRAME(2);
-  __shared__ uint2 s_multi[1 << kLutBits];
-  __shared__ uint32_t s_first[kMaxLen + 1], s_count[kMaxLen + 1], s_offs[kMaxLen + 1];
-  __shared__ uint16_t s_sorted[kNumSym];
-  for (int i = threadIdx.x; i < (1 << kLutBits); i += 256)
-    s_multi[i] = make_uint2(dp.tables[kTabMulti + 2 * i], dp.tables[kTabMulti + 2 * i + 1]);
-  for (int i = threadIdx.x; i < kNumSym; i += 256) s_sorted[i] = (uint16_t)dp.tables[kTabSorted + i];
+  __shared__ CodeTables s_t;
+  __shared__ uint32_t s_in[kChunkWaves][kChunkIn + 2];
+  __shared__ __align__(16) uint32_t s_out[kChunkWaves][kChunk / 4];
+  for (int i = threadIdx.x; i < (1 << kLutBits); i += 64 * kChunkWaves)
+    s_t.multi[i] = make_uint2(dp.tables[kTabMulti + 2 * i], dp.tables[kTabMulti + 2 * i + 1]);
+  for (int i = threadIdx.x; i < kNumSym; i += 64 * kChunkWaves)
+    s_t.sorted[i] = (uint16_t)dp.tables[kTabSorted + i];
   if (threadIdx.x <= kMaxLen) {
-    s_first[threadIdx.x] = dp.tables[kTabFirst + threadIdx.x];
-    s_count[threadIdx.x] = dp.tables[kTabCount + threadIdx.x];
-    s_offs[threadIdx.x] = dp.tables[kTabOffs + threadIdx.x];
+    s_t.first[threadIdx.x] = dp.tables[kTabFirst + threadIdx.x];
+    s_t.count[threadIdx.x] = dp.tables[kTabCount + threadIdx.x];
+    s_t.offs[threadIdx.x] = dp.tables[kTabOffs + threadIdx.x];
   }
-  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool ok = dec_ok(dp.status);
+  const RSZ_G uint32_t *co = gm((const uint32_t *)(dp.in + dp.off_chunks));
+  const uint32_t T = (uint32_t)dp.T;   // <= 32 nbins < 2^32
+  const uint32_t nchunks = dp.nchunks, nbins = dp.nbins;
+  int32_t *status = dp.status, *res = dp.res;
+  uint8_t *res8 = dp.res8;
+  BitSrc src;
+  src.words = dp.bits;   // the stream's bitstream, or the expanded runs
+  src.n = (uint32_t)((dp.T + 31) / 32);
+  src.lds = s_in[wv];
+  __syncthreads();   // tables loaded
+  if (!ok) return;
   // residual 0 (symbol 512) coded as the single bit 0: the only length-1
   // code, canonical code 0
-  const bool zrun = s_count[1] == 1 && s_first[1] == 0 && s_sorted[s_offs[1]] == kRadius;
-  const int lane = threadIdx.x & 63;
-  const uint32_t c = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (c >= dp.nchunks || !dec_ok(dp.status)) return;
-  const RSZ_G uint32_t *co = gm((const uint32_t *)(dp.in + dp.off_chunks));
-  const uint32_t *bw = dp.bits;   // the stream's bitstream, or the expanded runs
-  const uint64_t nwords = (dp.T + 31) / 32;
-  const uint64_t S = co[c], E = c + 1 < dp.nchunks ? co[c + 1] : dp.T;
-  const uint32_t g0 = c * kChunk;
-  const uint32_t nsym = min(kChunk, dp.nbins - g0);
-  const uint64_t len = E > S ? E - S : 0;
-  const uint64_t lim = lane == 63 ? E : S + len * (uint64_t)(lane + 1) / 64;
-  uint64_t start = lane == 0 ? S : S + len * (uint64_t)lane / 64;
-  uint64_t stop = start;
-  uint32_t m = 0;
-  bool converged = false, inv = false;
-  for (int round = 0; round <= 64 && !converged; ++round) {
-    BitWindow win;
-    win.init(bw, nwords, start);
-    uint64_t pos = start;
-    uint32_t z = 0;
-    inv = false;
-    m = decode_run<false>(win, pos, lim, s_multi, s_first, s_count, s_offs, s_sorted, nullptr, 0,
-                          z, inv, zrun);
-    stop = inv ? ~0ull : pos;   // a lane stuck on a non-codeword hands on no boundary
-    // the boundary the lane before stopped at is this lane's next start
-    const uint64_t prev = __shfl_up(stop, 1);
-    const uint64_t next = lane == 0 ? S : prev;
-    const bool changed = lane > 0 && next != start;
-    converged = __builtin_amdgcn_uicmp((uint32_t)changed, 0u, 33 /* ne */) == 0;
-    if (!converged) start = next == ~0ull ? lim : next;
+  const bool zrun = s_t.count[1] == 1 && s_t.first[1] == 0 && s_t.sorted[s_t.offs[1]] == kRadius;
+  for (uint32_t rep = 0; rep < db.chunk_reps; ++rep) {
+    const uint32_t c = (bid * db.chunk_reps + rep) * kChunkWaves + wv;
+    if (c >= nchunks) return;
+    const uint32_t S = co[c], E = max(S, c + 1 < nchunks ? co[c + 1] : T);
+    src.w0 = S >> 5;
+    // the chunk's words and the two after them (a window reaches past its end)
+    const uint32_t nin = (uint32_t)(((uint64_t)E + 31) / 32) - src.w0 + 2;
+    src.staged = nin <= kChunkIn + 2;
+    if (src.staged)
+      for (uint32_t i = lane; i < nin; i += 64)
+        s_in[wv][i] = src.w0 + i < src.n ? *gm(src.words + src.w0 + i) : 0u;
+    for (uint32_t i = lane; i < kChunk / 16; i += 64)
+      *(uint4 *)(s_out[wv] + 4 * i) = make_uint4(0u, 0u, 0u, 0u);
+    wave_sync();
+    const uint32_t g0 = c * kChunk;
+    const uint32_t nsym = min(kChunk, nbins - g0);
+    const uint64_t len = E - S;
+    const uint32_t lim = lane == 63 ? E : S + (uint32_t)(len * (uint64_t)(lane + 1) / 64);
+    const uint32_t s0 = S + (uint32_t)(len * (uint64_t)lane / 64);   // the slice's first bit
+    constexpr uint32_t kStuck = ~0u;   // (no position: T < 2^32 - 1)
+    // the first decode: its codeword starts within 64 bits of s0, its symbols,
+    // where it stopped (kStuck: at a bit pattern that is no codeword)
+    uint64_t seen = 0;
+    uint32_t m0 = 0, stop0;
+    {
+      uint32_t pos = s0;
+      bool inv = false;
+      while (pos < lim) {
+        const Step st = code_step(s_t, src.peek(pos), lim - pos, zrun);
+        if (!st.n) {
+          inv = true;
+          break;
+        }
+        const uint32_t off = pos - s0;
+        if (off < 64) seen |= (uint64_t)st.starts << off;
+        pos += st.adv;
+        m0 += st.n;
+      }
+      stop0 = inv ? kStuck : pos;
+    }
+    uint32_t start = s0, stop = stop0, m = m0;
+    bool converged = false;
+    for (int round = 0; round <= 64 && !converged; ++round) {
+      // the boundary the lane before stopped at is this lane's start (a stuck
+      // lane hands on none)
+      const uint32_t prev = __shfl_up(stop, 1);
+      const uint32_t next = lane == 0 ? S : (prev == kStuck ? lim : prev);
+      const bool changed = next != start;
+      converged = __ballot(changed) == 0;
+      if (!changed) continue;
+      start = next;
+      uint32_t pos = start, n = 0;
+      bool inv = false, met = false;
+      while (pos < lim) {
+        const uint32_t off = pos - s0;
+        if (off < 64 && ((seen >> off) & 1u)) {
+          met = true;
+          n += m0 - (uint32_t)__builtin_popcountll(seen & ((1ull << off) - 1ull));
+          break;
+        }
+        // one symbol at a time while the first decode's starts are known
+        Step st = code_step(s_t, src.peek(pos), lim - pos, zrun);
+        if (!st.n) {
+          inv = true;
+          break;
+        }
+        if (off < 64 && st.n > 1) {
+          const uint32_t second = st.starts & (st.starts - 1);
+          st.adv = (uint32_t)__builtin_ctz(second);
+          st.n = 1;
+        }
+        pos += st.adv;
+        n += st.n;
+      }
+      m = n;
+      stop = met ? stop0 : (inv ? kStuck : pos);
+    }
+    uint64_t tot;
+    const uint32_t off = (uint32_t)wave_exclusive_scan_u64(m, tot);
+    const uint32_t last = __shfl(stop, 63);
+    // a valid chunk converges (64 rounds at most) with no non-codeword on its path
+    if (!converged || __ballot(stop == kStuck) != 0 || tot != nsym || last != E) {
+      if (lane == 0) corrupt(status);
+      return;
+    }
+    // the output pass, from the true starts
+    uint32_t pos = start, k = off;
+    while (pos < lim) {
+      const Step st = code_step(s_t, src.peek(pos), lim - pos, zrun);
+      if (!st.n) break;   // (not reached: the same steps succeeded above)
+      if (st.bytes) {
+        const uint64_t w = (uint64_t)st.bytes << (8 * (k & 3));
+        if ((uint32_t)w) atomicOr(&s_out[wv][k >> 2], (uint32_t)w);
+        if ((uint32_t)(w >> 32)) atomicOr(&s_out[wv][(k >> 2) + 1], (uint32_t)(w >> 32));
+        if (st.esc) *gm(res + g0 + k) = st.sym ? (int32_t)st.sym - kRadius : kMark;
+      }
+      pos += st.adv;
+      k += st.n;
+    }
+    wave_sync();
+    // whole 16-byte groups (the region holds 64 bytes past the last chunk)
+    uint8_t *rc = res8 + g0;
+    for (uint32_t i = 16 * lane; i < nsym; i += 1024) {
+      const u32x4 x = *(const u32x4 *)((const uint8_t *)s_out[wv] + i);
+      *gm((u32x4 *)(rc + i)) = x ^ 0x80808080u;
+    }
+    wave_sync();
   }
-  uint64_t tot;
-  const uint32_t off = (uint32_t)wave_exclusive_scan_u64(m, tot);
-  const uint64_t last = __shfl(stop, 63);
-  // a valid chunk converges (64 rounds at most) with no non-codeword on its path
-  bool bad = !converged || __builtin_amdgcn_uicmp((uint32_t)inv, 0u, 33 /* ne */) != 0 ||
-             tot != nsym || last != E;
-  inv = false;
-  // the output pass, from the true starts: the wave zeroes the chunk's
-  // residuals with whole-row stores, waits for them to complete, and the
-  // lanes then store only their nonzero residuals (most are 0)
-  // (code bytes: 128, residual 0, in 16-byte stores; the region holds 64
-  // bytes past the last chunk)
-  if (!bad) {
-    RSZ_G uint8_t *rc = gm(dp.res8 + g0);
-    for (uint32_t i = 16 * lane; i < nsym; i += 1024)
-      *(RSZ_G u32x4 *)(rc + i) = u32x4{0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  }
-  BitWindow win;
-  win.init(bw, nwords, start);
-  uint64_t pos = start;
-  uint32_t zeros = 0;
-  if (!bad)
-    decode_run<true>(win, pos, lim, s_multi, s_first, s_count, s_offs, s_sorted, dp.res + g0 + off,
-                     off < nsym ? nsym - off : 0u, zeros, inv, zrun,
-                     dp.res8 + g0 + off);
-  bad |= __builtin_amdgcn_uicmp((uint32_t)inv, 0u, 33 /* ne */) != 0;
-  if (lane == 0 && bad) corrupt(dp.status);
 }
 
 // The outliers into their bins' residual slots; the frame's workgroups take
@@ -1577,12 +1602,12 @@ __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   if (roi_window<true>(dp, k, threadIdx.x & 63)) corrupt(dp.status);
 }
 
-void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
+void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
   for (int k = 0; k < kDecKernels; ++k) nb[k] = 0;
   nb[0] = 1;   // k_dec_tables writes every frame's status
   if (dp.init_status != RSZ_OK) return;
   if (dp.run_coding) nb[1] = (dp.nchunks + 3) / 4;
-  nb[2] = (dp.nchunks + 3) / 4;
+  nb[2] = (dp.nchunks + kChunkWaves * reps - 1) / (kChunkWaves * reps);
   nb[kDecOutliers] = (dp.n_out + 255) / 256;
   // inverse Lorenzo: prefix sums along each axis the predictor spans
   if (dp.dim == 3) nb[4] = (dp.Hb * dp.Wb + 1023) / 1024;
@@ -1620,7 +1645,7 @@ void decode_blocks(const DecodePlan &dp, uint32_t *nb) {
 hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStream_t s) {
   RSZ_DLAUNCH(0, "k_dec_tables", k_dec_tables, 256);
   RSZ_DLAUNCH(1, "k_dec_runs", k_dec_runs, 256);
-  RSZ_DLAUNCH(2, "k_dec_chunks", k_dec_chunks, 256);
+  RSZ_DLAUNCH(2, "k_dec_chunks", k_dec_chunks, 64 * kChunkWaves);
   RSZ_DLAUNCH(kDecOutliers, "k_dec_outliers", k_dec_outliers, 256);
   RSZ_DLAUNCH(4, "k_dec_panels", k_dec_panels, 256);
   RSZ_DLAUNCH(5, "k_dec_rowsum", k_dec_rowsum, 256);
@@ -1643,6 +1668,13 @@ void decode_geometry(DecodePlan &dp) {
   dp.nbands = (dp.Hb + kDecTH - 1) / kDecTH;
   dp.seg_bands = std::max(8u, (dp.nbands + 15) / 16);
   dp.nsegs = (dp.nbands + dp.seg_bands - 1) / dp.seg_bands;
+}
+
+// A workgroup of k_dec_chunks copies its stream's tables (18 KB) to LDS first,
+// so in a large batch its waves take several chunks each; a small one wants
+// every chunk on a wave of its own.
+uint32_t decode_chunk_reps(uint64_t all_chunks) {
+  return (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, all_chunks / (kChunkWaves * 1024)));
 }
 
 // k_dec_panel's waves and LDS words: the most that a panel of the batch takes.
