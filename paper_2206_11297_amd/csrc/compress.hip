@@ -475,6 +475,86 @@ __device__ __forceinline__ int32_t reduce_vec(const BinPix<BB> &px, uint32_t row
   return (int32_t)t;
 }
 
+// Any bin factor and width (a panel at least a bin wide): a lane's bin row is
+// one or two loads of its BB floats at a 4-byte aligned address from the
+// wave-uniform row pointer.  A bin cut by the panel's edge loads the last BB
+// columns: its own are the last of them, in order, and the others are left
+// out like window pixels.  m: the row's window bits from the first column
+// loaded.
+template <int BB, bool BG>
+__device__ __forceinline__ void load_any(BinPix<BB> &px, const float *__restrict__ fr, uint32_t H,
+                                         uint32_t W, uint32_t I, uint32_t J, const uint32_t *mask,
+                                         int64_t R0, int wpr, int64_t Cm) {
+  const uint32_t jl = min(J * BB, W - BB);
+  const uint32_t wd = (uint32_t)((int64_t)jl - Cm) >> 5, sh = jl & 31u;
+  const uint32_t wn = min(wd + 1, (uint32_t)wpr - 1);
+#pragma unroll
+  for (int di = 0; di < BB; ++di) {
+    const uint32_t i = min(I * BB + di, H - 1);
+    const char *row = (const char *)(fr + (size_t)i * W);
+    const RSZ_G float *a = (const RSZ_G float *)(row + jl * 4u);
+#pragma unroll
+    for (int k = 0; k + 4 <= BB; k += 4) {
+      const f32x4a x = *(const RSZ_G f32x4a *)(a + k);
+      px.v[di][k] = x.x;
+      px.v[di][k + 1] = x.y;
+      px.v[di][k + 2] = x.z;
+      px.v[di][k + 3] = x.w;
+    }
+    constexpr int K = BB / 4 * 4;
+    if constexpr (BB % 4 == 3) {
+      const f32x3a x = *(const RSZ_G f32x3a *)(a + K);
+      px.v[di][K] = x.x;
+      px.v[di][K + 1] = x.y;
+      px.v[di][K + 2] = x.z;
+    } else if constexpr (BB % 4 == 2) {
+      const f32x2a x = *(const RSZ_G f32x2a *)(a + K);
+      px.v[di][K] = x.x;
+      px.v[di][K + 1] = x.y;
+    } else if constexpr (BB % 4 == 1) {
+      px.v[di][K] = a[K];
+    }
+    if constexpr (BG) {
+      const uint32_t *mr = mask + (int)(i - R0) * wpr;
+      px.m[di] = __builtin_amdgcn_alignbit(mr[wn], mr[wd], sh);
+    } else {
+      px.m[di] = 0u;
+    }
+  }
+}
+
+// reduce_vec for load_any's pixels (no exact sum: the debug kernels take the
+// scalar path).
+template <int BB, bool BG>
+__device__ __forceinline__ int32_t reduce_any(const BinPix<BB> &px, uint32_t H, uint32_t W,
+                                              uint32_t I, uint32_t J, const double *inv,
+                                              double step, bool &range_err) {
+  const uint32_t cols = ((1u << BB) - 1u) & ~((1u << (J * BB - min(J * BB, W - BB))) - 1u);
+  double S = 0.0;
+  uint32_t n = 0;
+#pragma unroll
+  for (int di = 0; di < BB; ++di) {
+    uint32_t inc = I * BB + di < H ? cols : 0u;
+    if constexpr (BG) inc &= ~px.m[di];
+    n += (uint32_t)__builtin_popcount(inc);
+#pragma unroll
+    for (int dj = 0; dj < BB; ++dj) {
+      const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)inc, dj, 1);
+      const uint32_t xb = (__float_as_uint(px.v[di][dj]) & keep) | (0x80000000u & ~keep);
+      const double x = (double)__uint_as_float(xb);
+      S = di == 0 && dj == 0 ? x : S + x;
+    }
+  }
+  const double t1 = S * inv[n];
+  double t = rint(t1);
+  if (!(fabs(t1 - t) < 0.5 - 0x1p-20)) t = rint(S / ((double)n * step));
+  if (!(fabs(t) <= kQMax)) {
+    range_err = true;
+    return 0;
+  }
+  return (int32_t)t;
+}
+
 // Wave mask of one segment: raw rows [R0, R0 + mrows) x columns [C0, C0 +
 // 32*wpr) of panel p, bit set where a pixel lies in some peak's window.
 __device__ __forceinline__ void build_mask(const FramePlan &fp, uint32_t p, uint32_t *mask,
@@ -528,12 +608,6 @@ __device__ __forceinline__ void flush_zb(const SparseStage &stg, uint8_t *zb, ui
     *gm((u32x2 *)(zb + o)) = *(const u32x2 *)(stg.zb + (o & (kZbRing - 1)));
 }
 
-// Strips of a row whose loads are issued together.
-template <int BB>
-constexpr int strips_in_flight() {
-  return BB == 1 || BB == 2 ? 4 : (BB == 4 ? 2 : 1);
-}
-
 // One wave's tile: bin rows [I0, I1) of segment `seg` x the strips of 64 bin
 // columns [S0, S0 + ns) of column group `cg` of panel p, walked row by row.
 // The Lorenzo predictor of the tile's first row and first column reads the q
@@ -547,11 +621,13 @@ constexpr int strips_in_flight() {
 // r = q here and k_lorenzo_dims corrects it with the q of the row before's
 // last bin, kept in qedge.  Dimension 3 leaves the panel's 2D residual for
 // k_lorenzo_dims to difference across panels, and counts no histogram here.
-template <int BB, bool VEC, bool BG, bool DEBUG, int DIM>
+// MODE: how rows load -- kScalar, kVec (load_vec), kAny (load_any).
+constexpr int kScalar = 0, kVec = 1, kAny = 2;
+template <int BB, int MODE, bool BG, bool DEBUG, int DIM>
 __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32_t seg,
                                          uint32_t cg, uint32_t *hist, uint32_t *mask,
                                          const double *inv, SparseStage *stg) {
-  constexpr int G = strips_in_flight<BB>();
+  constexpr bool VEC = MODE == kVec;
   constexpr int NS = group_strips(BB);
   const int lane = threadIdx.x & 63;
   const int b = BB ? BB : (int)fp.b;
@@ -623,10 +699,15 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
     if (I0 > 0 && s < ns) {
       const uint32_t jc = RSZ_JC(s);
       BinPix<BB> px;
-      load_bin<BB, VEC, BG>(px, fr, H, W, b, I0 - 1, jc, mask, R0, wpr, RSZ_MW(jc));
-      const int32_t qh = reduce_bin<BB, BG>(px, H, W, b, I0 - 1, J0 + s * 64 + lane, step, inv,
-                                            range_err, Sd, nd, (int)((jc * b) & 31), mask, R0,
-                                            wpr, RSZ_MW(jc));
+      int32_t qh;
+      if constexpr (MODE == kAny) {
+        load_any<BB, BG>(px, fr, H, W, I0 - 1, jc, mask, R0, wpr, Cm);
+        qh = reduce_any<BB, BG>(px, H, W, I0 - 1, jc, inv, step, range_err);
+      } else {
+        load_bin<BB, VEC, BG>(px, fr, H, W, b, I0 - 1, jc, mask, R0, wpr, RSZ_MW(jc));
+        qh = reduce_bin<BB, BG>(px, H, W, b, I0 - 1, J0 + s * 64 + lane, step, inv, range_err, Sd,
+                                nd, (int)((jc * b) & 31), mask, R0, wpr, RSZ_MW(jc));
+      }
       q_up[s] = J0 + s * 64 + lane < Wb ? qh : 0;
     }
   }
@@ -669,7 +750,7 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
   // Dimension 1 needs each row's last q before the next row, so it keeps
   // the unpacked strip.
   const uint32_t rem = Wb - (J0 + 64 * (uint32_t)(ns - 1));
-  const bool packed = VEC && dim != 1 && last_group && ns >= 2 && rem * fp.TH <= 64;
+  const bool packed = MODE != kScalar && dim != 1 && last_group && ns >= 2 && rem * fp.TH <= 64;
   const int nsr = packed ? ns - 1 : ns;   // strips done row by row
   int32_t qlast = 0;                      // lane i: q of the row loop's last bin of tile row i
   int32_t qhl = 0;                        // q of bin (I0 - 1, last column of the row loop)
@@ -681,7 +762,6 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
   // The strips of a row are loaded together; each strip's registers take the
   // next row's loads as soon as the strip is reduced, so that they are in
   // flight while the rest of the row is computed.
-  static_assert(G == NS, "one group of strips per row");
   BinPix<BB> px[NS];
 #define RSZ_LOAD(s, Irow)                                                                   \
   do {                                                                                      \
@@ -689,6 +769,8 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
       const uint32_t jv_ = RSZ_JC(s);                                                       \
       load_vec<BB, BG>(px[s], fr, H, W, (Irow), jv_ * (uint32_t)b * 4u, mask + RSZ_MW(jv_), \
                        R0, wpr);                                                            \
+    } else if constexpr (MODE == kAny) {                                                    \
+      load_any<BB, BG>(px[s], fr, H, W, (Irow), RSZ_JC(s), mask, R0, wpr, Cm);              \
     } else {                                                                                \
       const uint32_t jc_ = RSZ_JC(s);                                                       \
       load_bin<BB, VEC, BG>(px[s], fr, H, W, b, (Irow), jc_, mask, R0, wpr, RSZ_MW(jc_));  \
@@ -726,6 +808,8 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
           if constexpr (VEC) {
             qv = reduce_vec<BB, BG>(px[s], rowbits, (int)((jc * b) & 31), inv, step, range_err,
                                     DEBUG, Sd, nd);
+          } else if constexpr (MODE == kAny) {
+            qv = reduce_any<BB, BG>(px[s], H, W, I, jc, inv, step, range_err);
           } else {
             qv = reduce_bin<BB, BG>(px[s], H, W, b, I, J, step, inv, range_err, Sd, nd,
                                     (int)((jc * b) & 31), mask, R0, wpr, RSZ_MW(jc));
@@ -806,7 +890,7 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
     case 3: if constexpr (NS >= 3) row_loop(std::integral_constant<int, 3>{}); break;
     default: if constexpr (NS >= 4) row_loop(std::integral_constant<int, 4>{}); break;
   }
-  if constexpr (VEC) {
+  if constexpr (MODE != kScalar) {
     if (packed) {
       const uint32_t nr = I1 - I0;
       const uint32_t r = (uint32_t)lane / rem, c = (uint32_t)lane - r * rem;
@@ -818,10 +902,16 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
       for (int s = 0; s < NS; ++s)
         if (s == nsr) qh = q_up[s];
       BinPix<BB> pxp;
-      load_vec<BB, BG>(pxp, fr, H, W, I, J * (uint32_t)b * 4u, mask + RSZ_MW(J), R0, wpr);
-      const uint32_t rowbits = (1u << (min((uint32_t)BB, H - I * BB) * BB)) - 1u;
-      const int32_t qv = reduce_vec<BB, BG>(pxp, rowbits, (int)((J * b) & 31), inv, step,
-                                            range_err, DEBUG, Sd, nd);
+      int32_t qv;
+      if constexpr (VEC) {
+        load_vec<BB, BG>(pxp, fr, H, W, I, J * (uint32_t)b * 4u, mask + RSZ_MW(J), R0, wpr);
+        const uint32_t rowbits = (1u << (min((uint32_t)BB, H - I * BB) * BB)) - 1u;
+        qv = reduce_vec<BB, BG>(pxp, rowbits, (int)((J * b) & 31), inv, step, range_err, DEBUG,
+                                Sd, nd);
+      } else {
+        load_any<BB, BG>(pxp, fr, H, W, I, J, mask, R0, wpr, Cm);
+        qv = reduce_any<BB, BG>(pxp, H, W, I, J, inv, step, range_err);
+      }
       const int32_t q = valid ? qv : 0;
       // neighbours: within the vector, or the row loop's last column (qlast)
       // and the halo row
@@ -893,11 +983,11 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
   if (range_err) set_status(fp.st, RSZ_ERR_RANGE);
 }
 
-// BB: the bin factor (1, 2, 4) compiled in, or 0 for any b (one strip per
+// BB: the bin factor compiled in, or 0 for any b (one strip per
 // column group).  DIM: the Lorenzo dimension compiled in, or 0 for a batch
 // mixing dimensions (read per frame).  Workgroup t of a frame: panel, column
 // group, then a group of kWaves consecutive segments, one per wave.
-template <int BB, bool DEBUG, int DIM, bool VONLY>
+template <int BB, bool DEBUG, int DIM, int ONLY>
 __device__ __forceinline__ void k_bin_body(BatchPlan bp) {
   __shared__ uint32_t s_hist[kNumSym];
   __shared__ uint32_t s_mask[kWaves][kMaskWords];
@@ -920,19 +1010,23 @@ __device__ __forceinline__ void k_bin_body(BatchPlan bp) {
     const bool bg = fp.mode == RSZ_BIN_BACKGROUND;
     uint32_t *mask = s_mask[wv];
     SparseStage *stg = &s_stage[DIM == 3 ? 0 : wv];
+    // ONLY: every frame of the batch takes that path, and the kernel holds
+    // only its registers
     bool vec = false;
-    if constexpr (BB == 2 || BB == 4) {
+    if constexpr (ONLY == kAny) {
+      vec = true;
+      if (bg) bin_tile<BB, kAny, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+      else bin_tile<BB, kAny, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+    } else if constexpr (BB == 2 || BB == 4) {
       vec = fp.vec != 0;
       if (vec) {
-        if (bg) bin_tile<BB, true, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
-        else bin_tile<BB, true, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+        if (bg) bin_tile<BB, kVec, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+        else bin_tile<BB, kVec, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
       }
     }
-    // VONLY: every frame of the batch takes the vector path, and the kernel
-    // holds only its registers (the scalar path needs more)
-    if (!VONLY && !vec) {
-      if (bg) bin_tile<BB, false, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
-      else bin_tile<BB, false, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+    if (ONLY == kScalar && !vec) {
+      if (bg) bin_tile<BB, kScalar, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+      else bin_tile<BB, kScalar, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
     }
   }
   __syncthreads();
@@ -942,7 +1036,7 @@ __device__ __forceinline__ void k_bin_body(BatchPlan bp) {
 
 template <int BB, bool DEBUG, int DIM>
 __global__ __launch_bounds__(256) void k_bin(BatchPlan bp) {
-  k_bin_body<BB, DEBUG, DIM, false>(bp);
+  k_bin_body<BB, DEBUG, DIM, kScalar>(bp);
 }
 
 // Batches whose frames all take the vector path, without the scalar path's
@@ -953,7 +1047,19 @@ __global__ __launch_bounds__(256) void k_bin(BatchPlan bp) {
 template <int BB, int DIM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bin_vec(
     BatchPlan bp) {
-  k_bin_body<BB, false, DIM, true>(bp);
+  k_bin_body<BB, false, DIM, kVec>(bp);
+}
+
+// Batches of one bin factor (2 to 8) and dimension whose frames are at least
+// a bin wide, where some frame's rows do not load as aligned vectors (b = 3
+// and 5 to 8; widths not a multiple of b): 200 frames of 5x187x389 take 82,
+// 98, 76, 80, 76, 54 and 55 us at b = 2 to 8, one load a pixel from k_bin took
+// 102, 213, 128, 192, 166, 99 and 181. At b = 1 a pixel is a load either way
+// and k_bin is the faster (180 against 203 us).
+template <int BB, int DIM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BB > 5 ? 3 : 4))) void k_bin_any(
+    BatchPlan bp) {
+  k_bin_body<BB, false, DIM, kAny>(bp);
 }
 
 // ------------------------------------------------------- k_lorenzo_dims
@@ -2795,6 +2901,23 @@ template <bool DEBUG, int DIM>
 static hipError_t launch_bin(const BatchPlan &bp, uint32_t b, hipStream_t s) {
   if (bp.total_tiles == 0) return hipSuccess;
   const uint32_t grid = bp.total_tiles;
+  if constexpr (!DEBUG && DIM != 0) {
+    if (bp.all_wide && !(bp.all_vec && (b == 2 || b == 4))) {
+#define RSZ_BIN_ANY(B) \
+  case B: RSZ_LAUNCH_B("k_bin", (k_bin_any<B, DIM>), grid, 64 * bp.bin_waves, s, bp); return hipSuccess;
+      switch (b) {
+        RSZ_BIN_ANY(2)
+        RSZ_BIN_ANY(3)
+        RSZ_BIN_ANY(4)
+        RSZ_BIN_ANY(5)
+        RSZ_BIN_ANY(6)
+        RSZ_BIN_ANY(7)
+        RSZ_BIN_ANY(8)
+        default: break;
+      }
+#undef RSZ_BIN_ANY
+    }
+  }
   switch (b) {
     case 1: RSZ_LAUNCH_B("k_bin", (k_bin<1, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;
     case 2:
@@ -2805,6 +2928,7 @@ static hipError_t launch_bin(const BatchPlan &bp, uint32_t b, hipStream_t s) {
       if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM>), grid, 64 * bp.bin_waves, s, bp);
       else RSZ_LAUNCH_B("k_bin", (k_bin<4, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp);
       break;
+    case 3: RSZ_LAUNCH_B("k_bin", (k_bin<3, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;
     default: RSZ_LAUNCH_B("k_bin", (k_bin<0, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;
   }
   return hipSuccess;

@@ -31,7 +31,7 @@ constexpr uint32_t kTileEntries = kMaxTH * 4;   // sparse codes: entries per bin
 // Strips per column group for bin factor b as compiled in the binning kernel
 // (0: any b, and batches mixing bin factors).
 __host__ __device__ constexpr int group_strips(int b) {
-  return b == 1 || b == 2 ? 4 : (b == 4 ? 2 : 1);
+  return b == 1 || b == 2 ? 4 : (b == 3 ? 3 : (b == 4 ? 2 : 1));
 }
 
 inline __host__ __device__ uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -187,6 +187,7 @@ struct BatchPlan {
   uint32_t total_tiles, total_units, total_peaks, total_chunks;
   uint32_t cpw;                  // chunks encoded by one k_encode workgroup
   uint32_t all_vec;              // every frame's rows load as float2/float4 (k_bin)
+  uint32_t all_wide;             // every frame is at least a bin wide (k_bin_any)
   uint32_t bin_waves;            // waves per k_bin workgroup (1..kWaves)
   uint32_t total_fix;            // workgroups of k_lorenzo_dims (0: every frame is 2D)
   uint32_t roi_coding;           // some frame codes its ROI windows
