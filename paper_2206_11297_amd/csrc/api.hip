@@ -1486,6 +1486,8 @@ int rsz_find_peaks_batch(const rsz_peak_params *q, uint32_t nframes, const rsz_p
     fp.P = d.panels;
     fp.H = d.height;
     fp.W = d.width;
+    fp.fd_W = fast_div(d.width);
+    fp.fd_H = fast_div(d.height);
     fp.cap = d.max_peaks;
     fp.frame = d.frame;
     fp.out = d.peaks;

@@ -46,17 +46,6 @@ __device__ __forceinline__ uint64_t low_bits(uint32_t n) {
   return n >= 64 ? ~0ull : (1ull << n) - 1ull;
 }
 
-// Frame owning flat work item `item`: the largest f with prefix[f] <= item.
-__device__ __forceinline__ uint32_t find_frame(const uint32_t *prefix, uint32_t nframes,
-                                               uint32_t item) {
-  uint32_t lo = 0, hi = nframes;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (prefix[mid] <= item) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ int32_t load_status(const FrameState *st) {
   return __hip_atomic_load(&st->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1141,7 +1130,7 @@ __device__ __forceinline__ uint4 code_group(const FramePlan &fp, uint32_t g0) {
 
 __global__ __launch_bounds__(256) void k_lorenzo_dims(BatchPlan bp) {
   __shared__ uint32_t s_hist[kNumSym];
-  const uint32_t f = find_frame(bp.fix_prefix, bp.nframes, blockIdx.x);
+  const uint32_t f = wave_find_frame(bp.fix_prefix, bp.nframes, blockIdx.x);
   const FramePlan &fp = bp.frames[f];
   if (load_status(fp.st) != RSZ_OK) return;   // the same frame for the whole workgroup
   const uint32_t blk = blockIdx.x - bp.fix_prefix[f];
@@ -2621,7 +2610,7 @@ __global__ __launch_bounds__(256) void k_run_count(BatchPlan bp) {
     roi_copy(bp, item - bp.total_chunks);
     return;
   }
-  const uint32_t f = find_frame(bp.chunk_prefix, bp.nframes, item);
+  const uint32_t f = wave_find_frame(bp.chunk_prefix, bp.nframes, item);
   const FramePlan &fp = bp.frames[f];
   const FrameState *st = fp.st;
   if (!fp.run_coding || load_status(st) != RSZ_OK) return;
@@ -2760,7 +2749,7 @@ __global__ __launch_bounds__(256) void k_run_pack(BatchPlan bp) {
     roi_copy(bp, item - bp.total_chunks);
     return;
   }
-  const uint32_t f = find_frame(bp.chunk_prefix, bp.nframes, item);
+  const uint32_t f = wave_find_frame(bp.chunk_prefix, bp.nframes, item);
   const FramePlan &fp = bp.frames[f];
   const FrameState *st = fp.st;
   if (!fp.run_coding || load_status(st) != RSZ_OK) return;

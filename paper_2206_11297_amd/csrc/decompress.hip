@@ -70,43 +70,18 @@ __device__ __forceinline__ uint32_t rd32(const uint8_t *p, uint64_t off) {
 
 // A batch of streams: each kernel's workgroups are numbered across the
 // frames, kernel K's per-frame counts in the prefix pre[K * (n + 1) ...]; a
-// workgroup finds its frame (the last with prefix <= its index) and works on
-// that frame's plan with its index and count inside the frame.  Every wave
-// searches 64 places at a time (all its lanes are active here): two rounds of
-// loads for up to 4096 frames, where a binary search of 1000 frames made ten
-// dependent ones before a workgroup could start.
-__device__ __forceinline__ uint32_t dec_frame(const uint32_t *pre, uint32_t n, uint32_t b) {
-  const uint32_t lane = threadIdx.x & 63;
-  uint32_t lo = 0, len = n;   // the frame lies in [lo, lo + len)
-  while (len > 1) {
-    const uint32_t step = (len + 63) / 64;
-    const uint32_t k = lane * step;
-    const bool le = k < len && *gm(pre + lo + k) <= b;   // true for lane 0
-    const uint32_t c = (uint32_t)__builtin_popcountll(__ballot(le)) - 1;
-    lo += c * step;
-    len = min(step, len - c * step);
-  }
-  return lo;
-}
+// workgroup finds its frame (wave_find_frame) and works on that frame's plan
+// with its index and count inside the frame.
 #define RSZ_DEC_FRAME_AT(K, BLK)                                           \
   const uint32_t *pre_ = db.pre + (size_t)(K) * (db.n + 1);                \
   const uint32_t blk_ = (BLK);                                             \
-  const uint32_t f_ = dec_frame(pre_, db.n, blk_);                         \
+  const uint32_t f_ = wave_find_frame(pre_, db.n, blk_);                   \
   const uint32_t bid = blk_ - pre_[f_];                                    \
   const uint32_t nblk = pre_[f_ + 1] - pre_[f_];                           \
   (void)bid;                                                               \
   (void)nblk;                                                              \
   const DecodePlan &dp = db.plans[f_]
 #define RSZ_DEC_FRAME(K) RSZ_DEC_FRAME_AT(K, blockIdx.x)
-
-// Workgroups go to the 8 XCDs in turn; each XCD takes a contiguous run of
-// them instead (the last few in order), so that its L2 holds neighbouring
-// pixels (a plain store kernel over 32000 panels of 185 x 388: 1.73 ms in
-// turn, 1.68 in runs; k_dec_panel on them 1.96 and 1.88).
-__device__ __forceinline__ uint32_t xcd_run() {
-  const uint32_t per = gridDim.x / 8;
-  return blockIdx.x < 8 * per ? (blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
-}
 
 __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
   RSZ_DEC_FRAME(0);

@@ -5,17 +5,15 @@
 //
 // k_peaks_init  zeroes each frame's peak counter.
 // k_peaks_find  streams every frame once, 16 float4 loads per lane.  The
-//               rare pixels at or above amax_min are taken by their wave in
-//               rounds: the wave stages the round's neighbourhoods in LDS
-//               with all loads in flight, then one lane per candidate decides
-//               (window maximum, background ring, peak pixels, cuts);
-//               accepted peaks are appended as (panel, row, col) keys.  (A
-//               lane that fetched its neighbourhood itself, one load after
-//               another, spent most of the kernel waiting on them.)
+//               rare pixels at or above amax_min are taken by their whole
+//               wave, a few at a time: a lane a pixel for the window maximum,
+//               which most fail, then the rest of the decision (background
+//               ring, peak pixels, cuts) with its sums taken from lane to
+//               lane; accepted peaks are appended as (panel, row, col) keys.
 // k_peaks_sort  one workgroup per frame: bitonic sort of the keys in LDS, so
 //               the list comes out in raster order whatever the append order.
 //
-// The arithmetic of a decision follows one fixed order on every lane: fp64
+// The arithmetic of a decision follows one fixed order: fp64
 // sums in raster order, a correctly rounded divide, products compared instead
 // of square roots.  Compiled with -ffp-contract=off.
 #include <hip/hip_runtime.h>
@@ -29,80 +27,80 @@ namespace rsz {
 
 namespace {
 
-__device__ __forceinline__ int64_t imax(int64_t a, int64_t b) { return a > b ? a : b; }
-__device__ __forceinline__ int64_t imin(int64_t a, int64_t b) { return a < b ? a : b; }
-__device__ __forceinline__ int64_t iabs(int64_t a) { return a < 0 ? -a : a; }
+// A wave's candidate pixel (i, j) of a panel of H x W at xp (all uniform).
+struct Candidate {
+  const float *xp;
+  int32_t p, i, j;
+};
 
-__device__ __forceinline__ uint32_t peak_frame_of(const uint32_t *prefix, uint32_t nframes,
-                                                  uint32_t item) {
-  uint32_t lo = 0, hi = nframes;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (prefix[mid] <= item) lo = mid; else hi = mid;
-  }
-  return lo;
+// This lane's pixel of the (2r + 1)^2 neighbourhood of the candidate, the
+// o-th in raster order; in: it lies in the neighbourhood and the panel.
+// mul = floor((2^32 - 1) / (2r + 1)) + 1 divides o < 2^16 exactly.
+__device__ __forceinline__ float neighbour(const Candidate &c, int32_t H, int32_t W, int32_t r,
+                                           uint32_t mul, uint32_t o, bool &in, int32_t &du,
+                                           int32_t &dv) {
+  const int32_t side = 2 * r + 1;
+  du = (int32_t)__umulhi(o, mul);
+  dv = (int32_t)o - du * side;
+  du -= r;
+  dv -= r;
+  const int32_t u = c.i + du, v = c.j + dv;
+  in = o < (uint32_t)(side * side) && u >= 0 && u < H && v >= 0 && v < W;
+  return in ? *gm(c.xp + (uint32_t)u * (uint32_t)W + (uint32_t)v) : 0.0f;
 }
 
-// LDS per wave for staged neighbourhoods ((2 * ring_out + 1)^2 pixels each,
-// ring_out <= 15): 1024 floats hold 8 neighbourhoods of the default ring
-// (11 x 11), one of the largest (31 x 31).  Twice that halved the workgroups
-// a CU holds and slowed the streaming part of the kernel by half.
-constexpr int kNbFloats = 1024;
-static_assert(kNbFloats >= 31 * 31, "a neighbourhood must fit");
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
+}
 
-// The decision for pixel (i, j) of a panel of H x W, from its neighbourhood
-// staged in nb: pixel (u, v) at nb[(u - i + R) * (2R + 1) + (v - j + R)],
-// R = ring_out (only in-panel pixels are staged and read).  One lane runs it,
-// in the oracle's order: window maximum (ties to the first pixel in raster
-// order), background ring mean and squared deviations, the cut, the
-// 4-connected component of the maximum, its sum, the cuts.
-__device__ bool peak_decide(const rsz_peak_params &q, const float *nb, int64_t H, int64_t W,
-                            int64_t i, int64_t j) {
-  const int64_t h = q.rank, ww = 2 * h + 1, ro = q.ring_out, ri = q.ring_in, side = 2 * ro + 1;
-  auto at = [&](int64_t u, int64_t v) { return nb[(u - i + ro) * side + (v - j + ro)]; };
-  const float c = at(i, j);
-  for (int64_t u = imax(i - h, 0); u <= imin(i + h, H - 1); ++u)
-    for (int64_t v = imax(j - h, 0); v <= imin(j + h, W - 1); ++v) {
-      if (u == i && v == j) continue;
-      const float o = at(u, v);
-      // earlier pixels must be smaller, later ones not larger (NaN fails both)
-      const bool before = u < i || (u == i && v < j);
-      if (before ? !(o < c) : !(o <= c)) return false;
-    }
-  const int64_t u0 = imax(i - ro, 0), u1 = imin(i + ro, H - 1);
-  const int64_t v0 = imax(j - ro, 0), v1 = imin(j + ro, W - 1);
+// The decision for a candidate that is its window's maximum, by its wave, in
+// the oracle's order: background ring mean and squared deviations, the cut,
+// the 4-connected component of the maximum, its sum, the cuts.  w: lane a *
+// ww + b holds the window's pixel (a, b) (in_w: the lanes inside the panel).
+// The sums take the pixels one after the other from the lanes that hold them,
+// each a readlane and an fp64 operation (one lane reading them from LDS,
+// whatever the others, took longer than a wave's whole share of the frame).
+__device__ bool peak_decide(const rsz_peak_params &q, const Candidate &c, int32_t H, int32_t W,
+                            float w, uint64_t in_w, int lane) {
+  const int32_t h = (int32_t)q.rank, ww = 2 * h + 1;
+  const int32_t ro = (int32_t)q.ring_out, ri = (int32_t)q.ring_in, side = 2 * ro + 1;
+  const uint32_t area = (uint32_t)(side * side), mul = 0xFFFFFFFFu / (uint32_t)side + 1u;
   // background ring: mean, then the sum of squared deviations
-  double sum = 0.0;
-  int64_t m = 0;
-  for (int64_t u = u0; u <= u1; ++u)
-    for (int64_t v = v0; v <= v1; ++v) {
-      if (imax(iabs(u - i), iabs(v - j)) < ri) continue;
-      sum += (double)at(u, v);
-      m++;
+  double sum = 0.0, mu = 0.0, V = 0.0;
+  uint32_t m = 0;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+    for (uint32_t o0 = 0; o0 < area; o0 += 64) {
+      bool in;
+      int32_t du, dv;
+      const float x = neighbour(c, H, W, ro, mul, o0 + (uint32_t)lane, in, du, dv);
+      uint64_t ring = __ballot(in && max(abs(du), abs(dv)) >= ri);
+      if (pass == 0) m += (uint32_t)__builtin_popcountll(ring);
+#pragma unroll 1
+      for (; ring; ring &= ring - 1) {
+        const double v = (double)lane_value(x, __builtin_ctzll(ring));
+        if (pass == 0) {
+          sum += v;
+        } else {
+          const double e = v - mu;
+          V += e * e;
+        }
+      }
     }
-  if (m == 0) return false;
-  const double mu = sum / (double)m;
-  double V = 0.0;
-  for (int64_t u = u0; u <= u1; ++u)
-    for (int64_t v = v0; v <= v1; ++v) {
-      if (imax(iabs(u - i), iabs(v - j)) < ri) continue;
-      const double e = (double)at(u, v) - mu;
-      V += e * e;
+    if (pass == 0) {
+      if (m == 0) return false;
+      mu = sum / (double)m;
     }
+  }
   const double k2V = q.pix_nsigma * q.pix_nsigma * V;
-  // window pixels above the cut, as bits a*ww + b of the (2h+1)^2 window
-  uint64_t above = 0;
-  for (int64_t a = 0; a < ww; ++a)
-    for (int64_t b = 0; b < ww; ++b) {
-      const int64_t u = i - h + a, v = j - h + b;
-      if (u < 0 || u >= H || v < 0 || v >= W) continue;
-      const double d = (double)at(u, v) - mu;
-      if (d > 0.0 && d * d * (double)m > k2V) above |= 1ull << (a * ww + b);
-    }
+  // window pixels above the cut, as bits a*ww + b of the window
+  const double d = (double)w - mu;
+  const uint64_t above = __ballot(d > 0.0 && d * d * (double)m > k2V) & in_w;
   // the 4-connected component of the maximum: grow by one step in each of the
   // four directions until nothing changes (shifts by 1 must not wrap rows)
   uint64_t first_col = 0, last_col = 0;
-  for (int64_t a = 0; a < ww; ++a) {
+  for (int32_t a = 0; a < ww; ++a) {
     first_col |= 1ull << (a * ww);
     last_col |= 1ull << (a * ww + ww - 1);
   }
@@ -114,23 +112,13 @@ __device__ bool peak_decide(const rsz_peak_params &q, const float *nb, int64_t H
     comp = grown;
   }
   double S = 0.0;
-  int64_t n = 0;
-  for (int64_t a = 0; a < ww; ++a)
-    for (int64_t b = 0; b < ww; ++b)
-      if ((comp >> (a * ww + b)) & 1u) {
-        S += (double)at(i - h + a, j - h + b);
-        n++;
-      }
-  if (n < (int64_t)q.npix_min || n > (int64_t)q.npix_max) return false;
+  const uint32_t n = (uint32_t)__builtin_popcountll(comp);
+#pragma unroll 1
+  for (uint64_t k = comp; k; k &= k - 1) S += (double)lane_value(w, __builtin_ctzll(k));
+  if (n < q.npix_min || n > q.npix_max) return false;
   if (!(S > q.atot_min)) return false;
   const double num = S - (double)n * mu;
   return num > 0.0 && num * num * (double)m > q.snr_min * q.snr_min * (double)n * V;
-}
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __global__ __launch_bounds__(256) void k_peaks_init(PeakBatchPlan pp) {
@@ -138,12 +126,17 @@ __global__ __launch_bounds__(256) void k_peaks_init(PeakBatchPlan pp) {
   if (f < pp.nframes) *pp.frames[f].count = 0u;
 }
 
+// HBM bounds it: 1000 frames of 32x185x388 (9.19 GB) take 1.29 ms, 7.1 TB/s,
+// with loads that leave the caches alone (1.44 ms without, 5.6 TB/s in a plain
+// streaming read).  One lane a candidate on neighbourhoods staged in LDS,
+// and a binary search for the frame, took 1.86 ms.
 __global__ __launch_bounds__(256) void k_peaks_find(PeakBatchPlan pp) {
-  const uint32_t f = peak_frame_of(pp.tile_prefix, pp.nframes, blockIdx.x);
+  const uint32_t blk = xcd_run();
+  const uint32_t f = wave_find_frame(pp.tile_prefix, pp.nframes, blk);
   const PeakFramePlan &fp = pp.frames[f];
   if (fp.init_status != RSZ_OK) return;
   const uint64_t npix = (uint64_t)fp.P * fp.H * fp.W;
-  const uint64_t base = (uint64_t)(blockIdx.x - pp.tile_prefix[f]) * kPeakTile;
+  const uint64_t base = (uint64_t)(blk - pp.tile_prefix[f]) * kPeakTile;
   const float *x = fp.frame;
   constexpr int K = (int)(kPeakTile / 1024);   // float4 loads per lane
   float v[K][4];
@@ -151,14 +144,15 @@ __global__ __launch_bounds__(256) void k_peaks_find(PeakBatchPlan pp) {
   for (int k = 0; k < K; ++k) {
     const uint64_t e0 = base + (uint64_t)(k * 256 + threadIdx.x) * 4;
     if (e0 + 4 <= npix) {
-      const float4 w = *(const float4 *)(x + e0);   // the frame is 16-byte aligned
+      // (the frame is 16-byte aligned)
+      const f32x4 w = __builtin_nontemporal_load(gm((const f32x4 *)(x + e0)));
       v[k][0] = w.x;
       v[k][1] = w.y;
       v[k][2] = w.z;
       v[k][3] = w.w;
     } else {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[k][t] = e0 + t < npix ? x[e0 + t] : -INFINITY;
+      for (int t = 0; t < 4; ++t) v[k][t] = e0 + t < npix ? *gm(x + e0 + t) : -INFINITY;
     }
   }
   // candidates: pixels at or above amax_min (amax_f is the smallest float
@@ -169,65 +163,70 @@ __global__ __launch_bounds__(256) void k_peaks_find(PeakBatchPlan pp) {
   for (int k = 0; k < K; ++k)
 #pragma unroll
     for (int t = 0; t < 4; ++t) cand |= (uint64_t)(v[k][t] >= amax_f) << (4 * k + t);
-  // The wave takes its candidates in rounds of up to kNbFloats / side^2: every
-  // lane loads part of the round's neighbourhoods into the wave's LDS slice
-  // (all loads in flight together), then one lane per candidate decides.
+  // The wave takes its candidates together, kBatch at a time: their windows (at
+  // most 7 x 7, a pixel a lane) are loaded with all loads in flight; most
+  // are not their window's maximum and end there (ties go to the first pixel
+  // in raster order; NaN fails every comparison).
   uint64_t pending = __builtin_amdgcn_uicmp((uint32_t)(cand | (cand >> 32)), 0u, 33 /* ne */);
   if (!pending) return;
-  __shared__ float s_nb[4][kNbFloats];
-  __shared__ int32_t s_pij[4][64][3];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  float *nb = s_nb[wv];
-  int32_t(*pij)[3] = s_pij[wv];
+  constexpr int kBatch = 4;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const rsz_peak_params q = pp.q;
   // a frame has < 2^31 pixels: 32-bit index arithmetic
-  const int32_t H = (int32_t)fp.H, W = (int32_t)fp.W, ro = (int32_t)q.ring_out;
-  const int32_t side = 2 * ro + 1, area = side * side;
-  const int per_round = min(64, kNbFloats / area);
-  uint64_t cm = 0;   // the lane's candidates not yet queued
-  int L = -1;        // the lane whose candidates are being queued
-  for (;;) {
-    // queue up to per_round candidates (uniform): their (panel, row, col)
-    int nq = 0;
-    while (nq < per_round) {
-      if (!cm) {
-        if (!pending) break;
+  const int32_t H = (int32_t)fp.H, W = (int32_t)fp.W, h = (int32_t)q.rank;
+  const int32_t ww = 2 * h + 1, mid = h * ww + h;
+  const uint32_t mul = 0xFFFFFFFFu / (uint32_t)ww + 1u;
+  const FastDiv dW = fp.fd_W, dH = fp.fd_H;
+  uint32_t *count = fp.count;
+  uint64_t *keys = fp.keys;
+  const uint32_t cap = fp.cap;
+  uint64_t cm = 0;   // the candidates of lane L not yet taken
+  int L = -1;
+  for (bool more = true; more;) {
+    Candidate c[kBatch];
+    float w[kBatch];
+    uint64_t in_w[kBatch];
+    int n = 0;
+#pragma unroll
+    for (int t = 0; t < kBatch; ++t) {
+      if (!cm && pending) {
         L = __builtin_ctzll(pending);
         pending &= pending - 1;
-        cm = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(cand >> 32), L) << 32) |
-             __builtin_amdgcn_readlane((uint32_t)cand, L);
+        cm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(cand >> 32), L) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)cand, L);
+      }
+      in_w[t] = 0;
+      if (!cm) {
+        more = false;
+        continue;
       }
       const int b = __builtin_ctzll(cm);
       cm &= cm - 1;
       const uint32_t e = (uint32_t)(base + (uint64_t)((b >> 2) * 256 + wv * 64 + L) * 4 + (b & 3));
+      const uint32_t r = fdiv(dW, e), pn = fdiv(dH, r);
+      c[t].p = (int32_t)pn;
+      c[t].i = (int32_t)(r - pn * (uint32_t)H);
+      c[t].j = (int32_t)(e - r * (uint32_t)W);
+      c[t].xp = x + (uint64_t)pn * (uint32_t)H * (uint32_t)W;
+      bool in;
+      int32_t du, dv;
+      w[t] = neighbour(c[t], H, W, h, mul, (uint32_t)lane, in, du, dv);
+      in_w[t] = __ballot(in);
+      n = t + 1;
+    }
+#pragma unroll
+    for (int t = 0; t < kBatch; ++t) {
+      if (t >= n) continue;
+      const float v0 = lane_value(w[t], mid);
+      const bool ok = lane < mid ? w[t] < v0 : w[t] <= v0;
+      if (__ballot(!ok) & in_w[t] & ~(1ull << mid)) continue;
+      if (!peak_decide(q, c[t], H, W, w[t], in_w[t], lane)) continue;
       if (lane == 0) {
-        const uint32_t r = e / (uint32_t)W;
-        pij[nq][0] = (int32_t)(r / (uint32_t)H);
-        pij[nq][1] = (int32_t)(r % (uint32_t)H);
-        pij[nq][2] = (int32_t)(e % (uint32_t)W);
-      }
-      nq++;
-    }
-    if (nq == 0) break;
-    wave_sync();
-    // stage: candidate c's neighbourhood at nb[c * area, (c + 1) * area)
-    for (int c = 0; c < nq; ++c) {
-      const int32_t p = pij[c][0], i = pij[c][1], j = pij[c][2];
-      const float *xp = x + ((uint64_t)p * H) * W;
-      for (int32_t o = lane; o < area; o += 64) {
-        const int32_t du = o / side, u = i - ro + du, w = j - ro + (o - du * side);
-        if (u >= 0 && u < H && w >= 0 && w < W) nb[c * area + o] = xp[(uint32_t)u * W + w];
+        const uint32_t slot = atomicAdd(count, 1u);
+        if (slot < cap)
+          keys[slot] = ((uint64_t)c[t].p << 32) | ((uint64_t)c[t].i << 16) | (uint64_t)c[t].j;
       }
     }
-    wave_sync();
-    if (lane < nq) {
-      const int32_t p = pij[lane][0], i = pij[lane][1], j = pij[lane][2];
-      if (peak_decide(q, nb + lane * area, H, W, i, j)) {
-        const uint32_t slot = atomicAdd(fp.count, 1u);
-        if (slot < fp.cap) fp.keys[slot] = ((uint64_t)p << 32) | ((uint64_t)i << 16) | (uint64_t)j;
-      }
-    }
-    wave_sync();
   }
 }
 

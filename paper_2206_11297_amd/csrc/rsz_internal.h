@@ -76,6 +76,34 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
   return x;
 }
 
+// The frame owning flat work item b: the last with prefix <= b.  Every wave
+// searches 64 places at a time (all its lanes are active where it is called):
+// two rounds of loads for up to 4096 frames, where a binary search of 1000
+// frames made ten dependent ones before a workgroup could start.
+__device__ __forceinline__ uint32_t wave_find_frame(const uint32_t *prefix, uint32_t n, uint32_t b) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t lo = 0, len = n;   // the frame lies in [lo, lo + len)
+  while (len > 1) {
+    const uint32_t step = (len + 63) / 64;
+    const uint32_t k = lane * step;
+    const bool le = k < len && *gm(prefix + lo + k) <= b;   // true for lane 0
+    const uint32_t c = (uint32_t)__builtin_popcountll(__ballot(le)) - 1;
+    lo += c * step;
+    len = min(step, len - c * step);
+  }
+  return lo;
+}
+
+// Workgroups go to the 8 XCDs in turn; each XCD takes a contiguous run of
+// them instead (the last few in order), so that its L2 holds neighbouring
+// pixels (a plain store kernel over 32000 panels of 185 x 388: 1.73 ms in
+// turn, 1.68 in runs; k_dec_panel on them 1.96 and 1.88; k_peaks_find on 1000
+// frames of 32 of them 1.86 and 1.80).
+__device__ __forceinline__ uint32_t xcd_run() {
+  const uint32_t per = gridDim.x / 8;
+  return blockIdx.x < 8 * per ? (blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
+}
+
 // Division by a run-time constant d (1 <= d < 2^16) through a multiply: with
 // l = ceil(log2 d) and m = floor(2^32 (2^l - d) / d) + 1, n / d = (hi32(n m) +
 // n) >> l for every n < 2^31 (Granlund and Montgomery, "Division by invariant
@@ -311,6 +339,7 @@ constexpr uint32_t kPeakCapMax = 8192;    // most peaks a frame's list may hold
 
 struct PeakFramePlan {
   uint32_t P, H, W, cap;
+  FastDiv fd_W, fd_H;
   int32_t init_status;       // RSZ_OK or RSZ_ERR_ARG
   const float *frame;
   rsz_peak *out;             // cap entries (caller's)

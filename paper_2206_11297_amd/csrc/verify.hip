@@ -164,22 +164,13 @@ __device__ __forceinline__ uint32_t verify_any(const VerifyRows &v, uint32_t b, 
 // in blocks of 256 rows, which left 12 waves a CU, took 1.10 ms.
 __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
   extern __shared__ uint32_t s_mask[];
-  __shared__ uint32_t s_f;
-  if (threadIdx.x == 0) {
-    uint32_t lo = 0, hi = vb.n;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (vb.wg_prefix[mid] <= blockIdx.x) lo = mid; else hi = mid;
-    }
-    s_f = lo;
-  }
-  __syncthreads();
-  const uint32_t f = s_f;
+  const uint32_t blkx = xcd_run();
+  const uint32_t f = wave_find_frame(vb.wg_prefix, vb.n, blkx);
   const VerifyFrame &vf = vb.frames[f];
   // both stages of this frame finished without an error (else k_vdone
   // reports it)
   if (!vf.valid || vf.cplan->st->status != RSZ_OK || *vf.dplan->status != RSZ_OK) return;
-  const uint32_t blk = blockIdx.x - vb.wg_prefix[f];
+  const uint32_t blk = blkx - vb.wg_prefix[f];
   const uint32_t p = blk / vf.chunks, r0 = (blk - p * vf.chunks) * vf.rows;
   const uint32_t H = vf.H, W = vf.W, b = vf.b;
   const uint32_t r1 = min(r0 + vf.rows, H), nr = r1 - r0, wpr = (W + 31) / 32;
