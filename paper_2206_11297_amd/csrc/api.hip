@@ -280,7 +280,7 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
   uint32_t *kp = rp + (nframes + 1);
   uint32_t *xp = kp + (nframes + 1);
   uint64_t tiles = 0, units = 0, npk_total = 0, chunks_done = 0, fixes = 0;
-  bool all_vec = true, all_wide = true;
+  bool all_vec = true, all_lines = true, all_wide = true;
   uint64_t all_chunks = 0;
   for (uint32_t f = 0; f < nframes; ++f)
     if (valid[f]) all_chunks += gs[f].nchunks;
@@ -327,6 +327,7 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
     fp.vec = (p->bin == 2 || p->bin == 4) && p->width % p->bin == 0 &&
              (uintptr_t)d[f].frame % (4 * p->bin) == 0;
     all_vec = all_vec && fp.vec;
+    all_lines = all_lines && fp.vec && p->width % 32 == 0 && (uintptr_t)d[f].frame % 128 == 0;
     all_wide = all_wide && p->width >= p->bin;
     fp.frame = d[f].frame;
     fp.peaks = (const int32_t *)d[f].peaks;
@@ -441,6 +442,7 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
   hp.bp.total_peaks = (uint32_t)npk_total;
   hp.bp.cpw = cpw;
   hp.bp.all_vec = all_vec ? 1u : 0u;
+  hp.bp.all_lines = all_lines ? 1u : 0u;
   hp.bp.all_wide = all_wide ? 1u : 0u;
   hp.bp.bin_waves = wpg;
   hp.bp.frames = (const FramePlan *)(ws + L.plans);

@@ -398,7 +398,9 @@ __device__ __forceinline__ int32_t reduce_bin(const BinPix<BB> &px, uint32_t H, 
 // Vector path (b = 2 or 4 with W % b == 0, rows 8- or 16-byte aligned): a
 // lane's bin row is one float2/float4 load at a 32-bit byte offset from a
 // wave-uniform row pointer, and the b x b pixels reduce branch-free.
-template <int BB, bool BG>
+// NT: loads that leave the caches alone, for frames whose rows are whole
+// 128-byte lines, so that no other wave wants a line again.
+template <int BB, bool BG, bool NT>
 __device__ __forceinline__ void load_vec(BinPix<BB> &px, const float *__restrict__ fr, uint32_t H,
                                          uint32_t W, uint32_t I, uint32_t lofs,
                                          const uint32_t *mlane, int64_t R0, int wpr) {
@@ -407,11 +409,13 @@ __device__ __forceinline__ void load_vec(BinPix<BB> &px, const float *__restrict
     const uint32_t i = min(I * BB + di, H - 1);
     const char *row = (const char *)(fr + (size_t)i * W);
     if constexpr (BB == 2) {
-      const f32x2 x = *gm((const f32x2 *)(row + lofs));
+      const RSZ_G f32x2 *a = gm((const f32x2 *)(row + lofs));
+      const f32x2 x = NT ? __builtin_nontemporal_load(a) : *a;
       px.v[di][0] = x.x;
       px.v[di][1] = x.y;
     } else {
-      const f32x4 x = *gm((const f32x4 *)(row + lofs));
+      const RSZ_G f32x4 *a = gm((const f32x4 *)(row + lofs));
+      const f32x4 x = NT ? __builtin_nontemporal_load(a) : *a;
       px.v[di][0] = x.x;
       px.v[di][1] = x.y;
       px.v[di][2] = x.z;
@@ -610,13 +614,13 @@ __device__ __forceinline__ void flush_zb(const SparseStage &stg, uint8_t *zb, ui
 // r = q here and k_lorenzo_dims corrects it with the q of the row before's
 // last bin, kept in qedge.  Dimension 3 leaves the panel's 2D residual for
 // k_lorenzo_dims to difference across panels, and counts no histogram here.
-// MODE: how rows load -- kScalar, kVec (load_vec), kAny (load_any).
-constexpr int kScalar = 0, kVec = 1, kAny = 2;
+// MODE: how rows load -- kScalar, kVec and kVecNt (load_vec), kAny (load_any).
+constexpr int kScalar = 0, kVec = 1, kAny = 2, kVecNt = 3;
 template <int BB, int MODE, bool BG, bool DEBUG, int DIM>
 __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32_t seg,
                                          uint32_t cg, uint32_t *hist, uint32_t *mask,
                                          const double *inv, SparseStage *stg) {
-  constexpr bool VEC = MODE == kVec;
+  constexpr bool NT = MODE == kVecNt, VEC = MODE == kVec || NT;
   constexpr int NS = group_strips(BB);
   const int lane = threadIdx.x & 63;
   const int b = BB ? BB : (int)fp.b;
@@ -756,8 +760,8 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
   do {                                                                                      \
     if constexpr (VEC) {                                                                    \
       const uint32_t jv_ = RSZ_JC(s);                                                       \
-      load_vec<BB, BG>(px[s], fr, H, W, (Irow), jv_ * (uint32_t)b * 4u, mask + RSZ_MW(jv_), \
-                       R0, wpr);                                                            \
+      load_vec<BB, BG, NT>(px[s], fr, H, W, (Irow), jv_ * (uint32_t)b * 4u,                 \
+                           mask + RSZ_MW(jv_), R0, wpr);                                    \
     } else if constexpr (MODE == kAny) {                                                    \
       load_any<BB, BG>(px[s], fr, H, W, (Irow), RSZ_JC(s), mask, R0, wpr, Cm);              \
     } else {                                                                                \
@@ -893,7 +897,7 @@ __device__ __forceinline__ void bin_tile(const FramePlan &fp, uint32_t p, uint32
       BinPix<BB> pxp;
       int32_t qv;
       if constexpr (VEC) {
-        load_vec<BB, BG>(pxp, fr, H, W, I, J * (uint32_t)b * 4u, mask + RSZ_MW(J), R0, wpr);
+        load_vec<BB, BG, NT>(pxp, fr, H, W, I, J * (uint32_t)b * 4u, mask + RSZ_MW(J), R0, wpr);
         const uint32_t rowbits = (1u << (min((uint32_t)BB, H - I * BB) * BB)) - 1u;
         qv = reduce_vec<BB, BG>(pxp, rowbits, (int)((J * b) & 31), inv, step, range_err, DEBUG,
                                 Sd, nd);
@@ -1002,10 +1006,10 @@ __device__ __forceinline__ void k_bin_body(BatchPlan bp) {
     // ONLY: every frame of the batch takes that path, and the kernel holds
     // only its registers
     bool vec = false;
-    if constexpr (ONLY == kAny) {
+    if constexpr (ONLY == kAny || ONLY == kVecNt) {
       vec = true;
-      if (bg) bin_tile<BB, kAny, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
-      else bin_tile<BB, kAny, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+      if (bg) bin_tile<BB, ONLY, true, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
+      else bin_tile<BB, ONLY, false, DEBUG, DIM>(fp, panel, seg, cg, s_hist, mask, s_inv, stg);
     } else if constexpr (BB == 2 || BB == 4) {
       vec = fp.vec != 0;
       if (vec) {
@@ -1033,10 +1037,13 @@ __global__ __launch_bounds__(256) void k_bin(BatchPlan bp) {
 // the kernel holds its strips' loads and its sums in 128 registers without
 // spilling (five waves spill 23 registers, and measured 0.17 ms slower on
 // the 1000-frame CSPAD batch; six spill more).
-template <int BB, int DIM>
+// NT: every frame's rows are whole lines (load_vec; 48 frames 8x512x1024 0.21
+// -> 0.19 ms, 64 of 16x512x1024 0.53 -> 0.51; with rows of 1552 bytes, whose
+// lines two strips or a row and the next share, 1.84 -> 1.92 ms).
+template <int BB, int DIM, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bin_vec(
     BatchPlan bp) {
-  k_bin_body<BB, false, DIM, kVec>(bp);
+  k_bin_body<BB, false, DIM, NT ? kVecNt : kVec>(bp);
 }
 
 // Batches of one bin factor (2 to 8) and dimension whose frames are at least
@@ -2910,11 +2917,13 @@ static hipError_t launch_bin(const BatchPlan &bp, uint32_t b, hipStream_t s) {
   switch (b) {
     case 1: RSZ_LAUNCH_B("k_bin", (k_bin<1, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;
     case 2:
-      if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM>), grid, 64 * bp.bin_waves, s, bp);
+      if (!DEBUG && DIM != 0 && bp.all_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
+      else if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM, false>), grid, 64 * bp.bin_waves, s, bp);
       else RSZ_LAUNCH_B("k_bin", (k_bin<2, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp);
       break;
     case 4:
-      if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM>), grid, 64 * bp.bin_waves, s, bp);
+      if (!DEBUG && DIM != 0 && bp.all_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
+      else if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM, false>), grid, 64 * bp.bin_waves, s, bp);
       else RSZ_LAUNCH_B("k_bin", (k_bin<4, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp);
       break;
     case 3: RSZ_LAUNCH_B("k_bin", (k_bin<3, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;

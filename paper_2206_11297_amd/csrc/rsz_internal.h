@@ -215,6 +215,7 @@ struct BatchPlan {
   uint32_t total_tiles, total_units, total_peaks, total_chunks;
   uint32_t cpw;                  // chunks encoded by one k_encode workgroup
   uint32_t all_vec;              // every frame's rows load as float2/float4 (k_bin)
+  uint32_t all_lines;            // and are whole 128-byte lines
   uint32_t all_wide;             // every frame is at least a bin wide (k_bin_any)
   uint32_t bin_waves;            // waves per k_bin workgroup (1..kWaves)
   uint32_t total_fix;            // workgroups of k_lorenzo_dims (0: every frame is 2D)
