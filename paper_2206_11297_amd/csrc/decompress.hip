@@ -28,9 +28,8 @@
 //                   and their inverse prediction (k_dec_roi_unpred for
 //                   windows larger than LDS holds).
 //   k_dec_roi       ROI windows restored from the payload bits, one wave
-//                   per window.
-//   k_dec_roi_check overlapping windows must agree on their shared pixels
-//                   (one wave per window).
+//                   per window; overlapping windows must agree on their
+//                   shared pixels (with many windows: k_dec_roi_check).
 // The inverse Lorenzo step is the prefix sum of the residuals along each
 // axis the predictor spans.
 #include <algorithm>
@@ -1537,28 +1536,71 @@ template <bool CHECK>
 __device__ __forceinline__ bool roi_window(const DecodePlan &dp, uint32_t k, uint32_t lane) {
   const uint32_t w = dp.w, ww = w * w;
   const uint16_t *pk = (const uint16_t *)(dp.in + dp.off_peaks);
-  const uint32_t *pay =
-      (dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi)) + (size_t)k * ww;
+  const RSZ_G uint32_t *pay = gm(
+      (dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi)) + (size_t)k * ww);
   const uint32_t pa = pk[3 * k];
   if (pa >= dp.P) return false;
   const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W;
   const int32_t i0 = (int32_t)pk[3 * k + 1] - h, j0 = (int32_t)pk[3 * k + 2] - h;
-  uint32_t *fr = (uint32_t *)dp.frame + (size_t)pa * dp.H * dp.W;
+  RSZ_G uint32_t *fr = gm((uint32_t *)dp.frame + (size_t)pa * dp.H * dp.W);
   const uint32_t du = 64 / w, dv = 64 % w;
   uint32_t u = lane / w, v = lane - u * w;
   bool bad = false;
-  for (uint32_t e = lane; e < ww; e += 64) {
-    const int32_t i = i0 + (int32_t)u, j = j0 + (int32_t)v;
-    if (i >= 0 && i < H && j >= 0 && j < W) {
-      uint32_t *px = fr + (size_t)i * dp.W + j;
-      if (CHECK) bad |= *px != pay[e];
-      else *px = pay[e];
+  constexpr uint32_t kSlots = 8;   // elements a lane loads before it stores any
+  for (uint32_t e0 = lane; e0 < ww; e0 += 64 * kSlots) {
+    uint32_t x[kSlots];
+#pragma unroll
+    for (uint32_t t = 0; t < kSlots; ++t)
+      x[t] = e0 + 64 * t < ww ? pay[e0 + 64 * t] : 0u;
+#pragma unroll
+    for (uint32_t t = 0; t < kSlots; ++t) {
+      const int32_t i = i0 + (int32_t)u, j = j0 + (int32_t)v;
+      if (e0 + 64 * t < ww && i >= 0 && i < H && j >= 0 && j < W) {
+        RSZ_G uint32_t *px = fr + (size_t)i * dp.W + j;
+        if (CHECK) bad |= *px != x[t];
+        else *px = x[t];
+      }
+      u += du;
+      v += dv;
+      if (v >= w) {
+        v -= w;
+        ++u;
+      }
     }
-    u += du;
-    v += dv;
-    if (v >= w) {
-      v -= w;
-      ++u;
+  }
+  return bad;
+}
+
+// Windows that overlap must carry the same bits for the pixels they share.
+// With few windows (kRoiPairs) the wave of window k looks for the earlier
+// ones that meet it, 64 at a time, and compares the two payloads; more
+// windows are compared with the frame that all of them were written to, by
+// k_dec_roi_check (the search grows with the square of their number).  The
+// comparison by a pass over the frame took 70 us on 1000 CSPAD frames.
+constexpr uint32_t kRoiPairs = 4096;
+__device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t lane) {
+  const uint32_t w = dp.w, ww = w * w;
+  const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
+  const RSZ_G uint32_t *pay =
+      gm(dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi));
+  const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W, iw = (int32_t)w;
+  const int32_t pa = pk[3 * k], r = pk[3 * k + 1], c = pk[3 * k + 2];
+  bool bad = false;
+  for (uint32_t b = 0; b < k; b += 64) {
+    const uint32_t o = min(b + lane, k - 1);
+    const int32_t opa = pk[3 * o], dr = (int32_t)pk[3 * o + 1] - r, dc = (int32_t)pk[3 * o + 2] - c;
+    const bool meet = b + lane < k && opa == pa && dr > -iw && dr < iw && dc > -iw && dc < iw;
+    for (uint64_t m = __ballot(meet); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const int32_t er = __builtin_amdgcn_readlane(dr, l), ec = __builtin_amdgcn_readlane(dc, l);
+      const RSZ_G uint32_t *mine = pay + (size_t)k * ww, *other = pay + (size_t)(b + l) * ww;
+      for (uint32_t e = lane; e < ww; e += 64) {   // element (u, v) of window k
+        const int32_t u = (int32_t)(e / w), v = (int32_t)(e - (uint32_t)u * w);
+        const int32_t ou = u - er, ov = v - ec;    // and of the other
+        const int32_t i = r - h + u, j = c - h + v;
+        if (ou >= 0 && ou < iw && ov >= 0 && ov < iw && i >= 0 && i < H && j >= 0 && j < W)
+          bad |= mine[e] != other[(uint32_t)ou * w + (uint32_t)ov];
+      }
     }
   }
   return bad;
@@ -1569,6 +1611,7 @@ __global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
   const uint32_t k = bid * 4 + (threadIdx.x >> 6);
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
   roi_window<false>(dp, k, threadIdx.x & 63);
+  if (dp.npeaks <= kRoiPairs && roi_overlaps(dp, k, threadIdx.x & 63)) corrupt(dp.status);
 }
 __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   RSZ_DEC_FRAME(13);
@@ -1602,7 +1645,8 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
     nb[10] = std::max(1u, (dp.npeaks + wins - 1) / wins);   // (no window: the lengths' check)
     if (!roi_in_lds(dp.w)) nb[11] = (dp.npeaks + 3) / 4;
   }
-  nb[12] = nb[13] = (dp.npeaks + 3) / 4;   // a wave per window
+  nb[12] = (dp.npeaks + 3) / 4;   // a wave per window
+  if (dp.npeaks > kRoiPairs) nb[13] = nb[12];
 }
 
 #define RSZ_DLAUNCH_S(k, name, kern, block, lds)                       \

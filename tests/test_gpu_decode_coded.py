@@ -84,3 +84,26 @@ def test_roi_windows(w, n):
         c[int(rng.integers(80, c.size))] ^= np.uint8(1 << int(rng.integers(0, 8)))
         host.append(c)
     _decode(host)
+
+
+@pytest.mark.parametrize("n,w", [(20, 5), (65, 9), (4096, 3), (4097, 3)])
+def test_windows_must_agree_on_shared_pixels(n, w):
+    """One payload word changed at a time (in a shared pixel, in a pixel of one
+    window alone, in one outside the frame): the oracle's status, and its frame
+    where the stream is still valid.  4096 windows is the most that are
+    compared with each other instead of with the frame."""
+    f, _ = synth.tiny_case(990 + w, (2, 60, 70), 0, "normal", scale=50.0)
+    rng = np.random.default_rng(n)
+    pk = np.stack([rng.integers(0, 2, n), rng.integers(0, 60, n), rng.integers(0, 70, n)],
+                  axis=1).astype(np.int32)
+    pk[n // 2] = pk[n // 3]
+    st, s, _ = O.compress(O.params(2, 60, 70, w, 2, 1.0), f, pk)
+    assert st == O.OK
+    off = 80 + (6 * n + 3) // 4 * 4
+    host = [s]
+    for t in range(24 if n < 1000 else 6):
+        c = s.copy()
+        k = (n // 2, 0, n - 1, int(rng.integers(0, n)))[t % 4]
+        c[off + 4 * (k * w * w + int(rng.integers(0, w * w))) + t % 4] ^= np.uint8(1 << (t % 8))
+        host.append(c)
+    _decode(host)
