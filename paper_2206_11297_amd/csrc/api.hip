@@ -498,6 +498,56 @@ static int stage_to_device(void *dst, const void *src, size_t n, hipStream_t s) 
   return RSZ_OK;
 }
 
+// Results of the calls that wait for the device: pinned words that kernels (or
+// a copy) write and the host reads after its stream synchronisation.  A copy
+// to pageable memory instead made the runtime stage it and wait twice.  One
+// page, made once; a call takes a slot and gives it back, and a call that
+// finds none falls back to the workspace and a pageable copy.
+namespace {
+struct ResultSlot {
+  uint64_t bytes;
+  int32_t status;
+  uint8_t header[kHeader];
+  uint8_t pad[128 - 12 - kHeader];
+};
+static_assert(sizeof(ResultSlot) == 128, "a slot is two cache lines");
+constexpr int kResultSlots = 32;
+std::mutex g_result_mu;
+ResultSlot *g_results = nullptr;
+bool g_results_failed = false;
+uint32_t g_results_used = 0;   // bit i: slot i is taken
+
+class Result {
+ public:
+  Result() {
+    std::lock_guard<std::mutex> lk(g_result_mu);
+    if (!g_results && !g_results_failed) {
+      void *p = nullptr;
+      if (hipHostMalloc(&p, kResultSlots * sizeof(ResultSlot),
+                        hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+        g_results = (ResultSlot *)p;
+      else
+        g_results_failed = true;
+    }
+    if (!g_results || g_results_used == ~0u) return;
+    index_ = __builtin_ctz(~g_results_used);
+    g_results_used |= 1u << index_;
+    slot = g_results + index_;
+  }
+  ~Result() {
+    if (!slot) return;
+    std::lock_guard<std::mutex> lk(g_result_mu);
+    g_results_used &= ~(1u << index_);
+  }
+  Result(const Result &) = delete;
+  Result &operator=(const Result &) = delete;
+  ResultSlot *slot = nullptr;   // null: none free
+
+ private:
+  int index_ = 0;
+};
+}  // namespace
+
 // Host record of a prepared batch (the public rsz_batch_plan is its storage).
 struct PlanRecord {
   BatchPlan bp;
@@ -817,6 +867,28 @@ static int single_frame(const rsz_params *p, const float *d_frame, const rsz_pea
     return RSZ_ERR_ARG;
   if ((uintptr_t)d_frame % 16 || (uintptr_t)d_ws % 256 || (d_out && (uintptr_t)d_out % 16))
     return RSZ_ERR_ARG;
+  // the size and status come back through pinned words (the allocation-free
+  // entry point and the debug call: through the workspace's tail)
+  if (!dbg && !direct_copy) {
+    Result result;
+    void *dev = nullptr;
+    if (result.slot && hipHostGetDevicePointer(&dev, result.slot, 0) == hipSuccess) {
+      if (ws_bytes < single_extra()) return RSZ_ERR_WORKSPACE;
+      ResultSlot *ds = (ResultSlot *)dev;
+      rsz_frame_desc d = one_desc(p, d_frame, d_peaks, npeaks, d_out, out_cap);
+      HostPlan hp;
+      st = enqueue(1, &d, &ds->bytes, &ds->status, d_ws, ws_bytes - single_extra(), s, nullptr,
+                   false, hp);
+      // (the slot is the device's until the stream has finished, also when
+      // the call failed half way)
+      if (hipStreamSynchronize(s) != hipSuccess) return st ? st : RSZ_ERR_HIP;
+      if (st) return st;
+      const int32_t status = *(volatile int32_t *)&result.slot->status;
+      if (status == RSZ_OK || status == RSZ_ERR_CAPACITY)
+        *h_out_bytes = *(volatile uint64_t *)&result.slot->bytes;
+      return status;
+    }
+  }
   uint64_t need = 0;
   rsz_workspace_bytes(p, npeaks, &need);
   if (ws_bytes < need) return RSZ_ERR_WORKSPACE;
@@ -931,11 +1003,16 @@ int rsz_decompress(const void *d_in, uint64_t in_bytes, float *d_frame, uint64_t
       (uintptr_t)d_ws % 256)
     return RSZ_ERR_ARG;
   if (in_bytes < kHeader) return RSZ_ERR_CORRUPT;
-  uint8_t hdr[80];
-  if (hipMemcpyAsync(hdr, d_in, 80, hipMemcpyDeviceToHost, s) != hipSuccess) return RSZ_ERR_HIP;
+  Result result;
+  uint8_t own_header[kHeader];
+  int32_t own_status = 0;
+  uint8_t *hdr = result.slot ? result.slot->header : own_header;
+  int32_t *status = result.slot ? &result.slot->status : &own_status;
+  if (hipMemcpyAsync(hdr, d_in, kHeader, hipMemcpyDeviceToHost, s) != hipSuccess)
+    return RSZ_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return RSZ_ERR_HIP;
   DecodePlan dp;
-  int st = parse_header(hdr, 80, in_bytes, nullptr, nullptr, &dp);
+  int st = parse_header(hdr, kHeader, in_bytes, nullptr, nullptr, &dp);
   if (st) return st;
   if (frame_elems < (uint64_t)dp.P * dp.H * dp.W) return RSZ_ERR_ARG;
   // a batch of one stream
@@ -943,11 +1020,10 @@ int rsz_decompress(const void *d_in, uint64_t in_bytes, float *d_frame, uint64_t
   int32_t *status_word = nullptr;
   st = decode_streams(1, &it, (uint8_t *)d_ws, ws_bytes, s, nullptr, &status_word);
   if (st) return st;
-  int32_t status = 0;
-  if (hipMemcpyAsync(&status, status_word, 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+  if (hipMemcpyAsync(status, status_word, 4, hipMemcpyDeviceToHost, s) != hipSuccess)
     return RSZ_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return RSZ_ERR_HIP;
-  return status;
+  return *(volatile int32_t *)status;
 }
 
 static int decode_items(uint32_t n, const rsz_decode_desc *d, int32_t *d_status,

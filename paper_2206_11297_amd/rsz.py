@@ -423,8 +423,13 @@ def decompress(stream, ws=None):
     frame = torch.empty((p.panels, p.height, p.width), dtype=torch.float32, device=stream.device)
     if ws is None or ws.numel() < wsb:
         ws = workspace(wsb, stream.device)
-    st = rsz_decompress(_ptr(stream), stream.numel(), _ptr(frame), frame.numel(), _ptr(ws),
-                        ws.numel(), _stream())
+    # a batch of one: the header, read above, is not read from the device again
+    desc = (rsz_decode_desc * 1)((stream.data_ptr(), stream.numel(),
+                                  C.cast(C.c_char_p(head), C.c_void_p), frame.data_ptr(),
+                                  frame.numel()))
+    status = torch.empty(1, dtype=torch.int32, device=stream.device)
+    st = rsz_decompress_batch(desc, _ptr(status), _ptr(ws), ws.numel(), _stream())
+    st = st or int(status)
     if st:
         raise RszError(st, "rsz_decompress")
     return frame
