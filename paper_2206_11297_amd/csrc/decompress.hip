@@ -47,7 +47,7 @@ constexpr int32_t kMark = INT32_MIN;  // residual slot waiting for its outlier
 // bit after the last << 16 | their count << 24
 constexpr int kTabFirst = 0, kTabCount = kTabFirst + 33,
               kTabOffs = kTabCount + 33, kTabSorted = kTabOffs + 33,
-              kTabMulti = kTabSorted + kNumSym, kTabWords = kTabMulti + 2 * (1 << kLutBits);
+              kTabMulti = kTabSorted + kNumSym + 1 /* 8-byte aligned */, kTabWords = kTabMulti + 2 * (1 << kLutBits);
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -82,85 +82,131 @@ __device__ __forceinline__ uint32_t rd32(const uint8_t *p, uint64_t off) {
   const DecodePlan &dp = db.plans[f_]
 #define RSZ_DEC_FRAME(K) RSZ_DEC_FRAME_AT(K, blockIdx.x)
 
+// One workgroup's chain of steps, each short: a thread takes four symbols'
+// lengths and all its loads go out first; the canonical first codes, the
+// Kraft sum and the number of used symbols come from the counts per length;
+// up to kRankSyms used symbols find their place by counting (a symbol a
+// thread, LDS broadcasts); a window's codeword is found against the first
+// codes in scalar registers, and the eight windows of a thread go through
+// the multi-symbol lookups together. One CSPAD stream: 12.2 us
+// (17.6 with LDS searches one after the other and one thread's loops).
+constexpr uint32_t kRankSyms = 256;
 __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
   RSZ_DEC_FRAME(0);
   __shared__ uint8_t s_len[kNumSym];
   __shared__ uint32_t s_count[kMaxLen + 1], s_first[kMaxLen + 1], s_offs[kMaxLen + 1],
       s_fill[kMaxLen + 1];
-  __shared__ uint16_t s_sorted[kNumSym];
-  __shared__ uint32_t s_lut[1 << kLutBits];
-  __shared__ unsigned long long s_kraft;
-  __shared__ int s_used, s_bad;
+  __shared__ uint16_t s_sorted[kNumSym], s_csym[kRankSyms];
+  __shared__ uint8_t s_clen[kRankSyms];
+  __shared__ uint32_t s_lut[1 << kLutBits], s_tmp[4];
+  __shared__ uint64_t s_kraft;
+  __shared__ uint32_t s_used;
+  __shared__ int s_bad;
   // a stream the host already rejected gets its status and no other work
   if (dp.init_status != RSZ_OK) {
     if (threadIdx.x == 0) *dp.status = dp.init_status;
     return;
   }
-  if (threadIdx.x == 0) {
-    s_kraft = 0;
-    s_used = 0;
+  const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const uint32_t l4 = *gm((const uint32_t *)(dp.in + dp.off_lens) + t);   // 4 lengths
+  bool bad = false;
+  const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
+  for (uint32_t k = t; k < dp.npeaks; k += 256)
+    bad |= pk[3 * k] >= dp.P || pk[3 * k + 1] >= dp.H || pk[3 * k + 2] >= dp.W;
+  const RSZ_G uint32_t *co = gm((const uint32_t *)(dp.in + dp.off_chunks));
+  for (uint32_t c = t; c < dp.nchunks; c += 256) {
+    const uint32_t o = co[c], before = co[max(c, 1u) - 1];
+    if (o > dp.T || (c == 0 && o != 0) || (c > 0 && o < before)) bad = true;
+    // the words that two chunks share, cleared for k_dec_runs
+    else if (dp.run_coding) *gm(dp.hbits + (o >> 5)) = 0u;
+  }
+  if (t == 0) {
+    if (dp.run_coding) *gm(dp.hbits + (dp.T >> 5)) = 0u;
     s_bad = 0;
     *dp.status = RSZ_OK;
   }
-  if (threadIdx.x <= kMaxLen) {
-    s_count[threadIdx.x] = 0;
-    s_fill[threadIdx.x] = 0;
+  if (t <= kMaxLen) {
+    s_count[t] = 0;
+    s_fill[t] = 0;
   }
-  for (int i = threadIdx.x; i < kNumSym; i += 256) s_sorted[i] = 0;
+  for (int i = t; i < kNumSym; i += 256) s_sorted[i] = 0;
+  ((uint32_t *)s_len)[t] = l4;
   __syncthreads();
-  for (int s = threadIdx.x; s < kNumSym; s += 256) {
-    const uint32_t L = dp.in[dp.off_lens + s];
-    s_len[s] = (uint8_t)L;
+  uint32_t used = 0;   // of this thread's symbols
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t L = (l4 >> (8 * e)) & 0xFFu;
     if (L > kMaxLen) {
-      s_bad = 1;
+      bad = true;
     } else if (L) {
-      atomicAdd(&s_kraft, 1ull << (kMaxLen - L));
-      atomicAdd(&s_used, 1);
       atomicAdd(&s_count[L], 1u);
+      ++used;
     }
   }
-  for (uint32_t k = threadIdx.x; k < dp.npeaks; k += 256) {
-    const uint16_t *pk = (const uint16_t *)(dp.in + dp.off_peaks) + 3 * k;
-    if (pk[0] >= dp.P || pk[1] >= dp.H || pk[2] >= dp.W) s_bad = 1;
-  }
-  const uint32_t *co = (const uint32_t *)(dp.in + dp.off_chunks);
-  for (uint32_t c = threadIdx.x; c < dp.nchunks; c += 256) {
-    const uint32_t o = co[c];
-    if (o > dp.T || (c == 0 && o != 0) || (c > 0 && o < co[c - 1])) s_bad = 1;
-    // the words that two chunks share, cleared for k_dec_runs
-    else if (dp.run_coding) dp.hbits[o >> 5] = 0u;
-  }
-  if (dp.run_coding && threadIdx.x == 0) dp.hbits[dp.T >> 5] = 0u;
+  if (bad) s_bad = 1;
+  const uint32_t incl = wave_inclusive_sum(used);
+  if (lane == 63) s_tmp[wv] = incl;
   __syncthreads();
+  if (t <= kMaxLen) {
+    // the codes and symbols of the shorter lengths; thread 0: of all
+    uint32_t code = 0, start = 0, n = 0;
+    uint64_t kraft = 0;
+#pragma unroll
+    for (uint32_t k = 1; k <= (uint32_t)kMaxLen; ++k) {
+      const uint32_t x = s_count[k];
+      kraft += (uint64_t)x << (kMaxLen - k);
+      n += x;
+      if (k < t) {
+        code += x << (t - k);
+        start += x;
+      }
+    }
+    s_first[t] = code;
+    s_offs[t] = start;
+    if (t == 0) {
+      s_kraft = kraft;
+      s_used = n;
+    }
+  }
+  uint32_t at = incl - used;   // this thread's first used symbol
+  for (uint32_t i = 0; i < wv; ++i) at += s_tmp[i];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t L = (l4 >> (8 * e)) & 0xFFu;
+    if (L && L <= kMaxLen) {
+      if (at < kRankSyms) {
+        s_csym[at] = (uint16_t)(4 * t + e);
+        s_clen[at] = (uint8_t)L;
+      }
+      ++at;
+    }
+  }
+  __syncthreads();
+  const uint32_t nused = s_used;
   const bool complete = s_kraft == (1ull << kMaxLen);
-  const bool single = s_used == 1 && s_kraft == (1ull << (kMaxLen - 1));
+  const bool single = nused == 1 && s_kraft == (1ull << (kMaxLen - 1));
   if (s_bad || !(complete || single)) {
-    if (threadIdx.x == 0) *dp.status = RSZ_ERR_CORRUPT;
+    if (t == 0) *dp.status = RSZ_ERR_CORRUPT;
     return;
   }
   uint32_t *tab = dp.tables;
-  if (threadIdx.x == 0) {
-    // canonical first code, symbol count and sorted offset per length
-    uint64_t code = 0;
-    uint32_t start = 0, prev = 0;
-    for (int L = 1; L <= kMaxLen; ++L) {
-      code = (code + prev) << 1;
-      s_first[L] = (uint32_t)code;
-      s_offs[L] = start;
-      start += s_count[L];
-      prev = s_count[L];
+  if (t <= kMaxLen && t > 0) {
+    *gm(tab + kTabFirst + t) = s_first[t];
+    *gm(tab + kTabCount + t) = s_count[t];
+    *gm(tab + kTabOffs + t) = s_offs[t];
+  }
+  // symbols in (length, symbol) order
+  if (nused <= kRankSyms) {
+    if (t < nused) {
+      const uint32_t L = s_clen[t];
+      uint32_t r = 0;
+#pragma unroll 8
+      for (uint32_t j = 0; j < nused; ++j) r += s_clen[j] == L && j < t;
+      s_sorted[s_offs[L] + r] = s_csym[t];
     }
-  }
-  __syncthreads();
-  if (threadIdx.x <= kMaxLen && threadIdx.x > 0) {
-    tab[kTabFirst + threadIdx.x] = s_first[threadIdx.x];
-    tab[kTabCount + threadIdx.x] = s_count[threadIdx.x];
-    tab[kTabOffs + threadIdx.x] = s_offs[threadIdx.x];
-  }
-  // symbols in (length, symbol) order: wave 0 walks the symbols 64 at a
-  // time; a symbol's rank among its length is the count of earlier ones
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
+  } else if (t < 64) {
+    // wave 0 walks the symbols 64 at a time; a symbol's rank among its
+    // length is the count of earlier ones
     for (int i = 0; i < kNumSym / 64; ++i) {
       const uint32_t sym = i * 64 + lane, L = s_len[sym];
       uint64_t pending = __builtin_amdgcn_uicmp(L, 0u, 33 /* ne */);
@@ -171,51 +217,67 @@ __global__ __launch_bounds__(256) void k_dec_tables(DecBatch db) {
         if ((same >> lane) & 1ull)
           s_sorted[s_offs[Lc] + s_fill[Lc] + __builtin_popcountll(same & ((1ull << lane) - 1))] =
               (uint16_t)sym;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane == leader) s_fill[Lc] += (uint32_t)__builtin_popcountll(same);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
+        if ((int)lane == leader) s_fill[Lc] += (uint32_t)__builtin_popcountll(same);
+        wave_sync();
         pending &= ~same;
       }
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kNumSym; i += 256) tab[kTabSorted + i] = s_sorted[i];
+  for (int i = t; i < kNumSym; i += 256) *gm(tab + kTabSorted + i) = s_sorted[i];
   // lookup entry of an 11-bit window: the codeword (at most 11 bits) that is
   // its prefix, if any (the code is prefix-free: at most one)
-  for (uint32_t x = threadIdx.x; x < (1u << kLutBits); x += 256) {
-    uint32_t e = 0;
-    for (uint32_t L = 1; L <= (uint32_t)kLutBits; ++L) {
-      const uint32_t n = s_count[L];
-      const uint32_t cd = x >> (kLutBits - L);
-      if (n && cd - s_first[L] < n) {
-        e = (uint32_t)s_sorted[s_offs[L] + cd - s_first[L]] | (L << 16);
-        break;
-      }
+  constexpr int kWin = (1 << kLutBits) / 256;   // windows a thread
+  uint32_t slot[kWin], len[kWin];
+#pragma unroll
+  for (int w = 0; w < kWin; ++w) slot[w] = len[w] = 0;
+#pragma unroll
+  for (uint32_t L = 1; L <= (uint32_t)kLutBits; ++L) {
+    const uint32_t n = __builtin_amdgcn_readfirstlane(s_count[L]);
+    const uint32_t f = __builtin_amdgcn_readfirstlane(s_first[L]);
+    const uint32_t o = __builtin_amdgcn_readfirstlane(s_offs[L]);
+#pragma unroll
+    for (int w = 0; w < kWin; ++w) {
+      const uint32_t cd = ((t + 256 * w) >> (kLutBits - L)) - f;
+      const bool hit = cd < n && len[w] == 0;
+      slot[w] = hit ? o + cd : slot[w];
+      len[w] = hit ? L : len[w];
     }
-    s_lut[x] = e;
   }
+#pragma unroll
+  for (int w = 0; w < kWin; ++w)
+    s_lut[t + 256 * w] = len[w] ? (uint32_t)s_sorted[slot[w]] | len[w] << 16 : 0u;
   __syncthreads();
   // multi-symbol entry: the whole codewords (at most 4) that the window
   // holds one after the other, while their residuals fit a byte
-  for (uint32_t x = threadIdx.x; x < (1u << kLutBits); x += 256) {
-    uint32_t bytes = 0, n = 0, pos = 0, starts = 0;
-    while (n < 4) {
-      const uint32_t e = s_lut[(x << pos) & ((1u << kLutBits) - 1)];
-      const uint32_t L = e >> 16;
-      const int32_t r = (int32_t)(e & 0x3FFu) - kRadius;
-      if (!e || pos + L > (uint32_t)kLutBits || r < -127 || r > 127) break;
-      bytes |= (uint32_t)(uint8_t)r << (8 * n);
-      starts |= 1u << pos;
-      pos += L;
-      ++n;
+  uint32_t bytes[kWin], n[kWin], pos[kWin], starts[kWin];
+#pragma unroll
+  for (int w = 0; w < kWin; ++w) bytes[w] = n[w] = pos[w] = starts[w] = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t e[kWin];
+#pragma unroll
+    for (int w = 0; w < kWin; ++w)
+      e[w] = s_lut[((t + 256 * w) << pos[w]) & ((1u << kLutBits) - 1)];
+#pragma unroll
+    for (int w = 0; w < kWin; ++w) {
+      const uint32_t L = e[w] >> 16;
+      const int32_t r = (int32_t)(e[w] & 0x3FFu) - kRadius;
+      const bool take = n[w] == (uint32_t)k && e[w] && pos[w] + L <= (uint32_t)kLutBits &&
+                        r >= -127 && r <= 127;
+      if (take) {
+        bytes[w] |= (uint32_t)(uint8_t)r << (8 * k);
+        starts[w] |= 1u << pos[w];
+        pos[w] += L;
+        ++n[w];
+      }
     }
-    tab[kTabMulti + 2 * x] = bytes;
-    tab[kTabMulti + 2 * x + 1] = starts | pos << 16 | n << 24;
   }
+#pragma unroll
+  for (int w = 0; w < kWin; ++w)
+    *(RSZ_G u32x2 *)gm(tab + kTabMulti + 2 * (t + 256 * w)) =
+        u32x2{bytes[w], starts[w] | pos[w] << 16 | n[w] << 24};
 }
 
 // Exclusive prefix sum of v over the lanes of a wave; total of all lanes.
