@@ -545,9 +545,10 @@ __device__ __forceinline__ Step code_step(const CodeTables &t, uint32_t v, uint3
 // The LDS lookups of a lane follow one another and bound it (the bits come
 // from LDS too, when the chunk has at most kChunkIn words of them), at 16
 // waves a CU: 8 share the tables' 18 KB (4 a workgroup 0.39 ms, 16 0.35, 8
-// 0.34 on 1000 CSPAD streams). With the bits by global loads, three whole
-// decodes a slice and byte stores straight to HBM it took 0.40 ms there and
-// 0.48 against 0.28 on 128 dense streams of 8x512x1024.
+// 0.34 on 1000 CSPAD streams), and the next chunk's words arrive while one is
+// decoded (0.32 ms; 0.25 on 128 dense streams of 8x512x1024, 0.28 without).
+// With the bits by global loads, three whole decodes a slice and byte stores
+// straight to HBM it took 0.40 and 0.48 ms.
 constexpr uint32_t kChunkIn = 640;
 constexpr uint32_t kChunkWaves = 8;
 __global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
@@ -581,17 +582,38 @@ __global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
   // residual 0 (symbol 512) coded as the single bit 0: the only length-1
   // code, canonical code 0
   const bool zrun = s_t.count[1] == 1 && s_t.first[1] == 0 && s_t.sorted[s_t.offs[1]] == kRadius;
-  for (uint32_t rep = 0; rep < db.chunk_reps; ++rep) {
-    const uint32_t c = (bid * db.chunk_reps + rep) * kChunkWaves + wv;
-    if (c >= nchunks) return;
-    const uint32_t S = co[c], E = max(S, c + 1 < nchunks ? co[c + 1] : T);
+  // the chunk's words and the two after them (a window reaches past its end),
+  // fetched while the chunk before is decoded
+  constexpr int kFetch = (int)((kChunkIn + 2 + 63) / 64);
+  uint32_t next[kFetch], S = 0, E = 0, nin = 0;
+  const uint32_t c0 = bid * db.chunk_reps * kChunkWaves + wv;
+  const uint32_t cend = min(c0 + db.chunk_reps * kChunkWaves, nchunks);
+  auto bounds = [&](uint32_t c, uint32_t &lo, uint32_t &hi) {
+    lo = co[c];
+    hi = max(lo, c + 1 < nchunks ? co[c + 1] : T);
+  };
+  auto fetch = [&](uint32_t lo, uint32_t hi) {
+    nin = (uint32_t)(((uint64_t)hi + 31) / 32) - (lo >> 5) + 2;
+#pragma unroll
+    for (int i = 0; i < kFetch; ++i) {
+      const uint32_t k = 64 * i + (uint32_t)lane, w = (lo >> 5) + k;
+      next[i] = nin <= kChunkIn + 2 && k < nin && w < src.n ? *gm(src.words + w) : 0u;
+    }
+  };
+  if (c0 < cend) {
+    bounds(c0, S, E);
+    fetch(S, E);
+  }
+  for (uint32_t c = c0; c < cend; c += kChunkWaves) {
     src.w0 = S >> 5;
-    // the chunk's words and the two after them (a window reaches past its end)
-    const uint32_t nin = (uint32_t)(((uint64_t)E + 31) / 32) - src.w0 + 2;
     src.staged = nin <= kChunkIn + 2;
-    if (src.staged)
-      for (uint32_t i = lane; i < nin; i += 64)
-        s_in[wv][i] = src.w0 + i < src.n ? *gm(src.words + src.w0 + i) : 0u;
+    if (src.staged) {
+#pragma unroll
+      for (int i = 0; i < kFetch; ++i)
+        if (64 * i + (uint32_t)lane < nin) s_in[wv][64 * i + lane] = next[i];
+    }
+    uint32_t nS = 0, nE = 0;
+    if (c + kChunkWaves < cend) bounds(c + kChunkWaves, nS, nE);
     for (uint32_t i = lane; i < kChunk / 16; i += 64)
       *(uint4 *)(s_out[wv] + 4 * i) = make_uint4(0u, 0u, 0u, 0u);
     wave_sync();
@@ -621,6 +643,7 @@ __global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
       }
       stop0 = inv ? kStuck : pos;
     }
+    if (c + kChunkWaves < cend) fetch(nS, nE);
     uint32_t start = s0, stop = stop0, m = m0;
     bool converged = false;
     for (int round = 0; round <= 64 && !converged; ++round) {
@@ -688,6 +711,8 @@ __global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
       *gm((u32x4 *)(rc + i)) = x ^ 0x80808080u;
     }
     wave_sync();
+    S = nS;
+    E = nE;
   }
 }
 
