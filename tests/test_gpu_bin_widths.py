@@ -44,3 +44,17 @@ def test_widths(b, dim):
             assert st == O.OK
             np.testing.assert_array_equal(B.stream(i).cpu().numpy(), ref,
                                           err_msg=f"b {b} {f.shape} mode {mode}")
+
+
+@pytest.mark.parametrize("panels", [1, 63, 65, 255, 257, 1025])
+def test_peak_bands(panels):
+    """Peaks sorted by (panel, segment) band: 256, 1024 and more bands, below and
+    above each."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a ROCm GPU")
+    f, pk = synth.tiny_case(1300 + panels, (panels, 17, 9), 300, "normal", scale=40.0)
+    st, ref, _ = O.compress(O.params(*f.shape, 3, 2, 1.0), f, pk)
+    assert st == O.OK
+    got = rsz.compress(torch.from_numpy(f).cuda(), torch.from_numpy(pk).cuda(), 3, 2, 1.0)
+    np.testing.assert_array_equal(got.cpu().numpy(), ref)
