@@ -378,7 +378,7 @@ def _counter_rows(root, counter):
 # Kernels whose counter records the roofline reads: (record name, the kernel
 # name in the counter output, the source file it is built from, and which of
 # its dispatches to take: the largest grid).
-TRAFFIC_KERNELS = [("k_bin", "k_bin_vec<2, 2>", "compress.hip"),
+TRAFFIC_KERNELS = [("k_bin", "k_bin_vec<2, 2, false>", "compress.hip"),
                    ("k_count", "k_count<true>", "compress.hip"),
                    ("k_encode", "k_encode", "compress.hip"),
                    ("k_lorenzo_dims", "k_lorenzo_dims", "compress.hip"),
