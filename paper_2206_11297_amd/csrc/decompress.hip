@@ -548,8 +548,10 @@ __device__ __forceinline__ Step code_step(const CodeTables &t, uint32_t v, uint3
 // 0.34 on 1000 CSPAD streams), and the next chunk's words arrive while one is
 // decoded (0.32 ms; 0.25 on 128 dense streams of 8x512x1024, 0.28 without).
 // With the bits by global loads, three whole decodes a slice and byte stores
-// straight to HBM it took 0.40 and 0.48 ms.
-constexpr uint32_t kChunkIn = 640;
+// straight to HBM it took 0.40 and 0.48 ms. kChunkIn is what two workgroups a
+// CU leave of the 160 KB: 7.25 bits a symbol (512 frames of 16x512x1024 at
+// eb 1, about 5.5 bits: 7.2 ms, with 640 words 8.3; at eb 10 1.8 with both).
+constexpr uint32_t kChunkIn = 928;
 constexpr uint32_t kChunkWaves = 8;
 __global__ __launch_bounds__(64 * kChunkWaves) void k_dec_chunks(DecBatch db) {
   RSZ_DEC_FRAME(2);
@@ -1662,9 +1664,11 @@ __device__ __forceinline__ bool roi_window(const DecodePlan &dp, uint32_t k, uin
 // With few windows (kRoiPairs) the wave of window k looks for the earlier
 // ones that meet it, 64 at a time, and compares the two payloads; more
 // windows are compared with the frame that all of them were written to, by
-// k_dec_roi_check (the search grows with the square of their number).  The
-// comparison by a pass over the frame took 70 us on 1000 CSPAD frames.
-constexpr uint32_t kRoiPairs = 4096;
+// k_dec_roi_check (the search grows with the square of their number).  At 60
+// windows a frame the search is nearly free and the pass over the frame takes
+// 70 us on 1000 frames; at 1500 a frame (512 frames) the search takes 1.0 ms
+// and the pass 0.5.
+constexpr uint32_t kRoiPairs = 512;
 __device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t lane) {
   const uint32_t w = dp.w, ww = w * w;
   const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));

@@ -71,6 +71,25 @@ def test_run_chunks_corrupt():
     _decode(host)
 
 
+@pytest.mark.parametrize("codes", [16, 24, 36, 42, 48, 64, 180])
+def test_dense_chunks(codes):
+    """Chunks of about 6 to 9 bits a symbol, below and above the 928 words of
+    them that a wave keeps in LDS, and a short last chunk; valid and corrupt."""
+    rng = np.random.default_rng(codes)
+    host = []
+    for p, h, w in ((1, 256, 80), (3, 97, 131)):
+        f = rng.integers(0, codes, (p, h, w)).astype(np.float32)
+        f[:, 1::2, 1::2] = f[:, :-1:2, :-1:2][:, :h // 2, :w // 2]
+        st, s, _ = O.compress(O.params(p, h, w, 3, 1, 0.5), f, np.zeros((0, 3), np.int32))
+        assert st == O.OK
+        host.append(s)
+        for _ in range(3):
+            c = s.copy()
+            c[int(rng.integers(80, c.size))] ^= np.uint8(1 << int(rng.integers(0, 8)))
+            host.append(c)
+    _decode(host)
+
+
 @pytest.mark.parametrize("w,n", [(1, 40), (17, 0), (17, 8), (17, 33), (25, 5), (31, 3), (33, 9),
                                  (48, 2), (49, 2), (70, 9)])
 def test_roi_windows(w, n):
@@ -86,11 +105,11 @@ def test_roi_windows(w, n):
     _decode(host)
 
 
-@pytest.mark.parametrize("n,w", [(20, 5), (65, 9), (4096, 3), (4097, 3)])
+@pytest.mark.parametrize("n,w", [(20, 5), (65, 9), (512, 5), (513, 5), (4096, 3), (4097, 3)])
 def test_windows_must_agree_on_shared_pixels(n, w):
     """One payload word changed at a time (in a shared pixel, in a pixel of one
     window alone, in one outside the frame): the oracle's status, and its frame
-    where the stream is still valid.  4096 windows is the most that are
+    where the stream is still valid.  512 windows is the most that are
     compared with each other instead of with the frame."""
     f, _ = synth.tiny_case(990 + w, (2, 60, 70), 0, "normal", scale=50.0)
     rng = np.random.default_rng(n)
