@@ -29,7 +29,8 @@
 //                   windows larger than LDS holds).
 //   k_dec_roi       ROI windows restored from the payload bits, one wave
 //                   per window; overlapping windows must agree on their
-//                   shared pixels (with many windows: k_dec_roi_check).
+//                   shared pixels (with many or large windows:
+//                   k_dec_roi_check).
 // The inverse Lorenzo step is the prefix sum of the residuals along each
 // axis the predictor spans.
 #include <algorithm>
@@ -1661,37 +1662,78 @@ __device__ __forceinline__ bool roi_window(const DecodePlan &dp, uint32_t k, uin
 }
 
 // Windows that overlap must carry the same bits for the pixels they share.
-// With few windows (kRoiPairs) the wave of window k looks for the earlier
-// ones that meet it, 64 at a time, and compares the two payloads; more
-// windows are compared with the frame that all of them were written to, by
-// k_dec_roi_check (the search grows with the square of their number).  At 60
-// windows a frame the search is nearly free and the pass over the frame takes
-// 70 us on 1000 frames; at 1500 a frame (512 frames) the search takes 1.0 ms
-// and the pass 0.5.
-constexpr uint32_t kRoiPairs = 512;
-__device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t lane) {
+// With few windows (roi_pairs) the wave of window k lists the earlier windows
+// that meet it, 64 a step, and compares each of its pixels with one of them
+// that covers it: the nearest in the list.  By induction along the windows
+// over a pixel all of them then agree, so a pixel is compared once however
+// many windows lie over it.  More windows are compared with the frame that
+// all of them were written to, by k_dec_roi_check: the listing grows with the
+// square of their number, and a wave steps through its list for every 64
+// pixels.  So the line lies at kRoiListed windows and kRoiSteps such steps of
+// the last wave (256 windows of 17, 128 of 25, 60 of 36), both known from the
+// header.  60 windows of 17 a frame, k_dec_roi (and k_dec_roi_check) in us on
+// 1 and on 50 frames: spread out 9 and 11 (the pass: 13 and 21), on one spot
+// 10 and 14, crowded in 51 x 51 pixels 18 and 24; 256 on one spot 11 and 29
+// (12 and 24).  Every element against every window met, with the line at 512
+// windows of any size: 60 on one spot 103 and 116, 256 427 and 1311, 512
+// windows of 101 there 35 and 112 ms against 0.10 and 0.45 of the pass.
+constexpr uint32_t kRoiListed = 512, kRoiSteps = 1280;
+__host__ __device__ inline bool roi_pairs(const DecodePlan &dp) {
+  return dp.npeaks <= kRoiListed && dp.npeaks * ((dp.w * dp.w + 63) / 64) <= kRoiSteps;
+}
+// list: this wave's kRoiListed words.
+__device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t *list,
+                                             uint32_t lane) {
   const uint32_t w = dp.w, ww = w * w;
   const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
-  const RSZ_G uint32_t *pay =
-      gm(dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi));
   const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W, iw = (int32_t)w;
   const int32_t pa = pk[3 * k], r = pk[3 * k + 1], c = pk[3 * k + 2];
-  bool bad = false;
+  // the earlier windows that meet this one: number (9 bits), and where their
+  // corner lies from this one's, row and column + 1023 (11 bits each)
+  uint32_t n = 0;
   for (uint32_t b = 0; b < k; b += 64) {
     const uint32_t o = min(b + lane, k - 1);
     const int32_t opa = pk[3 * o], dr = (int32_t)pk[3 * o + 1] - r, dc = (int32_t)pk[3 * o + 2] - c;
     const bool meet = b + lane < k && opa == pa && dr > -iw && dr < iw && dc > -iw && dc < iw;
-    for (uint64_t m = __ballot(meet); m; m &= m - 1) {
-      const int l = __builtin_ctzll(m);
-      const int32_t er = __builtin_amdgcn_readlane(dr, l), ec = __builtin_amdgcn_readlane(dc, l);
-      const RSZ_G uint32_t *mine = pay + (size_t)k * ww, *other = pay + (size_t)(b + l) * ww;
-      for (uint32_t e = lane; e < ww; e += 64) {   // element (u, v) of window k
-        const int32_t u = (int32_t)(e / w), v = (int32_t)(e - (uint32_t)u * w);
-        const int32_t ou = u - er, ov = v - ec;    // and of the other
-        const int32_t i = r - h + u, j = c - h + v;
-        if (ou >= 0 && ou < iw && ov >= 0 && ov < iw && i >= 0 && i < H && j >= 0 && j < W)
-          bad |= mine[e] != other[(uint32_t)ou * w + (uint32_t)ov];
+    const uint64_t m = __ballot(meet);
+    if (meet)
+      list[n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
+          o << 22 | (uint32_t)(dr + 1023) << 11 | (uint32_t)(dc + 1023);
+    n += (uint32_t)__builtin_popcountll(m);
+  }
+  if (n == 0) return false;
+  wave_sync();
+  const RSZ_G uint32_t *pay =
+      gm(dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi));
+  const RSZ_G uint32_t *mine = pay + (size_t)k * ww;
+  const int32_t du = (int32_t)(64 / w), dv = (int32_t)(64 % w);
+  int32_t u = (int32_t)(lane / w), v = (int32_t)lane - u * iw;   // element e of window k
+  bool bad = false;
+  for (uint32_t e0 = 0; e0 < ww; e0 += 64) {
+    const int32_t i = r - h + u, j = c - h + v;
+    bool open = u < iw && i >= 0 && i < H && j >= 0 && j < W;   // in the frame, not yet compared
+    uint32_t at = 0;
+    bool found = false;
+    for (uint32_t t = n; t > 0 && __ballot(open) != 0;) {
+      // the next up to 64 of the list, a lane each
+      const uint32_t t0 = (t - 1) & ~63u, x64 = list[min(t0 + lane, n - 1)];
+      for (; t > t0 && __ballot(open) != 0; --t) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)((t - 1) & 63));
+        const int32_t ou = u - ((int32_t)((x >> 11) & 2047u) - 1023);
+        const int32_t ov = v - ((int32_t)(x & 2047u) - 1023);
+        if (open && (uint32_t)ou < w && (uint32_t)ov < w) {
+          at = (x >> 22) * ww + (uint32_t)ou * w + (uint32_t)ov;
+          found = true;
+          open = false;
+        }
       }
+    }
+    if (found) bad |= mine[e0 + lane] != pay[at];
+    u += du;
+    v += dv;
+    if (v >= iw) {
+      v -= iw;
+      ++u;
     }
   }
   return bad;
@@ -1699,10 +1741,11 @@ __device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, u
 
 __global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
   RSZ_DEC_FRAME(12);
-  const uint32_t k = bid * 4 + (threadIdx.x >> 6);
+  __shared__ uint32_t s_list[4][kRoiListed];
+  const uint32_t wv = threadIdx.x >> 6, k = bid * 4 + wv;
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
   roi_window<false>(dp, k, threadIdx.x & 63);
-  if (dp.npeaks <= kRoiPairs && roi_overlaps(dp, k, threadIdx.x & 63)) corrupt(dp.status);
+  if (roi_pairs(dp) && roi_overlaps(dp, k, s_list[wv], threadIdx.x & 63)) corrupt(dp.status);
 }
 __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   RSZ_DEC_FRAME(13);
@@ -1737,7 +1780,7 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
     if (!roi_in_lds(dp.w)) nb[11] = (dp.npeaks + 3) / 4;
   }
   nb[12] = (dp.npeaks + 3) / 4;   // a wave per window
-  if (dp.npeaks > kRoiPairs) nb[13] = nb[12];
+  if (!roi_pairs(dp)) nb[13] = nb[12];
 }
 
 #define RSZ_DLAUNCH_S(k, name, kern, block, lds)                       \
