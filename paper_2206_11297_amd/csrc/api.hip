@@ -764,12 +764,16 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
   memcpy(host.data(), dps.data(), sizeof(DecodePlan) * n);
   uint32_t *pre = (uint32_t *)(host.data() + align_up((uint64_t)sizeof(DecodePlan) * n, 256));
   uint32_t total_blocks[kDecKernels] = {0};
-  uint64_t all_chunks = 0;
-  for (uint32_t f = 0; f < n; ++f) all_chunks += dps[f].nchunks;
+  uint64_t all_chunks = 0, all_bands = 0;
+  for (uint32_t f = 0; f < n; ++f) {
+    all_chunks += dps[f].nchunks;
+    all_bands += (uint64_t)dps[f].P * dps[f].nbands;
+  }
   const uint32_t reps = decode_chunk_reps(all_chunks);
+  const BandSplit split = decode_split(all_bands);
   for (uint32_t f = 0; f < n; ++f) {
     uint32_t nb[kDecKernels];
-    decode_blocks(dps[f], reps, nb);
+    decode_blocks(dps[f], reps, split, nb);
     for (int k = 0; k < kDecKernels; ++k) {
       pre[(size_t)k * (n + 1) + f] = total_blocks[k];
       if ((uint64_t)total_blocks[k] + nb[k] > 0x7FFFFFFFull) return RSZ_ERR_ARG;
@@ -781,6 +785,8 @@ static int decode_streams(uint32_t n, const DecodeItem *it, uint8_t *ws, uint64_
   if (st) return st;
   DecBatch db = {};
   db.chunk_reps = reps;
+  db.row_split = split.rows;
+  db.col_split = split.cols;
   for (uint32_t f = 0; f < n; ++f) decode_panel_shape(db, dps[f]);
   db.n = n;
   db.plans = (const DecodePlan *)ws;
@@ -1239,9 +1245,13 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   uint32_t *vpre = (uint32_t *)(host.data() + h_dp + h_pre + h_vf);
   uint64_t off = head;
   uint32_t dec_total[kDecKernels] = {0};
-  uint64_t all_chunks = 0;
-  for (uint32_t f = 0; f < n; ++f) all_chunks += dps[f].nchunks;
+  uint64_t all_chunks = 0, all_bands = 0;
+  for (uint32_t f = 0; f < n; ++f) {
+    all_chunks += dps[f].nchunks;
+    all_bands += (uint64_t)dps[f].P * dps[f].nbands;
+  }
   const uint32_t reps = decode_chunk_reps(all_chunks);
+  const BandSplit split = decode_split(all_bands);
   uint64_t wgs = 0;
   uint32_t mask_words = 0;
   for (uint32_t f = 0; f < n; ++f) {
@@ -1260,7 +1270,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     vf.dplan = (DecodePlan *)ws + f;
     vf.bad = d_bad + f;
     uint32_t nb[kDecKernels];
-    decode_blocks(dp, reps, nb);
+    decode_blocks(dp, reps, split, nb);
     // the outliers: a fixed number of workgroups (their count is known only
     // on the device), each striding over them
     if (vf.valid) nb[kDecOutliers] = std::min<uint32_t>(kVerifyOutlierBlocks, (dp.nbins + 255) / 256);
@@ -1289,6 +1299,8 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   vr->vb.total_wgs = (uint32_t)wgs;
   vr->vb.mask_words = mask_words;
   vr->db.chunk_reps = reps;
+  vr->db.row_split = split.rows;
+  vr->db.col_split = split.cols;
   for (uint32_t f = 0; f < n; ++f) decode_panel_shape(vr->db, dps[f]);
   vr->db.n = n;
   vr->db.plans = (const DecodePlan *)ws;

@@ -769,6 +769,7 @@ __device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {
 // Words at any address (global accesses take any alignment).
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 __device__ __forceinline__ uint32_t ld_any32(const uint8_t *p) {
   return *(const RSZ_G u32_any *)p;
 }
@@ -1050,6 +1051,7 @@ struct EmitPlan {
   const int32_t *res;
   float *out;           // and its first pixel
   uint32_t I0, nr;
+  uint32_t lo, hi;      // SPLIT: the band's rows that this wave emits
 };
 
 // One row's q of the band's strips: r the residuals, acc the column sums
@@ -1119,7 +1121,8 @@ __device__ __forceinline__ void row_pixels(const EmitPlan &ep, uint32_t I, float
 // i's.  The loop loads nothing: loads and stores share one wait counter, so
 // a load's wait would wait for every store before it too, and the pixels of
 // a row would leave only when the row before had reached memory.
-template <int B, int NS, bool D1>
+// SPLIT: rows [lo, hi) alone, the others being other waves'.
+template <int B, int NS, bool D1, bool SPLIT>
 __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd, uint32_t j0,
                                           int ns, int lane,
                                           uint32_t (&acc)[Band<B>::S][Band<B>::V],
@@ -1127,9 +1130,19 @@ __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd,
   using D = Band<B>;
   constexpr int N = NS ? NS : D::S;
   const uint32_t b = B ? (uint32_t)B : ep.b;
+  if (SPLIT && !D1 && ep.lo) {   // the columns' sums over the rows above
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+#pragma unroll
+      for (int i = 0; i < D::R; ++i)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          acc[s][v] += (uint32_t)i < ep.lo ? (uint32_t)bd.residual(s, i, v) : 0u;
+  }
 #pragma unroll
   for (int i = 0; i < D::R; ++i) {
-    if ((uint32_t)i >= ep.nr) continue;
+    if (SPLIT && !D1 ? (uint32_t)i < ep.lo || (uint32_t)i >= ep.hi : (uint32_t)i >= ep.nr)
+      continue;
     int32_t r[N][D::V];
     float q[N][D::V];
 #pragma unroll
@@ -1146,7 +1159,7 @@ __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd,
 // The same for a band with escapes (rare): row by row, the bytes read again
 // (one row ahead) and the residuals of the bytes 0 from res.  Returns
 // whether an outlier's mark is left.
-template <int B, bool D1>
+template <int B, bool D1, bool SPLIT>
 __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, int ns, int lane,
                                               uint32_t (&acc)[Band<B>::S][Band<B>::V],
                                               uint32_t &carry) {
@@ -1165,9 +1178,10 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
       }
   };
   bool bad = false;
+  const uint32_t i1 = SPLIT ? ep.hi : ep.nr;
   load(0);
 #pragma unroll 1
-  for (uint32_t i = 0; i < ep.nr; ++i) {
+  for (uint32_t i = 0; i < i1; ++i) {
     int32_t r[D::S][D::V];
     float q[D::S][D::V];
 #pragma unroll
@@ -1185,6 +1199,14 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
       if (s < ns)
 #pragma unroll
         for (int v = 0; v < D::V; ++v) bad |= r[s][v] == kMark;
+    if (SPLIT && !D1 && i < ep.lo) {   // a row above
+#pragma unroll
+      for (int s = 0; s < D::S; ++s)
+        if (s < ns)
+#pragma unroll
+          for (int v = 0; v < D::V; ++v) acc[s][v] += (uint32_t)r[s][v];
+      continue;
+    }
     uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)carry, (int)i);
     row_q<B, 0, D1>(ep.step, ns, r, acc, c, q);
     carry = (uint32_t)lane == i ? c : carry;
@@ -1193,9 +1215,12 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
   return bad;
 }
 
+// part: which of the `split` waves that share the band's rows.
 __device__ __forceinline__ EmitPlan emit_plan(const DecodePlan &dp, uint32_t p, uint32_t I0,
-                                              uint32_t nr) {
+                                              uint32_t nr, uint32_t part, uint32_t split) {
   EmitPlan ep;
+  ep.lo = part * (kDecTH / split);
+  ep.hi = min(ep.lo + kDecTH / split, nr);
   ep.b = dp.b;
   ep.Wb = dp.Wb;
   ep.H = dp.H;
@@ -1209,16 +1234,54 @@ __device__ __forceinline__ EmitPlan emit_plan(const DecodePlan &dp, uint32_t p, 
   return ep;
 }
 
+// One of the waves that share a row's groups of strips.
+struct ColPart {
+  uint32_t part, split;
+};
+
+// A lane's part of the sum of n rows of residuals over their first cols
+// columns (a multiple of 256): 16 columns of 8 rows at a time.
+__device__ __forceinline__ uint32_t left_sum(const uint8_t *src, const int32_t *res, uint32_t Wb,
+                                             uint32_t n, uint32_t cols, int lane) {
+  constexpr uint32_t R = 8;
+  uint32_t sum = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += R)
+    for (uint32_t j = 16 * (uint32_t)lane; j < cols; j += 1024) {
+      u32x4 w[R];
+#pragma unroll
+      for (uint32_t i = 0; i < R; ++i)
+        w[i] = *(const RSZ_G u32x4_any *)(src + (size_t)min(i0 + i, n - 1) * Wb + j);
+#pragma unroll
+      for (uint32_t i = 0; i < R; ++i) {
+        if (i0 + i >= n) continue;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+          sum = __builtin_amdgcn_sad_u8(w[i][k], 0u, sum) - 128u * 4u;
+          for (uint32_t z = zero_bytes(w[i][k]); z; z &= z - 1)   // escapes
+            sum += 128u + (uint32_t)*gm(res + (size_t)(i0 + i) * Wb + j + 4 * k +
+                                        ((uint32_t)__builtin_ctz(z) >> 3));
+        }
+      }
+    }
+  return sum;
+}
+
 // One wave's band of a panel of any size: strips group by group from left to
 // right, the column sums above from k_dec_cols.  D1: Lorenzo dimension 1
 // (each row continues the one before: only row sums, from the row's carry).
-template <int B, bool D1>
+template <int B, bool D1, bool SPLIT>
 __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint32_t band,
-                                         int lane) {
+                                         uint32_t part, uint32_t split, ColPart cols, int lane) {
   using D = Band<B>;
   const uint32_t Hb = dp.Hb, Wb = dp.Wb;
-  const uint32_t I0 = band * kDecTH, nr = min(kDecTH, Hb - I0);
-  const EmitPlan ep = emit_plan(dp, p, I0, nr);
+  // (dimension 1 needs nothing of the rows above: its part is a band of its own)
+  const uint32_t rows = SPLIT && D1 ? kDecTH / split : kDecTH;
+  const uint32_t I0 = band * kDecTH + (SPLIT && D1 ? part * rows : 0u);
+  if (SPLIT && D1 && I0 >= Hb) return;
+  const uint32_t nr = min(rows, Hb - I0);
+  const EmitPlan ep = SPLIT && D1 ? emit_plan(dp, p, I0, nr, 0, 1)
+                                  : emit_plan(dp, p, I0, nr, part, split);
+  if (SPLIT && ep.lo >= ep.hi) return;   // (a last band of few rows)
   const uint32_t seg = band / dp.seg_bands, nsegs = dp.nsegs;
   const uint32_t *cb = D1 || band == seg * dp.seg_bands
                            ? nullptr : dp.colbase + ((size_t)p * dp.nbands + band) * Wb;
@@ -1227,10 +1290,29 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
   int32_t *status = dp.status;
   uint32_t carry = D1 ? *gm(dp.carry + (size_t)p * Hb + I0 + min((uint32_t)lane, nr - 1)) : 0u;
   bool bad = false;
-  for (uint32_t j0 = 0; j0 < Wb; j0 += D::kCols) {
+  uint32_t ja = 0, jb = Wb;   // the columns of its group of strips
+  if (SPLIT && cols.split > 1) {
+    const uint32_t groups = (Wb + D::kCols - 1) / D::kCols;
+    ja = D::kCols * (groups * cols.part / cols.split);
+    jb = min(Wb, D::kCols * (groups * (cols.part + 1) / cols.split));
+    if (ja >= jb) return;
+    // and its one row's q left of them
+    uint32_t left = left_sum(ep.src, ep.res, Wb, D1 ? 1u : ep.lo + 1, ja, lane);
+    auto add = [&](const uint32_t *sums) {
+      for (uint32_t j = 4 * (uint32_t)lane; j < ja; j += 256) {
+        const u32x4 x = *(const RSZ_G u32x4a *)(sums + j);
+        left += x[0] + x[1] + x[2] + x[3];
+      }
+    };
+    if (!D1)
+      for (uint32_t g = 0; g < seg; ++g) add(st + (size_t)g * Wb);
+    if (!D1 && cb) add(cb);
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(left), 63);
+  }
+  for (uint32_t j0 = ja; j0 < jb; j0 += D::kCols) {
     const int ns = (int)min((uint32_t)D::S, (Wb - j0 + 64 * D::V - 1) / (64 * D::V));
     D bd;
-    bd.template load<0>(ep.src, Wb, j0, ns, nr, lane);
+    bd.template load<0>(ep.src, Wb, j0, ns, SPLIT ? ep.hi : nr, lane);
     uint32_t acc[D::S][D::V];
 #pragma unroll
     for (int s = 0; s < D::S; ++s) {
@@ -1248,34 +1330,44 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
           if (J + v < Wb) acc[s][v] += *gm(cb + J + v);
       }
     }
-    if (bd.esc) bad |= band_emit_esc<B, D1>(ep, j0, ns, lane, acc, carry);
-    else if (!D1 && ns == D::S) band_emit<B, D::S, D1>(ep, bd, j0, ns, lane, acc, carry);
-    else band_emit<B, 0, D1>(ep, bd, j0, ns, lane, acc, carry);
+    if (bd.esc) bad |= band_emit_esc<B, D1, SPLIT>(ep, j0, ns, lane, acc, carry);
+    else if (!D1 && ns == D::S) band_emit<B, D::S, D1, SPLIT>(ep, bd, j0, ns, lane, acc, carry);
+    else band_emit<B, 0, D1, SPLIT>(ep, bd, j0, ns, lane, acc, carry);
   }
   if (bad && marks) corrupt(status);
 }
 
+// SPLIT: db.row_split waves share a band's rows and db.col_split a row's
+// columns.  Each reads the bytes of the band's rows up to its own (1 byte a
+// bin, from the L2, against the 4 b^2 its pixels take) and those left of its
+// columns.  A kernel of its own: the bounds on every row cost the other a
+// third of its occupancy.
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void k_dec_pixels(DecBatch db) {
   RSZ_DEC_FRAME_AT(8, xcd_run());
   const uint32_t it = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (it >= dp.P * dp.nbands || !dec_ok(dp.status)) return;
+  const uint32_t split = SPLIT ? db.row_split : 1u;
+  ColPart cols = {0u, SPLIT ? db.col_split : 1u};
+  const uint32_t row = it / cols.split, pb = row / split, part = row - pb * split;
+  cols.part = it - row * cols.split;
+  if (pb >= dp.P * dp.nbands || !dec_ok(dp.status)) return;
   const int lane = threadIdx.x & 63;
-  const uint32_t p = it / dp.nbands, band = it - p * dp.nbands;
+  const uint32_t p = pb / dp.nbands, band = pb - p * dp.nbands;
   if (dp.dim == 1) {
     switch (dp.b) {
-      case 1: dec_band<1, true>(dp, p, band, lane); break;
-      case 2: dec_band<2, true>(dp, p, band, lane); break;
-      case 3: dec_band<3, true>(dp, p, band, lane); break;
-      case 4: dec_band<4, true>(dp, p, band, lane); break;
-      default: dec_band<0, true>(dp, p, band, lane); break;
+      case 1: dec_band<1, true, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 2: dec_band<2, true, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 3: dec_band<3, true, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 4: dec_band<4, true, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      default: dec_band<0, true, SPLIT>(dp, p, band, part, split, cols, lane); break;
     }
   } else {
     switch (dp.b) {
-      case 1: dec_band<1, false>(dp, p, band, lane); break;
-      case 2: dec_band<2, false>(dp, p, band, lane); break;
-      case 3: dec_band<3, false>(dp, p, band, lane); break;
-      case 4: dec_band<4, false>(dp, p, band, lane); break;
-      default: dec_band<0, false>(dp, p, band, lane); break;
+      case 1: dec_band<1, false, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 2: dec_band<2, false, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 3: dec_band<3, false, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      case 4: dec_band<4, false, SPLIT>(dp, p, band, part, split, cols, lane); break;
+      default: dec_band<0, false, SPLIT>(dp, p, band, part, split, cols, lane); break;
     }
   }
 }
@@ -1292,7 +1384,7 @@ __host__ __device__ inline bool panel_fits(const DecodePlan &dp) {
 // Wave wv's band of panel p; every wave of the workgroup calls it (mine: the
 // panel has the band).  Returns whether the band holds escapes, its pixels
 // then left to the caller (acc: the column sums above).
-template <int B, int NS>
+template <int B, int NS, bool SPLIT>
 __device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint32_t wv,
                                              uint32_t *s_col, int lane,
                                              uint32_t (&acc)[Band<B>::S][Band<B>::V]) {
@@ -1330,35 +1422,38 @@ __device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint
       if ((uint32_t)((64 * s + lane) * D::V + v) >= Wb) acc[s][v] = 0;
   if (bd.esc) return true;
   uint32_t carry = 0;
-  band_emit<B, NS, false>(ep, bd, 0, NS, lane, acc, carry);
+  band_emit<B, NS, false, SPLIT>(ep, bd, 0, NS, lane, acc, carry);
   return false;
 }
 
-template <int B>
-__device__ __forceinline__ void dec_panel(const DecodePlan &dp, uint32_t p, uint32_t wv,
-                                          uint32_t *s_col, int lane) {
+template <int B, bool SPLIT>
+__device__ __forceinline__ void dec_panel(const DecodePlan &dp, uint32_t p, uint32_t part,
+                                          uint32_t split, uint32_t wv, uint32_t *s_col,
+                                          int lane) {
   using D = Band<B>;
   const bool mine = wv < dp.nbands;
   const uint32_t I0 = mine ? wv * kDecTH : 0u;
-  const EmitPlan ep = emit_plan(dp, p, I0, min(kDecTH, dp.Hb - I0));
+  const EmitPlan ep = emit_plan(dp, p, I0, min(kDecTH, dp.Hb - I0), part, split);
   const bool marks = dp.dim != 3;   // (dimension 3: k_dec_panels looked)
   int32_t *status = dp.status;
   const int ns = (int)((ep.Wb + 64 * D::V - 1) / (64 * D::V));
   uint32_t acc[D::S][D::V];
   bool esc = false;
   switch (ns) {
-    case 1: esc = dec_panel_ns<B, 1>(ep, mine, wv, s_col, lane, acc); break;
-    case 2: esc = dec_panel_ns<B, 2>(ep, mine, wv, s_col, lane, acc); break;
-    case 3: if constexpr (D::S >= 3) esc = dec_panel_ns<B, 3>(ep, mine, wv, s_col, lane, acc); break;
-    default: if constexpr (D::S >= 4) esc = dec_panel_ns<B, 4>(ep, mine, wv, s_col, lane, acc); break;
+    case 1: esc = dec_panel_ns<B, 1, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
+    case 2: esc = dec_panel_ns<B, 2, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
+    case 3: if constexpr (D::S >= 3) esc = dec_panel_ns<B, 3, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
+    default: if constexpr (D::S >= 4) esc = dec_panel_ns<B, 4, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
   }
   if (esc) {
     uint32_t carry = 0;
-    if (band_emit_esc<B, false>(ep, 0, ns, lane, acc, carry) && marks) corrupt(status);
+    if (band_emit_esc<B, false, SPLIT>(ep, 0, ns, lane, acc, carry) && marks) corrupt(status);
   }
 }
 
-// LDS: the bands' column sums.
+// LDS: the bands' column sums.  SPLIT: as many workgroups a panel, each with
+// all the column sums and a part of every band's rows.
+template <bool SPLIT>
 __global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
   RSZ_DEC_FRAME_AT(9, xcd_run());
   extern __shared__ __align__(16) uint32_t s_col[];
@@ -1370,12 +1465,13 @@ __global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
   if (!s_ok) return;
   const int lane = threadIdx.x & 63;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t split = SPLIT ? db.row_split : 1u, p = bid / split, part = bid - p * split;
   switch (dp.b) {
-    case 1: dec_panel<1>(dp, bid, wv, s_col, lane); break;
-    case 2: dec_panel<2>(dp, bid, wv, s_col, lane); break;
-    case 3: dec_panel<3>(dp, bid, wv, s_col, lane); break;
-    case 4: dec_panel<4>(dp, bid, wv, s_col, lane); break;
-    default: dec_panel<0>(dp, bid, wv, s_col, lane); break;
+    case 1: dec_panel<1, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
+    case 2: dec_panel<2, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
+    case 3: dec_panel<3, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
+    case 4: dec_panel<4, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
+    default: dec_panel<0, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
   }
 }
 
@@ -1754,7 +1850,7 @@ __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   if (roi_window<true>(dp, k, threadIdx.x & 63)) corrupt(dp.status);
 }
 
-void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
+void decode_blocks(const DecodePlan &dp, uint32_t reps, BandSplit split, uint32_t *nb) {
   for (int k = 0; k < kDecKernels; ++k) nb[k] = 0;
   nb[0] = 1;   // k_dec_tables writes every frame's status
   if (dp.init_status != RSZ_OK) return;
@@ -1764,7 +1860,7 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
   // inverse Lorenzo: prefix sums along each axis the predictor spans
   if (dp.dim == 3) nb[4] = (dp.Hb * dp.Wb + 1023) / 1024;
   if (panel_fits(dp)) {
-    nb[9] = dp.P;
+    nb[9] = dp.P * split.rows;
   } else {
     if (dp.dim == 1) {
       nb[5] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
@@ -1772,7 +1868,7 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb) {
     } else if (dp.nbands > 1) {
       nb[7] = (uint32_t)(((uint64_t)dp.P * dp.nsegs * ((dp.Wb + 3) / 4) + 255) / 256);
     }
-    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nbands + 3) / 4);
+    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nbands * split.rows * split.cols + 3) / 4);
   }
   if (dp.roi_coding) {
     const uint32_t wins = 4 * roi_wins(dp.w);
@@ -1804,8 +1900,13 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
   RSZ_DLAUNCH(5, "k_dec_rowsum", k_dec_rowsum, 256);
   RSZ_DLAUNCH(6, "k_dec_carry", k_dec_carry, 256);
   RSZ_DLAUNCH(7, "k_dec_cols", k_dec_cols, 256);
-  RSZ_DLAUNCH(8, "k_dec_pixels", k_dec_pixels, 256);
-  RSZ_DLAUNCH_S(9, "k_dec_panel", k_dec_panel, 64 * db.panel_waves, 4 * db.panel_lds);
+  if (db.row_split > 1) {
+    RSZ_DLAUNCH(8, "k_dec_pixels", k_dec_pixels<true>, 256);
+    RSZ_DLAUNCH_S(9, "k_dec_panel", k_dec_panel<true>, 64 * db.panel_waves, 4 * db.panel_lds);
+  } else {
+    RSZ_DLAUNCH(8, "k_dec_pixels", k_dec_pixels<false>, 256);
+    RSZ_DLAUNCH_S(9, "k_dec_panel", k_dec_panel<false>, 64 * db.panel_waves, 4 * db.panel_lds);
+  }
   RSZ_DLAUNCH(10, "k_dec_roi_decode", k_dec_roi_decode, 256);
   RSZ_DLAUNCH(11, "k_dec_roi_unpred", k_dec_roi_unpred, 256);
   RSZ_DLAUNCH(12, "k_dec_roi", k_dec_roi, 256);
@@ -1828,6 +1929,22 @@ void decode_geometry(DecodePlan &dp) {
 // every chunk on a wave of its own.
 uint32_t decode_chunk_reps(uint64_t all_chunks) {
   return (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, all_chunks / (kChunkWaves * 1024)));
+}
+
+// How many waves share a band: with one wave each, a batch of few bands leaves
+// the GPU idle while its waves walk their rows, so the bands are split, by
+// rows down to one and then by columns, until there are kDecWaves (with two
+// and four times as many, waves read the bytes above them too often: 8 frames
+// of 32x185x388 at b = 2 take 18 us, 27 and 38).  The pixel kernel on one
+// frame of 1x2048x2048 at b = 5 79 -> 19 us, at b = 2 49 -> 34, of 32x185x388
+// 15 -> 10, of 1x40x30000 at b = 5 390 -> 25.
+constexpr uint64_t kDecWaves = 1024;
+BandSplit decode_split(uint64_t all_bands) {
+  BandSplit split = {1, 1};
+  while (split.rows < kDecTH && all_bands * split.rows < kDecWaves) split.rows *= 2;
+  if (split.rows == kDecTH)
+    while (split.cols < 16 && all_bands * kDecTH * split.cols < kDecWaves) split.cols *= 2;
+  return split;
 }
 
 // k_dec_panel's waves and LDS words: the most that a panel of the batch takes.

@@ -292,15 +292,21 @@ struct DecBatch {
   uint32_t panel_waves, panel_cols, panel_lds;   // k_dec_panel's workgroups: waves, bin
                                                  // columns, LDS words
   uint32_t chunk_reps;   // chunks a wave of k_dec_chunks takes
+  uint32_t row_split, col_split;   // waves that share a band's rows (k_dec_pixels,
+                                   // k_dec_panel) and a row's columns (k_dec_pixels)
+};
+struct BandSplit {
+  uint32_t rows, cols;
 };
 void decode_panel_shape(DecBatch &db, const DecodePlan &dp);
 uint32_t decode_chunk_reps(uint64_t all_chunks);
+BandSplit decode_split(uint64_t all_bands);
 // Bands and segments of a plan whose bin geometry is set; its workspace region.
 void decode_geometry(DecodePlan &dp);
 uint8_t *decode_region(DecodePlan &dp, uint8_t *w);
 // Workgroups of each decoder kernel for one frame (0: not launched for it).
-// reps: the batch's chunk_reps.
-void decode_blocks(const DecodePlan &dp, uint32_t reps, uint32_t *nb);
+// reps, split: the batch's.
+void decode_blocks(const DecodePlan &dp, uint32_t reps, BandSplit split, uint32_t *nb);
 // Launches the kernels with total[K] workgroups (the prefixes' last entries).
 hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStream_t s);
 
