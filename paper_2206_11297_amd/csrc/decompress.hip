@@ -779,27 +779,26 @@ __device__ __forceinline__ uint32_t ld_any16(const uint8_t *p) {
 
 // Dimension 3: the residuals' inclusive prefix sum across the panels, in
 // place, after which each panel holds its 2D residuals.  A thread takes 4
-// consecutive bins of the panel plane through every panel, kPanelsAhead
-// panels' bytes loaded before any is stored.
+// consecutive bins of the panel plane through its panels, kPanelsAhead
+// panels' bytes loaded before any is stored: through all of them, or, where
+// the planes are small and the panels many, through one of dp.panel_segs
+// segments, whose sums are taken first.
 constexpr uint32_t kPanelsAhead = 8;
-__global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
-  RSZ_DEC_FRAME(4);
-  const uint32_t plane = dp.Hb * dp.Wb, P = dp.P;
-  const uint32_t c = (bid * 256 + threadIdx.x) * 4;
-  if (c >= plane || !dec_ok(dp.status)) return;
-  const uint32_t n = min(4u, plane - c);
-  uint8_t *src = dp.res8 + c;
-  int32_t *res = dp.res + c;
-  uint32_t run[4] = {0u, 0u, 0u, 0u};
+
+// Panels [p0, p1) of the n (<= 4) bins at src: run advances past them; WRITE:
+// they become their prefix sums.  Returns whether an outlier's mark is left.
+template <bool WRITE>
+__device__ __forceinline__ bool panels_sum(uint8_t *src, int32_t *res, uint32_t plane, uint32_t p0,
+                                           uint32_t p1, uint32_t n, uint32_t (&run)[4]) {
   bool bad = false;
-  for (uint32_t p0 = 0; p0 < P; p0 += kPanelsAhead) {
+  for (; p0 < p1; p0 += kPanelsAhead) {
     uint32_t w[kPanelsAhead];
 #pragma unroll
     for (uint32_t k = 0; k < kPanelsAhead; ++k)
-      w[k] = ld_any32(src + (size_t)min(p0 + k, P - 1) * plane);
+      w[k] = ld_any32(src + (size_t)min(p0 + k, p1 - 1) * plane);
 #pragma unroll
     for (uint32_t k = 0; k < kPanelsAhead; ++k) {
-      if (p0 + k >= P) break;
+      if (p0 + k >= p1) break;
       const size_t o = (size_t)(p0 + k) * plane;
       uint32_t y = 0;
 #pragma unroll
@@ -811,18 +810,53 @@ __global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
           bad |= r == kMark;
         }
         run[t] += (uint32_t)r;
-        const bool small = run[t] + 127u < 255u;
-        y |= (small ? run[t] + 128u : 0u) << (8 * t);
-        if (!small && t < n) *gm(res + o + t) = (int32_t)run[t];
+        if (WRITE) {
+          const bool small = run[t] + 127u < 255u;
+          y |= (small ? run[t] + 128u : 0u) << (8 * t);
+          if (!small && t < n) *gm(res + o + t) = (int32_t)run[t];
+        }
       }
-      if (n == 4) {
+      if (WRITE && n == 4) {
         *(RSZ_G u32_any *)(src + o) = y;
-      } else {   // the plane's last bins: the bytes after them are another's
+      } else if (WRITE) {   // the plane's last bins: the bytes after them are another's
         for (uint32_t t = 0; t < n; ++t) *gm(src + o + t) = (uint8_t)(y >> (8 * t));
       }
     }
   }
-  if (bad) corrupt(dp.status);
+  return bad;
+}
+
+__global__ __launch_bounds__(256) void k_dec_panels(DecBatch db) {
+  RSZ_DEC_FRAME(4);
+  const uint32_t plane = dp.Hb * dp.Wb, P = dp.P, segs = dp.panel_segs;
+  if (segs == 1) {
+    const uint32_t c = (bid * 256 + threadIdx.x) * 4;
+    if (c >= plane || !dec_ok(dp.status)) return;
+    uint32_t run[4] = {0u, 0u, 0u, 0u};
+    if (panels_sum<true>(dp.res8 + c, dp.res + c, plane, 0, P, min(4u, plane - c), run))
+      corrupt(dp.status);
+    return;
+  }
+  __shared__ uint32_t s_sum[256][4];
+  __shared__ int s_ok;
+  if (threadIdx.x == 0) s_ok = dec_ok(dp.status);
+  __syncthreads();
+  if (!s_ok) return;
+  const uint32_t cols = 256 / segs, seg = threadIdx.x / cols, col = threadIdx.x - seg * cols;
+  const uint32_t c = (bid * cols + col) * 4, n = c < plane ? min(4u, plane - c) : 0u;
+  const uint32_t len = (P + segs - 1) / segs, p0 = min(seg * len, P), p1 = min(p0 + len, P);
+  uint32_t run[4] = {0u, 0u, 0u, 0u};
+  if (n) (void)panels_sum<false>(dp.res8 + c, dp.res + c, plane, p0, p1, n, run);
+#pragma unroll
+  for (uint32_t t = 0; t < 4; ++t) {
+    s_sum[threadIdx.x][t] = run[t];
+    run[t] = 0;
+  }
+  __syncthreads();   // (every segment of these bins is read before any is written)
+  for (uint32_t i = col; i < threadIdx.x; i += cols)
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) run[t] += s_sum[i][t];
+  if (n && panels_sum<true>(dp.res8 + c, dp.res + c, plane, p0, p1, n, run)) corrupt(dp.status);
 }
 
 // Dimension 1: the sum of each bin row (kDecRowsPerWave rows a wave).
@@ -1858,7 +1892,10 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, BandSplit split, uint32_
   nb[2] = (dp.nchunks + kChunkWaves * reps - 1) / (kChunkWaves * reps);
   nb[kDecOutliers] = (dp.n_out + 255) / 256;
   // inverse Lorenzo: prefix sums along each axis the predictor spans
-  if (dp.dim == 3) nb[4] = (dp.Hb * dp.Wb + 1023) / 1024;
+  if (dp.dim == 3) {
+    const uint32_t cols = 4 * (256 / dp.panel_segs);
+    nb[4] = (dp.Hb * dp.Wb + cols - 1) / cols;
+  }
   if (panel_fits(dp)) {
     nb[9] = dp.P * split.rows;
   } else {
@@ -1918,10 +1955,21 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
 // walks.  Every segment of a panel is summed by threads of its own and a band
 // adds the segments above it, so a tall panel is split (8 bands, 128 rows, a
 // segment) but into at most 16, which bounds what a band adds.
+//
+// And the segments of panels of k_dec_panels: a thread's panels follow one
+// another, 0.33 us each, so a frame with few bins a panel leaves the GPU to a
+// few long chains.  Up to 64 segments of 16 panels or more, while the threads
+// are few (a segment's panels are read twice).  k_dec_panels on one frame of
+// 300x48x60 at b = 1 105 -> 47 us, of 4000x48x8 1290 -> 72, of 60000x3x5 23.6
+// -> 0.64 ms.
 void decode_geometry(DecodePlan &dp) {
   dp.nbands = (dp.Hb + kDecTH - 1) / kDecTH;
   dp.seg_bands = std::max(8u, (dp.nbands + 15) / 16);
   dp.nsegs = (dp.nbands + dp.seg_bands - 1) / dp.seg_bands;
+  const uint32_t cols = (dp.Hb * dp.Wb + 3) / 4;
+  dp.panel_segs = 1;
+  while (dp.panel_segs < 64 && cols * dp.panel_segs < 2048 && dp.P >= 32 * dp.panel_segs)
+    dp.panel_segs *= 2;
 }
 
 // A workgroup of k_dec_chunks copies its stream's tables (18 KB) to LDS first,

@@ -271,6 +271,7 @@ struct DecodePlan {
   uint32_t *carry;      // dim 1: P*Hb row sums, then the carries into the rows
   uint32_t nbands, seg_bands, nsegs;   // bands of kDecTH bin rows of a panel, bands
                                        // of a k_dec_cols segment, segments
+  uint32_t panel_segs;                 // segments of panels (k_dec_panels)
   uint32_t *colbase;    // dims 2, 3 (nbands > 1): per panel and band, the column
                         // sums of its segment's rows above it (Wb a band)
   uint32_t *segtot;     // and per panel and segment, the segment's column sums
