@@ -1185,12 +1185,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     bool ok = check_params(p, d[f].npeaks) == RSZ_OK && !p->roi_coding && !p->run_coding &&
               d[f].frame && d[f].out && (d[f].npeaks == 0 || d[f].peaks);
     if (ok && ws && !(frames_out && frames_out[f])) return RSZ_ERR_ARG;
-    uint32_t rows = 0;
-    if (ok) {
-      const uint32_t wpr = (p->width + 31) / 32;
-      rows = (kVerifyMaskWords / wpr) / p->bin * p->bin;
-      ok = rows > 0;
-    }
+    if (ok) ok = kVerifyMaskWords / ((p->width + 31) / 32) >= p->bin;
     if (!ok) {
       dp.init_status = RSZ_ERR_ARG;
       region[f] = 256;   // its status word
@@ -1219,8 +1214,8 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     decode_geometry(dp);
     region[f] = decode_ws_bytes(dp);
     total += region[f];
-    rows = std::min<uint32_t>({rows, (uint32_t)align_up(p->height, p->bin),
-                               std::max(p->bin, kVerifyRows / p->bin * p->bin)});
+    const uint32_t rows = std::min<uint32_t>((uint32_t)align_up(p->height, p->bin),
+                                             kVerifyRows / p->bin * p->bin);
     vf.x = d[f].frame;
     vf.y = frames_out ? frames_out[f] : nullptr;
     vf.peaks = (const int32_t *)d[f].peaks;
@@ -1233,7 +1228,9 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     vf.mode = p->bin_mode;
     vf.eb = p->eb;
     vf.rows = rows;
+    vf.cols = p->width <= kVerifyCols ? p->width : kVerifyCols / (32 * p->bin) * (32 * p->bin);
     vf.chunks = (p->height + rows - 1) / rows;
+    vf.across = (p->width + vf.cols - 1) / vf.cols;
     vf.valid = 1;
   }
   if (need) *need = total;
@@ -1281,8 +1278,8 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     }
     vpre[f] = (uint32_t)wgs;
     if (vf.valid) {
-      wgs += (uint64_t)vf.P * vf.chunks;
-      mask_words = std::max(mask_words, vf.rows * ((vf.W + 31) / 32));
+      wgs += (uint64_t)vf.P * vf.chunks * vf.across;
+      mask_words = std::max(mask_words, vf.rows * ((vf.cols + 31) / 32));
     }
     if (wgs > 0x7FFFFFFFull) return RSZ_ERR_ARG;
   }

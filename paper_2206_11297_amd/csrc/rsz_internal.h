@@ -315,8 +315,12 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
 // streams decoded by the decoder kernels (their plans completed on the
 // device from the compression's totals), then every pixel checked against
 // the frame it came from.
-constexpr uint32_t kVerifyMaskWords = 8192;   // most words of a workgroup's LDS ROI bitmap
-constexpr uint32_t kVerifyRows = 32;          // raw rows of a workgroup, where they fit
+constexpr uint32_t kVerifyMaskWords = 8192;   // a frame is verified if its widest bin row's
+                                              // ROI bitmap takes no more words
+// Raw rows and columns of a workgroup's block (both in whole bins), and so 2048
+// words of bitmap at most.  Blocks across matter to wide panels: in blocks of
+// whole rows one of 1x16x65535 at b = 2 took 1016 us, now 72.
+constexpr uint32_t kVerifyRows = 32, kVerifyCols = 2048;
 constexpr uint32_t kVerifyOutlierBlocks = 16; // k_dec_outliers workgroups per frame
 struct VerifyFrame {
   const float *x;           // the frame
@@ -325,7 +329,8 @@ struct VerifyFrame {
   uint32_t npeaks, P, H, W, w, b, mode;
   double eb;
   uint32_t rows;            // raw rows per k_verify workgroup (a multiple of b)
-  uint32_t chunks;          // k_verify workgroups per panel
+  uint32_t cols;            // and columns (a multiple of 32 b, or the whole width)
+  uint32_t chunks, across;  // blocks down and across a panel
   int32_t valid;            // the descriptor was valid
   const FramePlan *cplan;   // the compression's plan of the frame (device)
   DecodePlan *dplan;        // the decoder's plan (device; k_vplan completes it)

@@ -58,8 +58,8 @@ __device__ __forceinline__ bool pixel_fails(float x, float y, bool roi, double m
 
 struct VerifyRows {
   const float *x, *y;        // the panel
-  const uint32_t *mask;      // the block's ROI bitmap, wpr words a row from row r0
-  uint32_t H, W, wpr, r0, mode;
+  const uint32_t *mask;      // the block's ROI bitmap, wpr words a row from row r0, column c0
+  uint32_t H, W, wpr, r0, c0, c1, mode;   // (c0 a multiple of 32 and of b)
   double eb;
 };
 
@@ -71,29 +71,29 @@ constexpr int kVerifyAhead = 2;
 template <int B>
 __device__ __forceinline__ uint32_t verify_vec(const VerifyRows &v, uint32_t Ia, uint32_t Ib,
                                                uint32_t lane) {
-  const uint32_t W4 = v.W / 4;
+  const uint32_t W4 = v.W / 4, a4 = v.c0 / 4, e4 = v.c1 / 4;
   uint32_t bad = 0;
   for (uint32_t I = Ia; I < Ib; I += 4) {
     const uint32_t nrow = min((uint32_t)B, v.H - I * B);
-    for (uint32_t c0 = 0; c0 < W4; c0 += 64 * kVerifyAhead) {
+    for (uint32_t c0 = a4; c0 < e4; c0 += 64 * kVerifyAhead) {
       f32x4 xv[kVerifyAhead][B], yv[kVerifyAhead][B];
 #pragma unroll
       for (int u = 0; u < kVerifyAhead; ++u)
 #pragma unroll
         for (int d = 0; d < B; ++d) {
           const size_t g = (size_t)(I * B + min((uint32_t)d, nrow - 1)) * W4 +
-                           min(c0 + 64 * u + lane, W4 - 1);
+                           min(c0 + 64 * u + lane, e4 - 1);
           xv[u][d] = __builtin_nontemporal_load(gm((const f32x4 *)v.x) + g);
           yv[u][d] = __builtin_nontemporal_load(gm((const f32x4 *)v.y) + g);
         }
 #pragma unroll
       for (int u = 0; u < kVerifyAhead; ++u) {
         const uint32_t c = c0 + 64 * u + lane;
-        if (c >= W4) continue;
+        if (c >= e4) continue;
         uint32_t roi[B];
 #pragma unroll
         for (int d = 0; d < B; ++d)
-          roi[d] = v.mask[(I * B + min((uint32_t)d, nrow - 1) - v.r0) * v.wpr + (c >> 3)] >>
+          roi[d] = v.mask[(I * B + min((uint32_t)d, nrow - 1) - v.r0) * v.wpr + ((c - a4) >> 3)] >>
                    (4 * (c & 7));
 #pragma unroll
         for (int e = 0; e < 4 / B; ++e) {
@@ -126,16 +126,15 @@ __device__ __forceinline__ uint32_t verify_vec(const VerifyRows &v, uint32_t Ia,
 // The same for any b and width, a lane on a bin.
 __device__ __forceinline__ uint32_t verify_any(const VerifyRows &v, uint32_t b, uint32_t Ia,
                                                uint32_t Ib, uint32_t lane) {
-  const uint32_t Wb = (v.W + b - 1) / b;
   uint32_t bad = 0;
   for (uint32_t I = Ia; I < Ib; I += 4)
-    for (uint32_t J = lane; J < Wb; J += 64) {
-      const uint32_t ia = I * b, ie = min(ia + b, v.H), ja = J * b, je = min(ja + b, v.W);
+    for (uint32_t ja = v.c0 + lane * b; ja < v.c1; ja += 64 * b) {
+      const uint32_t ia = I * b, ie = min(ia + b, v.H), je = min(ja + b, v.W);
       double S = 0.0;
       uint32_t n = 0;
       for (uint32_t r = ia; r < ie; ++r)
         for (uint32_t c = ja; c < je; ++c) {
-          const bool roi = (v.mask[(r - v.r0) * v.wpr + c / 32] >> (c & 31)) & 1u;
+          const bool roi = (v.mask[(r - v.r0) * v.wpr + (c - v.c0) / 32] >> (c & 31)) & 1u;
           if (v.mode || !roi) {
             S += (double)*gm(v.x + (size_t)r * v.W + c);
             ++n;
@@ -145,24 +144,24 @@ __device__ __forceinline__ uint32_t verify_any(const VerifyRows &v, uint32_t b, 
       for (uint32_t r = ia; r < ie; ++r)
         for (uint32_t c = ja; c < je; ++c) {
           const size_t g = (size_t)r * v.W + c;
-          const bool roi = (v.mask[(r - v.r0) * v.wpr + c / 32] >> (c & 31)) & 1u;
+          const bool roi = (v.mask[(r - v.r0) * v.wpr + (c - v.c0) / 32] >> (c & 31)) & 1u;
           bad += pixel_fails(*gm(v.x + g), *gm(v.y + g), roi, mean, v.eb);
         }
     }
   return bad;
 }
 
-// One workgroup per block of `rows` raw rows of a panel: the block's ROI
-// bitmap in LDS from the frame's peaks (the windows of Sec. IV, clipped to
-// the panel), then its bin rows, a wave on every fourth: the mean of the
-// bin's pixels that enter it (all of them, or those outside every window) in
-// fp64, and each pixel's check.  A background pixel passes when |y - mean| <=
-// eb + |y| 2^-23 + |mean| 2^-40: the bound, plus the float32 rounding of the
-// stored value and the rounding of the fp64 sums (taken here in another
-// order than the compressor's).  Both frames are read once and HBM bounds it:
-// 48 frames of 8x512x1024 at b = 2 take 0.28 ms, 5.7 TB/s (0.34 with
-// loads that fill the caches); one load a pixel
-// in blocks of 256 rows, which left 12 waves a CU, took 1.10 ms.
+// One workgroup per block of `rows` raw rows and `cols` columns of a panel:
+// the block's ROI bitmap in LDS from the frame's peaks (the windows of Sec.
+// IV, clipped to the panel), then its bin rows, a wave on every fourth: the
+// mean of the bin's pixels that enter it (all of them, or those outside every
+// window) in fp64, and each pixel's check.  A background pixel passes when
+// |y - mean| <= eb + |y| 2^-23 + |mean| 2^-40: the bound, plus the float32
+// rounding of the stored value and the rounding of the fp64 sums (taken here
+// in another order than the compressor's).  Both frames are read once and HBM
+// bounds it: 48 frames of 8x512x1024 at b = 2 take 0.28 ms, 5.7 TB/s (0.34
+// with loads that fill the caches); one load a pixel in blocks of 256 rows,
+// which left 12 waves a CU, took 1.10 ms.
 __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
   extern __shared__ uint32_t s_mask[];
   const uint32_t blkx = xcd_run();
@@ -172,9 +171,15 @@ __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
   // reports it)
   if (!vf.valid || vf.cplan->st->status != RSZ_OK || *vf.dplan->status != RSZ_OK) return;
   const uint32_t blk = blkx - vb.wg_prefix[f];
-  const uint32_t p = blk / vf.chunks, r0 = (blk - p * vf.chunks) * vf.rows;
   const uint32_t H = vf.H, W = vf.W, b = vf.b;
-  const uint32_t r1 = min(r0 + vf.rows, H), nr = r1 - r0, wpr = (W + 31) / 32;
+  uint32_t rb = blk, c0 = 0, c1 = W;
+  if (vf.across > 1) {
+    rb = blk / vf.across;
+    c0 = (blk - rb * vf.across) * vf.cols;
+    c1 = min(c0 + vf.cols, W);
+  }
+  const uint32_t p = rb / vf.chunks, r0 = (rb - p * vf.chunks) * vf.rows;
+  const uint32_t r1 = min(r0 + vf.rows, H), nr = r1 - r0, wpr = (c1 - c0 + 31) / 32;
   for (uint32_t i = threadIdx.x; i < nr * wpr; i += 256) s_mask[i] = 0u;
   __syncthreads();
   const int32_t h = (int32_t)(vf.w / 2);
@@ -182,12 +187,12 @@ __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
     if ((uint32_t)vf.peaks[3 * k] != p) continue;
     const int32_t pr = vf.peaks[3 * k + 1] - h, pc = vf.peaks[3 * k + 2] - h;
     const int32_t ra = max(pr, (int32_t)r0), rb = min(pr + (int32_t)vf.w, (int32_t)r1);
-    const int32_t ca = max(pc, 0), cb = min(pc + (int32_t)vf.w, (int32_t)W);
+    const int32_t ca = max(pc, (int32_t)c0), cb = min(pc + (int32_t)vf.w, (int32_t)c1);
     for (int32_t r = ra; r < rb; ++r)
       for (int32_t c = ca; c < cb;) {
         const int32_t e = min(cb, (c & ~31) + 32);
         const uint32_t bits = (e - c == 32 ? ~0u : ((1u << (e - c)) - 1u)) << (c & 31);
-        atomicOr(&s_mask[(uint32_t)(r - (int32_t)r0) * wpr + (uint32_t)c / 32], bits);
+        atomicOr(&s_mask[(uint32_t)(r - (int32_t)r0) * wpr + ((uint32_t)c - c0) / 32], bits);
         c = e;
       }
   }
@@ -203,6 +208,8 @@ __global__ __launch_bounds__(256) void k_verify(VerifyBatch vb) {
   v.W = W;
   v.wpr = wpr;
   v.r0 = r0;
+  v.c0 = c0;
+  v.c1 = c1;
   v.mode = vf.mode;
   v.eb = vf.eb;
   const bool vec = W % 4 == 0 && (((uintptr_t)v.x | (uintptr_t)v.y) & 15) == 0;
