@@ -231,7 +231,6 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
     }
     first = false;
   }
-  const uint32_t gsw = (uint32_t)group_strips((int)hp.common_b);
   // waves per binning workgroup: the first valid frame's tile_waves
   uint32_t wpg = kWaves;
   for (uint32_t f = 0; f < nframes; ++f)
@@ -242,32 +241,48 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
   // tile shape of each frame: the caller's tile_rows / tile_strips, else the
   // coarsest shape of the ladder below that gives the batch kTargetWaves
   // binning waves, down to 8-row single-strip tiles (shorter tiles re-read
-  // too many halo rows; measured on MI355X across 1..1000-frame batches)
+  // too many halo rows; measured on MI355X across 1..1000-frame batches).
+  // gsw: the most strips of a column group.
   static const uint32_t ladder[][2] = {{kMaxTH, 0}, {16, 0}, {8, 0}, {8, 1}};
-  auto shape_of = [&](uint32_t f, uint32_t rung, uint32_t &rows, uint32_t &strips) {
-    rows = d[f].tile_rows ? d[f].tile_rows : (th_cap ? th_cap : ladder[rung][0]);
-    const uint32_t sd = th_cap ? 0 : ladder[rung][1];
-    strips = d[f].tile_strips ? std::min(d[f].tile_strips, gsw) : (sd ? std::min(sd, gsw) : gsw);
+  auto plan_tiles = [&](uint32_t gsw) {
+    auto shape_of = [&](uint32_t f, uint32_t rung, uint32_t &rows, uint32_t &strips) {
+      rows = d[f].tile_rows ? d[f].tile_rows : (th_cap ? th_cap : ladder[rung][0]);
+      const uint32_t sd = th_cap ? 0 : ladder[rung][1];
+      strips = d[f].tile_strips ? std::min(d[f].tile_strips, gsw) : (sd ? std::min(sd, gsw) : gsw);
+    };
+    uint32_t rung = 0;
+    for (; rung + 1 < sizeof ladder / sizeof ladder[0]; ++rung) {
+      uint64_t waves = 0;
+      for (uint32_t f = 0; f < nframes; ++f) {
+        if (!valid[f]) continue;
+        uint32_t rows, strips;
+        shape_of(f, rung, rows, strips);
+        const Geom g = geometry(ps[f], np[f], rows, strips, wpg);
+        waves += (uint64_t)ps[f]->panels * g.cgs * g.groups * wpg;
+      }
+      if (waves >= kTargetWaves) break;
+    }
+    for (uint32_t f = 0; f < nframes; ++f)
+      if (valid[f]) {
+        uint32_t rows, strips;
+        shape_of(f, rung, rows, strips);
+        gs[f] = geometry(ps[f], np[f], rows, strips, wpg);
+      }
+    return layout(nframes, ps, np, gs, valid);
   };
-  uint32_t rung = 0;
-  for (; rung + 1 < sizeof ladder / sizeof ladder[0]; ++rung) {
-    uint64_t waves = 0;
-    for (uint32_t f = 0; f < nframes; ++f) {
-      if (!valid[f]) continue;
-      uint32_t rows, strips;
-      shape_of(f, rung, rows, strips);
-      const Geom g = geometry(ps[f], np[f], rows, strips, wpg);
-      waves += (uint64_t)ps[f]->panels * g.cgs * g.groups * wpg;
-    }
-    if (waves >= kTargetWaves) break;
+  Layout L = plan_tiles((uint32_t)group_strips((int)hp.common_b));
+  if (hp.common_b == 3) {
+    // Groups of three strips make fewer waves, for which the ladder may go to
+    // shorter tiles, whose tables take more memory (by up to a sixth); such a
+    // batch keeps single strips, as its caller's memory may be fixed
+    // (rsz_compress_noalloc).  It is the faster for them too: 200 frames of
+    // 5x187x389 99 -> 79 us in k_bin; where three strips take no more memory,
+    // 100 of 32x185x388 take 189 with them and 214 with one.
+    const std::vector<Geom> wide = gs;
+    Layout one = plan_tiles(1);
+    if (one.total < L.total) L = std::move(one);
+    else gs = wide;
   }
-  for (uint32_t f = 0; f < nframes; ++f)
-    if (valid[f]) {
-      uint32_t rows, strips;
-      shape_of(f, rung, rows, strips);
-      gs[f] = geometry(ps[f], np[f], rows, strips, wpg);
-    }
-  Layout L = layout(nframes, ps, np, gs, valid);
   if (need) *need = L.total;
   if (!ws) return RSZ_OK;
   if (ws_bytes < L.total) return RSZ_ERR_WORKSPACE;

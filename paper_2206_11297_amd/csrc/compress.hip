@@ -1056,9 +1056,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // Batches of one bin factor (2 to 8) and dimension whose frames are at least
 // a bin wide, where some frame's rows do not load as aligned vectors (b = 3
 // and 5 to 8; widths not a multiple of b): 200 frames of 5x187x389 take 82,
-// 98, 76, 80, 76, 54 and 55 us at b = 2 to 8, one load a pixel from k_bin took
-// 102, 213, 128, 192, 166, 99 and 181. At b = 1 a pixel is a load either way
-// and k_bin is the faster (180 against 203 us).
+// 79, 76, 80, 76, 54 and 55 us at b = 2 to 8, one load a pixel from k_bin took
+// 102, 213, 128, 192, 166, 99 and 181. The whole call on 60 frames of
+// 3x300x517 97, 76, 73, 61, 65, 66 and 69 us (106, 131, 101, 78, 100, 93 and
+// 186), on one of 1x2161x2070 60, 44, 43, 42, 47, 45 and 49 (66, 54, 50, 52,
+// 67, 61 and 98). At b = 1 a pixel is a load either way and k_bin is the
+// faster (180 against 203 us).
 template <int BB, int DIM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BB > 5 ? 3 : 4))) void k_bin_any(
     BatchPlan bp) {
