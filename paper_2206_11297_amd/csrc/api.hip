@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "result_slots.h"
 #include "rsz_internal.h"
 
 namespace rsz {
@@ -536,54 +537,15 @@ static int stage_to_device(void *dst, const void *src, size_t n, hipStream_t s) 
   return RSZ_OK;
 }
 
-// Results of the calls that wait for the device: pinned words that kernels (or
-// a copy) write and the host reads after its stream synchronisation.  A copy
-// to pageable memory instead made the runtime stage it and wait twice.  One
-// page, made once; a call takes a slot and gives it back, and a call that
-// finds none falls back to the workspace and a pageable copy.
 namespace {
-struct ResultSlot {
-  uint64_t bytes;
-  int32_t status;
-  uint8_t header[kHeader];
-  uint8_t pad[128 - 12 - kHeader];
-};
-static_assert(sizeof(ResultSlot) == 128, "a slot is two cache lines");
-constexpr int kResultSlots = 32;
-std::mutex g_result_mu;
-ResultSlot *g_results = nullptr;
-bool g_results_failed = false;
-uint32_t g_results_used = 0;   // bit i: slot i is taken
-
-class Result {
- public:
-  Result() {
-    std::lock_guard<std::mutex> lk(g_result_mu);
-    if (!g_results && !g_results_failed) {
-      void *p = nullptr;
-      if (hipHostMalloc(&p, kResultSlots * sizeof(ResultSlot),
-                        hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-        g_results = (ResultSlot *)p;
-      else
-        g_results_failed = true;
-    }
-    if (!g_results || g_results_used == ~0u) return;
-    index_ = __builtin_ctz(~g_results_used);
-    g_results_used |= 1u << index_;
-    slot = g_results + index_;
-  }
-  ~Result() {
-    if (!slot) return;
-    std::lock_guard<std::mutex> lk(g_result_mu);
-    g_results_used &= ~(1u << index_);
-  }
-  Result(const Result &) = delete;
-  Result &operator=(const Result &) = delete;
-  ResultSlot *slot = nullptr;   // null: none free
-
- private:
-  int index_ = 0;
-};
+static_assert(kResultHeader == kHeader, "a slot holds a stream's header");
+void *pinned_page(size_t n) {
+  void *p = nullptr;
+  if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+  (void)hipGetLastError();   // (the launches that follow must not report it)
+  return nullptr;
+}
+ResultSlots g_results(pinned_page);
 }  // namespace
 
 // Host record of a prepared batch (the public rsz_batch_plan is its storage).
@@ -914,9 +876,12 @@ static int single_frame(const rsz_params *p, const float *d_frame, const rsz_pea
   // the size and status come back through pinned words (the allocation-free
   // entry point and the debug call: through the workspace's tail)
   if (!dbg && !direct_copy) {
-    Result result;
+    Result result(g_results);
     void *dev = nullptr;
-    if (result.slot && hipHostGetDevicePointer(&dev, result.slot, 0) == hipSuccess) {
+    const bool mapped =
+        result.slot && hipHostGetDevicePointer(&dev, result.slot, 0) == hipSuccess;
+    if (result.slot && !mapped) (void)hipGetLastError();
+    if (mapped) {
       if (ws_bytes < single_extra()) return RSZ_ERR_WORKSPACE;
       ResultSlot *ds = (ResultSlot *)dev;
       rsz_frame_desc d = one_desc(p, d_frame, d_peaks, npeaks, d_out, out_cap);
@@ -925,7 +890,10 @@ static int single_frame(const rsz_params *p, const float *d_frame, const rsz_pea
                    false, hp);
       // (the slot is the device's until the stream has finished, also when
       // the call failed half way)
-      if (hipStreamSynchronize(s) != hipSuccess) return st ? st : RSZ_ERR_HIP;
+      if (hipStreamSynchronize(s) != hipSuccess) {
+        result.abandon();
+        return st ? st : RSZ_ERR_HIP;
+      }
       if (st) return st;
       const int32_t status = *(volatile int32_t *)&result.slot->status;
       if (status == RSZ_OK || status == RSZ_ERR_CAPACITY)
@@ -1047,14 +1015,17 @@ int rsz_decompress(const void *d_in, uint64_t in_bytes, float *d_frame, uint64_t
       (uintptr_t)d_ws % 256)
     return RSZ_ERR_ARG;
   if (in_bytes < kHeader) return RSZ_ERR_CORRUPT;
-  Result result;
+  Result result(g_results);
   uint8_t own_header[kHeader];
   int32_t own_status = 0;
   uint8_t *hdr = result.slot ? result.slot->header : own_header;
   int32_t *status = result.slot ? &result.slot->status : &own_status;
   if (hipMemcpyAsync(hdr, d_in, kHeader, hipMemcpyDeviceToHost, s) != hipSuccess)
     return RSZ_ERR_HIP;
-  if (hipStreamSynchronize(s) != hipSuccess) return RSZ_ERR_HIP;
+  if (hipStreamSynchronize(s) != hipSuccess) {
+    result.abandon();
+    return RSZ_ERR_HIP;
+  }
   DecodePlan dp;
   int st = parse_header(hdr, kHeader, in_bytes, nullptr, nullptr, &dp);
   if (st) return st;
@@ -1066,7 +1037,10 @@ int rsz_decompress(const void *d_in, uint64_t in_bytes, float *d_frame, uint64_t
   if (st) return st;
   if (hipMemcpyAsync(status, status_word, 4, hipMemcpyDeviceToHost, s) != hipSuccess)
     return RSZ_ERR_HIP;
-  if (hipStreamSynchronize(s) != hipSuccess) return RSZ_ERR_HIP;
+  if (hipStreamSynchronize(s) != hipSuccess) {
+    result.abandon();
+    return RSZ_ERR_HIP;
+  }
   return *(volatile int32_t *)status;
 }
 
