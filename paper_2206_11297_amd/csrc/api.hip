@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -556,17 +557,11 @@ struct PlanRecord {
 };
 static_assert(sizeof(PlanRecord) <= sizeof(rsz_batch_plan), "plan record too large");
 
-// Queue the whole path for a batch; results land in res_bytes/res_status.
-static int enqueue(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_bytes,
-                   int32_t *res_status, void *ws, uint64_t ws_bytes, hipStream_t s,
-                   const rsz_debug_bufs *dbg, bool front_only, HostPlan &hp,
-                   bool direct_copy = false) {
-  const int st = build_plan(nframes, d, res_bytes, res_status, (uint8_t *)ws, ws_bytes,
-                            0, hp, nullptr, dbg);
-  if (st) return st;
-  // direct_copy: the plan goes straight from hp (which the caller keeps
-  // until the stream has finished) instead of through the pinned staging
-  // slots, which may grow
+// Queue the whole path of a planned batch.  direct_copy: the plan goes straight
+// from hp (which the caller keeps until the stream has finished) instead of
+// through the pinned staging slots, which may grow.
+static int queue_plan(const HostPlan &hp, void *ws, hipStream_t s, const rsz_debug_bufs *dbg,
+                      bool direct_copy) {
   if (direct_copy ? hipMemcpyAsync(ws, hp.bytes.data(), hp.bytes.size(), hipMemcpyHostToDevice,
                                    s) != hipSuccess
                   : stage_to_device(ws, hp.bytes.data(), hp.bytes.size(), s) != RSZ_OK)
@@ -574,7 +569,7 @@ static int enqueue(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_byte
   if (launch_compress_front_b(hp.bp, hp.common_b, hp.common_dim, s, dbg != nullptr) !=
       hipSuccess)
     return RSZ_ERR_HIP;
-  if (!front_only && launch_compress_back(hp.bp, s) != hipSuccess) return RSZ_ERR_HIP;
+  if (!dbg && launch_compress_back(hp.bp, s) != hipSuccess) return RSZ_ERR_HIP;
   return RSZ_OK;
 }
 
@@ -873,45 +868,52 @@ static int single_frame(const rsz_params *p, const float *d_frame, const rsz_pea
     return RSZ_ERR_ARG;
   if ((uintptr_t)d_frame % 16 || (uintptr_t)d_ws % 256 || (d_out && (uintptr_t)d_out % 16))
     return RSZ_ERR_ARG;
-  // the size and status come back through pinned words (the allocation-free
-  // entry point and the debug call: through the workspace's tail)
-  if (!dbg && !direct_copy) {
-    Result result(g_results);
-    void *dev = nullptr;
-    const bool mapped =
-        result.slot && hipHostGetDevicePointer(&dev, result.slot, 0) == hipSuccess;
-    if (result.slot && !mapped) (void)hipGetLastError();
-    if (mapped) {
-      if (ws_bytes < single_extra()) return RSZ_ERR_WORKSPACE;
-      ResultSlot *ds = (ResultSlot *)dev;
-      rsz_frame_desc d = one_desc(p, d_frame, d_peaks, npeaks, d_out, out_cap);
-      HostPlan hp;
-      st = enqueue(1, &d, &ds->bytes, &ds->status, d_ws, ws_bytes - single_extra(), s, nullptr,
-                   false, hp);
-      // (the slot is the device's until the stream has finished, also when
-      // the call failed half way)
-      if (hipStreamSynchronize(s) != hipSuccess) {
-        result.abandon();
-        return st ? st : RSZ_ERR_HIP;
-      }
-      if (st) return st;
-      const int32_t status = *(volatile int32_t *)&result.slot->status;
-      if (status == RSZ_OK || status == RSZ_ERR_CAPACITY)
-        *h_out_bytes = *(volatile uint64_t *)&result.slot->bytes;
-      return status;
-    }
-  }
-  uint64_t need = 0;
-  rsz_workspace_bytes(p, npeaks, &need);
-  if (ws_bytes < need) return RSZ_ERR_WORKSPACE;
-  // result slots at the workspace tail
-  uint8_t *tail = (uint8_t *)d_ws + (need - single_extra());
-  uint64_t *res_bytes = (uint64_t *)tail;
-  int32_t *res_status = (int32_t *)(tail + 8);
+  // the plan first: a call that it refuses makes no HIP call (its stream may
+  // be busy, or capturing)
+  if (ws_bytes < single_extra()) return RSZ_ERR_WORKSPACE;
   rsz_frame_desc d = one_desc(p, d_frame, d_peaks, npeaks, d_out ? d_out : (void *)d_ws, out_cap);
   HostPlan hp;
-  st = enqueue(1, &d, res_bytes, res_status, d_ws, need - single_extra(), s, dbg, dbg != nullptr,
-               hp, direct_copy);
+  uint64_t need = 0;
+  st = build_plan(1, &d, nullptr, nullptr, (uint8_t *)d_ws, ws_bytes - single_extra(), 0, hp,
+                  &need, dbg);
+  if (st) return st;
+  // the size and status come back through pinned words (the allocation-free
+  // entry point, the debug call and a call that finds no slot: through the
+  // workspace's tail)
+  uint8_t *tail = (uint8_t *)d_ws + need;
+  uint64_t *res_bytes = (uint64_t *)tail;
+  int32_t *res_status = (int32_t *)(tail + 8);
+  std::optional<Result> result;
+  bool pinned = false;
+  if (!dbg && !direct_copy) {
+    result.emplace(g_results);
+    void *dev = nullptr;
+    if (result->slot) {
+      pinned = hipHostGetDevicePointer(&dev, result->slot, 0) == hipSuccess;
+      if (!pinned) (void)hipGetLastError();
+    }
+    if (pinned) {
+      res_bytes = &((ResultSlot *)dev)->bytes;
+      res_status = &((ResultSlot *)dev)->status;
+    }
+  }
+  FramePlan *plan = (FramePlan *)hp.bytes.data();
+  plan->res_bytes = res_bytes;
+  plan->res_status = res_status;
+  st = queue_plan(hp, d_ws, s, dbg, direct_copy);
+  if (pinned) {
+    // (the slot is the device's until the stream has finished, also when the
+    // call failed half way)
+    if (hipStreamSynchronize(s) != hipSuccess) {
+      result->abandon();
+      return st ? st : RSZ_ERR_HIP;
+    }
+    if (st) return st;
+    const int32_t status = *(volatile int32_t *)&result->slot->status;
+    if (status == RSZ_OK || status == RSZ_ERR_CAPACITY)
+      *h_out_bytes = *(volatile uint64_t *)&result->slot->bytes;
+    return status;
+  }
   if (st) return st;
   if (dbg) {
     // the codebook intermediates sit in the frame's state and region
@@ -982,8 +984,9 @@ int rsz_compress_batch(uint32_t nframes, const rsz_frame_desc *h_descs, uint64_t
   if (nframes == 0 || !h_descs || !d_out_bytes || !d_status || !d_ws) return RSZ_ERR_ARG;
   if ((uintptr_t)d_ws % 256) return RSZ_ERR_ARG;
   HostPlan hp;
-  return enqueue(nframes, h_descs, d_out_bytes, d_status, d_ws, ws_bytes, (hipStream_t)stream,
-                 nullptr, false, hp);
+  const int st = build_plan(nframes, h_descs, d_out_bytes, d_status, (uint8_t *)d_ws, ws_bytes,
+                            0, hp, nullptr, nullptr);
+  return st ? st : queue_plan(hp, d_ws, (hipStream_t)stream, nullptr, false);
 }
 
 int rsz_stream_info(const void *h_stream, uint64_t n, rsz_params *p, uint32_t *npeaks,
