@@ -1793,20 +1793,23 @@ __device__ __forceinline__ bool roi_window(const DecodePlan &dp, uint32_t k, uin
 
 // Windows that overlap must carry the same bits for the pixels they share.
 // With few windows (roi_pairs) the wave of window k lists the earlier windows
-// that meet it, 64 a step, and compares each of its pixels with one of them
-// that covers it: the nearest in the list.  By induction along the windows
-// over a pixel all of them then agree, so a pixel is compared once however
-// many windows lie over it.  More windows are compared with the frame that
-// all of them were written to, by k_dec_roi_check: the listing grows with the
-// square of their number, and a wave steps through its list for every 64
-// pixels.  So the line lies at kRoiListed windows and kRoiSteps such steps of
-// the last wave (256 windows of 17, 128 of 25, 60 of 36), both known from the
-// header.  60 windows of 17 a frame, k_dec_roi (and k_dec_roi_check) in us on
-// 1 and on 50 frames: spread out 9 and 11 (the pass: 13 and 21), on one spot
-// 10 and 14, crowded in 51 x 51 pixels 18 and 24; 256 on one spot 11 and 29
-// (12 and 24).  Every element against every window met, with the line at 512
-// windows of any size: 60 on one spot 103 and 116, 256 427 and 1311, 512
-// windows of 101 there 35 and 112 ms against 0.10 and 0.45 of the pass.
+// that meet it, 64 a step.  Where these cover little of it, it compares the
+// rectangle shared with each.  Where they crowd, it compares each of its
+// pixels with one of them that covers it, the nearest in the list: by
+// induction along the windows over a pixel all of them then agree, so a pixel
+// is compared once however many windows lie over it.  More windows are
+// compared with the frame that all of them were written to, by
+// k_dec_roi_check: the listing grows with the square of their number, and
+// where they crowd a wave steps through its list for every 64 pixels.  So the
+// line lies at kRoiListed windows and kRoiSteps such steps of the last wave
+// (256 windows of 17, 128 of 25, 60 of 36), both known from the header.
+// k_dec_roi (and k_dec_roi_check) in us on 1 and on 50 frames with 60 windows
+// of 17: spread out 7 and 10 (the pass: 13 and 18), on one spot 10 and 13,
+// crowded in 51 x 51 pixels 18 and 24; 256 on one spot 11 and 30 (12 and 24);
+// 8 of 60 on 7 frames, in pairs, 18 (pixel by pixel 44).  Every element
+// against every window met, with the line at 512 windows of any size: 60 on
+// one spot 103 and 116, 256 427 and 1311, 512 windows of 101 there 35 and 112
+// ms against 0.10 and 0.45 of the pass.
 constexpr uint32_t kRoiListed = 512, kRoiSteps = 1280;
 __host__ __device__ inline bool roi_pairs(const DecodePlan &dp) {
   return dp.npeaks <= kRoiListed && dp.npeaks * ((dp.w * dp.w + 63) / 64) <= kRoiSteps;
@@ -1817,18 +1820,18 @@ __device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, u
   const uint32_t w = dp.w, ww = w * w;
   const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
   const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W, iw = (int32_t)w;
-  const int32_t pa = pk[3 * k], r = pk[3 * k + 1], c = pk[3 * k + 2];
-  // the earlier windows that meet this one: number (9 bits), and where their
-  // corner lies from this one's, row and column + 1023 (11 bits each)
-  uint32_t n = 0;
+  const int32_t pa = pk[3 * k], r = (int32_t)pk[3 * k + 1] - h, c = (int32_t)pk[3 * k + 2] - h;
+  uint32_t n = 0, area = 0;   // the earlier windows that meet this one; of the shared rectangles
   for (uint32_t b = 0; b < k; b += 64) {
     const uint32_t o = min(b + lane, k - 1);
-    const int32_t opa = pk[3 * o], dr = (int32_t)pk[3 * o + 1] - r, dc = (int32_t)pk[3 * o + 2] - c;
+    const int32_t opa = pk[3 * o];
+    const int32_t dr = (int32_t)pk[3 * o + 1] - h - r, dc = (int32_t)pk[3 * o + 2] - h - c;
     const bool meet = b + lane < k && opa == pa && dr > -iw && dr < iw && dc > -iw && dc < iw;
     const uint64_t m = __ballot(meet);
-    if (meet)
-      list[n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
-          o << 22 | (uint32_t)(dr + 1023) << 11 | (uint32_t)(dc + 1023);
+    if (meet) {
+      list[n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = roi_entry(o, dr, dc);
+      area += (uint32_t)((iw - abs(dr)) * (iw - abs(dc)));
+    }
     n += (uint32_t)__builtin_popcountll(m);
   }
   if (n == 0) return false;
@@ -1838,15 +1841,16 @@ __device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, u
   const RSZ_G uint32_t *mine = pay + (size_t)k * ww;
   const int32_t du = (int32_t)(64 / w), dv = (int32_t)(64 % w);
   int32_t u = (int32_t)(lane / w), v = (int32_t)lane - u * iw;   // element e of window k
-  bool bad = false;
   for (uint32_t e0 = 0; e0 < ww; e0 += 64) {
-    const int32_t i = r - h + u, j = c - h + v;
-    bool open = u < iw && i >= 0 && i < H && j >= 0 && j < W;   // in the frame, not yet compared
+    const int32_t i = r + u, j = c + v;
+    bool open = u < iw && i >= 0 && i < H && j >= 0 && j < W;   // in the panel, not yet compared
     uint32_t at = 0;
     bool found = false;
     for (uint32_t t = n; t > 0 && __ballot(open) != 0;) {
-      // the next up to 64 of the list, a lane each
-      const uint32_t t0 = (t - 1) & ~63u, x64 = list[min(t0 + lane, n - 1)];
+      if (((t - 1) & ~63u) != t0) {
+        t0 = (t - 1) & ~63u;
+        x64 = list[min(t0 + lane, n - 1)];
+      }
       for (; t > t0 && __ballot(open) != 0; --t) {
         const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)((t - 1) & 63));
         const int32_t ou = u - ((int32_t)((x >> 11) & 2047u) - 1023);
@@ -1876,6 +1880,51 @@ __global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
   if (k >= dp.npeaks || !dec_ok(dp.status)) return;
   roi_window<false>(dp, k, threadIdx.x & 63);
   if (roi_pairs(dp) && roi_overlaps(dp, k, s_list[wv], threadIdx.x & 63)) corrupt(dp.status);
+
+// An earlier window in a wave's list: its number (9 bits), and where its
+// corner lies from this one's, row and column + 1023 (11 bits each).
+__device__ __forceinline__ uint32_t roi_entry(uint32_t o, int32_t dr, int32_t dc) {
+  return o << 22 | (uint32_t)(dr + 1023) << 11 | (uint32_t)(dc + 1023);
+}
+
+// Whether the rectangle that window k (its corner at row r, column c of the
+// panel) shares with the listed window x differs inside the panel.
+__device__ __forceinline__ bool roi_rect_differs(const RSZ_G uint32_t *pay, uint32_t k, uint32_t x,
+                                                 int32_t w, int32_t r, int32_t c, int32_t H,
+                                                 int32_t W, uint32_t lane) {
+  const int32_t dr = (int32_t)((x >> 11) & 2047u) - 1023, dc = (int32_t)(x & 2047u) - 1023;
+  const int32_t u0 = max(max(0, dr), -r), u1 = min(min(w, w + dr), H - r);
+  const int32_t v0 = max(max(0, dc), -c), v1 = min(min(w, w + dc), W - c);
+  if (u0 >= u1 || v0 >= v1) return false;
+  const uint32_t rw = (uint32_t)(v1 - v0), rh = (uint32_t)(u1 - u0);
+  const uint32_t ww = (uint32_t)(w * w);
+  const RSZ_G uint32_t *mine = pay + (size_t)k * ww + u0 * w + v0;
+  const RSZ_G uint32_t *other = pay + (size_t)(x >> 22) * ww + (u0 - dr) * w + (v0 - dc);
+  const uint32_t da = 64 / rw, db = 64 - da * rw;
+  uint32_t a = lane / rw, b = lane - a * rw;   // row and column of the rectangle
+  constexpr int kAhead = 4;   // elements a lane loads before it compares any
+  bool bad = false;
+  for (uint32_t e0 = lane; e0 < rw * rh; e0 += 64 * kAhead) {
+    uint32_t m[kAhead], o[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const bool in = e0 + 64 * q < rw * rh;
+      const uint32_t at = a * (uint32_t)w + b;
+      m[q] = in ? mine[at] : 0u;
+      o[q] = in ? other[at] : 0u;
+      a += da;
+      b += db;
+      if (b >= rw) {
+        b -= rw;
+        ++a;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) bad |= m[q] != o[q];
+  }
+  return bad;
+}
+
 }
 __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   RSZ_DEC_FRAME(13);
@@ -1900,6 +1949,15 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, BandSplit split, uint32_
     nb[9] = dp.P * split.rows;
   } else {
     if (dp.dim == 1) {
+  area = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(area), 63);
+  bool bad = false;
+  uint32_t t0 = (n - 1) & ~63u, x64 = list[min(t0 + lane, n - 1)];   // the list's last 64
+  if (area <= 2 * ww && t0 == 0) {
+    for (uint32_t t = 0; t < n; ++t)
+      bad |= roi_rect_differs(pay, k, (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)t), iw, r,
+                              c, H, W, lane);
+    return bad;
+  }
       nb[5] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
       nb[6] = 1;
     } else if (dp.nbands > 1) {
