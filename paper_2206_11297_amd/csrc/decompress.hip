@@ -1045,6 +1045,32 @@ struct Band {
     }
     esc = __ballot(z != 0) != 0;
   }
+  // Rows [0, lo) leave and row lo becomes row 0.
+  __device__ __forceinline__ void drop(uint32_t lo) {
+    auto words = [&](int d) {
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int k = 0; k < R / C; ++k) w[s][k] = k + d < R / C ? w[s][k + d] : 0u;
+    };
+    auto bits = [&](int d) {
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int k = 0; k < R / C; ++k)
+          w[s][k] = __builtin_amdgcn_alignbit(k + 1 < R / C ? w[s][k + 1] : 0u, w[s][k], d);
+    };
+    if (lo & 8) words(8 / C);
+    if (lo & 4) words(4 / C);
+    if (lo & 2) {
+      if constexpr (C <= 2) words(2 / C);
+      else bits(16);
+    }
+    if (lo & 1) {
+      if constexpr (C == 1) words(1);
+      else bits(8 * V);
+    }
+  }
   __device__ __forceinline__ int32_t residual(int s, int i, int v) const {
     return (int8_t)(w[s][i / C] >> (8 * ((i % C) * V + v)));
   }
@@ -1077,6 +1103,32 @@ __device__ __forceinline__ void band_sums(const Band<B> &bd, const int32_t *res,
   }
 }
 
+// The column sums of the band's rows [0, lo), added to acc.
+template <int B, int NS>
+__device__ __forceinline__ void add_rows(const Band<B> &bd, const int32_t *res, uint32_t Wb,
+                                         int ns, uint32_t lo, int lane,
+                                         uint32_t (&acc)[Band<B>::S][Band<B>::V]) {
+  using D = Band<B>;
+#pragma unroll
+  for (int s = 0; s < (NS ? NS : D::S); ++s) {
+    if (!NS && s >= ns) continue;
+#pragma unroll
+    for (int i = 0; i < D::R; ++i)
+#pragma unroll
+      for (int v = 0; v < D::V; ++v)
+        acc[s][v] += (uint32_t)i < lo ? (uint32_t)bd.residual(s, i, v) : 0u;
+    if (bd.esc) {   // escapes, counted as -128 above
+      const uint32_t J = (uint32_t)((64 * s + lane) * D::V);
+#pragma unroll
+      for (int i = 0; i < D::R; ++i)
+#pragma unroll
+        for (int v = 0; v < D::V; ++v)
+          if ((uint32_t)i < lo && bd.residual(s, i, v) == D::kEsc)
+            acc[s][v] += 128u + (uint32_t)*gm(res + (size_t)i * Wb + J + v);
+    }
+  }
+}
+
 // What the row loop needs of the plan, in registers before it starts.
 struct EmitPlan {
   uint32_t b, Wb, H, W;
@@ -1085,7 +1137,16 @@ struct EmitPlan {
   const int32_t *res;
   float *out;           // and its first pixel
   uint32_t I0, nr;
-  uint32_t lo, hi;      // SPLIT: the band's rows that this wave emits
+  // rows [lo, lo + n) of the band alone
+  __device__ __forceinline__ EmitPlan rows(uint32_t lo, uint32_t n) const {
+    EmitPlan e = *this;
+    e.src += (size_t)lo * Wb;
+    e.res += (size_t)lo * Wb;
+    e.out += (size_t)lo * b * W;
+    e.I0 += lo;
+    e.nr = n;
+    return e;
+  }
 };
 
 // One row's q of the band's strips: r the residuals, acc the column sums
@@ -1155,8 +1216,7 @@ __device__ __forceinline__ void row_pixels(const EmitPlan &ep, uint32_t I, float
 // i's.  The loop loads nothing: loads and stores share one wait counter, so
 // a load's wait would wait for every store before it too, and the pixels of
 // a row would leave only when the row before had reached memory.
-// SPLIT: rows [lo, hi) alone, the others being other waves'.
-template <int B, int NS, bool D1, bool SPLIT>
+template <int B, int NS, bool D1>
 __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd, uint32_t j0,
                                           int ns, int lane,
                                           uint32_t (&acc)[Band<B>::S][Band<B>::V],
@@ -1164,19 +1224,9 @@ __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd,
   using D = Band<B>;
   constexpr int N = NS ? NS : D::S;
   const uint32_t b = B ? (uint32_t)B : ep.b;
-  if (SPLIT && !D1 && ep.lo) {   // the columns' sums over the rows above
-#pragma unroll
-    for (int s = 0; s < N; ++s)
-#pragma unroll
-      for (int i = 0; i < D::R; ++i)
-#pragma unroll
-        for (int v = 0; v < D::V; ++v)
-          acc[s][v] += (uint32_t)i < ep.lo ? (uint32_t)bd.residual(s, i, v) : 0u;
-  }
 #pragma unroll
   for (int i = 0; i < D::R; ++i) {
-    if (SPLIT && !D1 ? (uint32_t)i < ep.lo || (uint32_t)i >= ep.hi : (uint32_t)i >= ep.nr)
-      continue;
+    if ((uint32_t)i >= ep.nr) continue;
     int32_t r[N][D::V];
     float q[N][D::V];
 #pragma unroll
@@ -1193,7 +1243,7 @@ __device__ __forceinline__ void band_emit(const EmitPlan &ep, const Band<B> &bd,
 // The same for a band with escapes (rare): row by row, the bytes read again
 // (one row ahead) and the residuals of the bytes 0 from res.  Returns
 // whether an outlier's mark is left.
-template <int B, bool D1, bool SPLIT>
+template <int B, bool D1>
 __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, int ns, int lane,
                                               uint32_t (&acc)[Band<B>::S][Band<B>::V],
                                               uint32_t &carry) {
@@ -1212,10 +1262,9 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
       }
   };
   bool bad = false;
-  const uint32_t i1 = SPLIT ? ep.hi : ep.nr;
   load(0);
 #pragma unroll 1
-  for (uint32_t i = 0; i < i1; ++i) {
+  for (uint32_t i = 0; i < ep.nr; ++i) {
     int32_t r[D::S][D::V];
     float q[D::S][D::V];
 #pragma unroll
@@ -1233,14 +1282,6 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
       if (s < ns)
 #pragma unroll
         for (int v = 0; v < D::V; ++v) bad |= r[s][v] == kMark;
-    if (SPLIT && !D1 && i < ep.lo) {   // a row above
-#pragma unroll
-      for (int s = 0; s < D::S; ++s)
-        if (s < ns)
-#pragma unroll
-          for (int v = 0; v < D::V; ++v) acc[s][v] += (uint32_t)r[s][v];
-      continue;
-    }
     uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)carry, (int)i);
     row_q<B, 0, D1>(ep.step, ns, r, acc, c, q);
     carry = (uint32_t)lane == i ? c : carry;
@@ -1249,12 +1290,9 @@ __device__ __forceinline__ bool band_emit_esc(const EmitPlan &ep, uint32_t j0, i
   return bad;
 }
 
-// part: which of the `split` waves that share the band's rows.
 __device__ __forceinline__ EmitPlan emit_plan(const DecodePlan &dp, uint32_t p, uint32_t I0,
-                                              uint32_t nr, uint32_t part, uint32_t split) {
+                                              uint32_t nr) {
   EmitPlan ep;
-  ep.lo = part * (kDecTH / split);
-  ep.hi = min(ep.lo + kDecTH / split, nr);
   ep.b = dp.b;
   ep.Wb = dp.Wb;
   ep.H = dp.H;
@@ -1266,6 +1304,19 @@ __device__ __forceinline__ EmitPlan emit_plan(const DecodePlan &dp, uint32_t p, 
   ep.I0 = I0;
   ep.nr = nr;
   return ep;
+}
+
+// The parts of a band's rows, of kDecTH / split rows each.  A panel of one band
+// has as many as its rows fill, as evenly as they go: workgroups without a row
+// leave CUs idle (66 frames of 6x56x714 at b = 7, half of whose parts were
+// empty, 37 us; 24 without them).
+__host__ __device__ inline uint32_t band_parts(const DecodePlan &dp, uint32_t split) {
+  const uint32_t rows = kDecTH / split;
+  return dp.nbands > 1 ? split : (dp.Hb + rows - 1) / rows;
+}
+__device__ __forceinline__ uint32_t part_rows(const DecodePlan &dp, uint32_t split) {
+  const uint32_t parts = band_parts(dp, split);
+  return dp.nbands > 1 ? kDecTH / split : (dp.Hb + parts - 1) / parts;
 }
 
 // One of the waves that share a row's groups of strips.
@@ -1308,21 +1359,21 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
                                          uint32_t part, uint32_t split, ColPart cols, int lane) {
   using D = Band<B>;
   const uint32_t Hb = dp.Hb, Wb = dp.Wb;
-  // (dimension 1 needs nothing of the rows above: its part is a band of its own)
-  const uint32_t rows = SPLIT && D1 ? kDecTH / split : kDecTH;
-  const uint32_t I0 = band * kDecTH + (SPLIT && D1 ? part * rows : 0u);
-  if (SPLIT && D1 && I0 >= Hb) return;
-  const uint32_t nr = min(rows, Hb - I0);
-  const EmitPlan ep = SPLIT && D1 ? emit_plan(dp, p, I0, nr, 0, 1)
-                                  : emit_plan(dp, p, I0, nr, part, split);
-  if (SPLIT && ep.lo >= ep.hi) return;   // (a last band of few rows)
+  // the part's rows, from row lo of the band (dimension 1 needs nothing of the
+  // rows above: its part is a band of its own)
+  const uint32_t rows = SPLIT ? part_rows(dp, split) : kDecTH;
+  const uint32_t B0 = band * kDecTH, lo = part * rows;
+  if (SPLIT && B0 + lo >= Hb) return;   // (a last band of few rows)
+  const uint32_t nr = min(rows, Hb - B0 - lo);
+  const EmitPlan ep = emit_plan(dp, p, B0 + lo, nr);
+  const uint32_t up = SPLIT && !D1 ? lo : 0u;   // rows of the band above the part's
   const uint32_t seg = band / dp.seg_bands, nsegs = dp.nsegs;
   const uint32_t *cb = D1 || band == seg * dp.seg_bands
                            ? nullptr : dp.colbase + ((size_t)p * dp.nbands + band) * Wb;
   const uint32_t *st = D1 ? nullptr : dp.segtot + (size_t)p * nsegs * Wb;
   const bool marks = dp.dim != 3;   // (dimension 3: k_dec_panels looked)
   int32_t *status = dp.status;
-  uint32_t carry = D1 ? *gm(dp.carry + (size_t)p * Hb + I0 + min((uint32_t)lane, nr - 1)) : 0u;
+  uint32_t carry = D1 ? *gm(dp.carry + (size_t)p * Hb + ep.I0 + min((uint32_t)lane, nr - 1)) : 0u;
   bool bad = false;
   uint32_t ja = 0, jb = Wb;   // the columns of its group of strips
   if (SPLIT && cols.split > 1) {
@@ -1331,7 +1382,8 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
     jb = min(Wb, D::kCols * (groups * (cols.part + 1) / cols.split));
     if (ja >= jb) return;
     // and its one row's q left of them
-    uint32_t left = left_sum(ep.src, ep.res, Wb, D1 ? 1u : ep.lo + 1, ja, lane);
+    uint32_t left = left_sum(ep.src - (size_t)up * Wb, ep.res - (size_t)up * Wb, Wb, up + 1, ja,
+                             lane);
     auto add = [&](const uint32_t *sums) {
       for (uint32_t j = 4 * (uint32_t)lane; j < ja; j += 256) {
         const u32x4 x = *(const RSZ_G u32x4a *)(sums + j);
@@ -1346,7 +1398,7 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
   for (uint32_t j0 = ja; j0 < jb; j0 += D::kCols) {
     const int ns = (int)min((uint32_t)D::S, (Wb - j0 + 64 * D::V - 1) / (64 * D::V));
     D bd;
-    bd.template load<0>(ep.src, Wb, j0, ns, SPLIT ? ep.hi : nr, lane);
+    bd.template load<0>(ep.src - (size_t)up * Wb, Wb, j0, ns, up + nr, lane);
     uint32_t acc[D::S][D::V];
 #pragma unroll
     for (int s = 0; s < D::S; ++s) {
@@ -1364,9 +1416,13 @@ __device__ __forceinline__ void dec_band(const DecodePlan &dp, uint32_t p, uint3
           if (J + v < Wb) acc[s][v] += *gm(cb + J + v);
       }
     }
-    if (bd.esc) bad |= band_emit_esc<B, D1, SPLIT>(ep, j0, ns, lane, acc, carry);
-    else if (!D1 && ns == D::S) band_emit<B, D::S, D1, SPLIT>(ep, bd, j0, ns, lane, acc, carry);
-    else band_emit<B, 0, D1, SPLIT>(ep, bd, j0, ns, lane, acc, carry);
+    if (SPLIT && up) {
+      add_rows<B, 0>(bd, ep.res - (size_t)up * Wb + j0, Wb, ns, up, lane, acc);
+      bd.drop(up);
+    }
+    if (bd.esc) bad |= band_emit_esc<B, D1>(ep, j0, ns, lane, acc, carry);
+    else if (!D1 && ns == D::S) band_emit<B, D::S, D1>(ep, bd, j0, ns, lane, acc, carry);
+    else band_emit<B, 0, D1>(ep, bd, j0, ns, lane, acc, carry);
   }
   if (bad && marks) corrupt(status);
 }
@@ -1382,7 +1438,8 @@ __global__ __launch_bounds__(256) void k_dec_pixels(DecBatch db) {
   const uint32_t it = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t split = SPLIT ? db.row_split : 1u;
   ColPart cols = {0u, SPLIT ? db.col_split : 1u};
-  const uint32_t row = it / cols.split, pb = row / split, part = row - pb * split;
+  const uint32_t parts = SPLIT ? band_parts(dp, split) : 1u;
+  const uint32_t row = it / cols.split, pb = row / parts, part = row - pb * parts;
   cols.part = it - row * cols.split;
   if (pb >= dp.P * dp.nbands || !dec_ok(dp.status)) return;
   const int lane = threadIdx.x & 63;
@@ -1416,11 +1473,12 @@ __host__ __device__ inline bool panel_fits(const DecodePlan &dp) {
 }
 
 // Wave wv's band of panel p; every wave of the workgroup calls it (mine: the
-// panel has the band).  Returns whether the band holds escapes, its pixels
-// then left to the caller (acc: the column sums above).
+// panel has the band).  own: its rows to emit, from row lo of the band.
+// Returns whether the band holds escapes, its pixels then left to the caller
+// (acc: the column sums above).
 template <int B, int NS, bool SPLIT>
-__device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint32_t wv,
-                                             uint32_t *s_col, int lane,
+__device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, const EmitPlan &own, uint32_t lo,
+                                             bool mine, uint32_t wv, uint32_t *s_col, int lane,
                                              uint32_t (&acc)[Band<B>::S][Band<B>::V]) {
   using D = Band<B>;
   const uint32_t Wb = ep.Wb;
@@ -1437,7 +1495,7 @@ __device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint
       }
   }
   __syncthreads();
-  if (!mine) return false;
+  if (!mine || (SPLIT && own.nr == 0)) return false;
 #pragma unroll
   for (int s = 0; s < NS; ++s)
 #pragma unroll
@@ -1448,6 +1506,10 @@ __device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint
 #pragma unroll
       for (int v = 0; v < D::V; ++v)
         acc[s][v] += s_col[k * Wb + min((uint32_t)((64 * s + lane) * D::V + v), Wb - 1)];
+  if (SPLIT && lo) {
+    add_rows<B, NS>(bd, ep.res, Wb, NS, lo, lane, acc);
+    bd.drop(lo);
+  }
   // lanes past the row add nothing to its sums
 #pragma unroll
   for (int s = 0; s < NS; ++s)
@@ -1456,7 +1518,7 @@ __device__ __forceinline__ bool dec_panel_ns(const EmitPlan &ep, bool mine, uint
       if ((uint32_t)((64 * s + lane) * D::V + v) >= Wb) acc[s][v] = 0;
   if (bd.esc) return true;
   uint32_t carry = 0;
-  band_emit<B, NS, false, SPLIT>(ep, bd, 0, NS, lane, acc, carry);
+  band_emit<B, NS, false>(own, bd, 0, NS, lane, acc, carry);
   return false;
 }
 
@@ -1467,21 +1529,23 @@ __device__ __forceinline__ void dec_panel(const DecodePlan &dp, uint32_t p, uint
   using D = Band<B>;
   const bool mine = wv < dp.nbands;
   const uint32_t I0 = mine ? wv * kDecTH : 0u;
-  const EmitPlan ep = emit_plan(dp, p, I0, min(kDecTH, dp.Hb - I0), part, split);
+  const EmitPlan ep = emit_plan(dp, p, I0, min(kDecTH, dp.Hb - I0));
+  const uint32_t rows = SPLIT ? part_rows(dp, split) : kDecTH, lo = min(part * rows, ep.nr);
+  const EmitPlan own = ep.rows(lo, min(rows, ep.nr - lo));
   const bool marks = dp.dim != 3;   // (dimension 3: k_dec_panels looked)
   int32_t *status = dp.status;
   const int ns = (int)((ep.Wb + 64 * D::V - 1) / (64 * D::V));
   uint32_t acc[D::S][D::V];
   bool esc = false;
   switch (ns) {
-    case 1: esc = dec_panel_ns<B, 1, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
-    case 2: esc = dec_panel_ns<B, 2, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
-    case 3: if constexpr (D::S >= 3) esc = dec_panel_ns<B, 3, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
-    default: if constexpr (D::S >= 4) esc = dec_panel_ns<B, 4, SPLIT>(ep, mine, wv, s_col, lane, acc); break;
+    case 1: esc = dec_panel_ns<B, 1, SPLIT>(ep, own, lo, mine, wv, s_col, lane, acc); break;
+    case 2: esc = dec_panel_ns<B, 2, SPLIT>(ep, own, lo, mine, wv, s_col, lane, acc); break;
+    case 3: if constexpr (D::S >= 3) esc = dec_panel_ns<B, 3, SPLIT>(ep, own, lo, mine, wv, s_col, lane, acc); break;
+    default: if constexpr (D::S >= 4) esc = dec_panel_ns<B, 4, SPLIT>(ep, own, lo, mine, wv, s_col, lane, acc); break;
   }
   if (esc) {
     uint32_t carry = 0;
-    if (band_emit_esc<B, false, SPLIT>(ep, 0, ns, lane, acc, carry) && marks) corrupt(status);
+    if (band_emit_esc<B, false>(own, 0, ns, lane, acc, carry) && marks) corrupt(status);
   }
 }
 
@@ -1499,7 +1563,8 @@ __global__ __launch_bounds__(1024) void k_dec_panel(DecBatch db) {
   if (!s_ok) return;
   const int lane = threadIdx.x & 63;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t split = SPLIT ? db.row_split : 1u, p = bid / split, part = bid - p * split;
+  const uint32_t split = SPLIT ? db.row_split : 1u;
+  const uint32_t parts = SPLIT ? band_parts(dp, split) : 1u, p = bid / parts, part = bid - p * parts;
   switch (dp.b) {
     case 1: dec_panel<1, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
     case 2: dec_panel<2, SPLIT>(dp, p, part, split, wv, s_col, lane); break;
@@ -1814,72 +1879,6 @@ constexpr uint32_t kRoiListed = 512, kRoiSteps = 1280;
 __host__ __device__ inline bool roi_pairs(const DecodePlan &dp) {
   return dp.npeaks <= kRoiListed && dp.npeaks * ((dp.w * dp.w + 63) / 64) <= kRoiSteps;
 }
-// list: this wave's kRoiListed words.
-__device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t *list,
-                                             uint32_t lane) {
-  const uint32_t w = dp.w, ww = w * w;
-  const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
-  const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W, iw = (int32_t)w;
-  const int32_t pa = pk[3 * k], r = (int32_t)pk[3 * k + 1] - h, c = (int32_t)pk[3 * k + 2] - h;
-  uint32_t n = 0, area = 0;   // the earlier windows that meet this one; of the shared rectangles
-  for (uint32_t b = 0; b < k; b += 64) {
-    const uint32_t o = min(b + lane, k - 1);
-    const int32_t opa = pk[3 * o];
-    const int32_t dr = (int32_t)pk[3 * o + 1] - h - r, dc = (int32_t)pk[3 * o + 2] - h - c;
-    const bool meet = b + lane < k && opa == pa && dr > -iw && dr < iw && dc > -iw && dc < iw;
-    const uint64_t m = __ballot(meet);
-    if (meet) {
-      list[n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = roi_entry(o, dr, dc);
-      area += (uint32_t)((iw - abs(dr)) * (iw - abs(dc)));
-    }
-    n += (uint32_t)__builtin_popcountll(m);
-  }
-  if (n == 0) return false;
-  wave_sync();
-  const RSZ_G uint32_t *pay =
-      gm(dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi));
-  const RSZ_G uint32_t *mine = pay + (size_t)k * ww;
-  const int32_t du = (int32_t)(64 / w), dv = (int32_t)(64 % w);
-  int32_t u = (int32_t)(lane / w), v = (int32_t)lane - u * iw;   // element e of window k
-  for (uint32_t e0 = 0; e0 < ww; e0 += 64) {
-    const int32_t i = r + u, j = c + v;
-    bool open = u < iw && i >= 0 && i < H && j >= 0 && j < W;   // in the panel, not yet compared
-    uint32_t at = 0;
-    bool found = false;
-    for (uint32_t t = n; t > 0 && __ballot(open) != 0;) {
-      if (((t - 1) & ~63u) != t0) {
-        t0 = (t - 1) & ~63u;
-        x64 = list[min(t0 + lane, n - 1)];
-      }
-      for (; t > t0 && __ballot(open) != 0; --t) {
-        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)((t - 1) & 63));
-        const int32_t ou = u - ((int32_t)((x >> 11) & 2047u) - 1023);
-        const int32_t ov = v - ((int32_t)(x & 2047u) - 1023);
-        if (open && (uint32_t)ou < w && (uint32_t)ov < w) {
-          at = (x >> 22) * ww + (uint32_t)ou * w + (uint32_t)ov;
-          found = true;
-          open = false;
-        }
-      }
-    }
-    if (found) bad |= mine[e0 + lane] != pay[at];
-    u += du;
-    v += dv;
-    if (v >= iw) {
-      v -= iw;
-      ++u;
-    }
-  }
-  return bad;
-}
-
-__global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
-  RSZ_DEC_FRAME(12);
-  __shared__ uint32_t s_list[4][kRoiListed];
-  const uint32_t wv = threadIdx.x >> 6, k = bid * 4 + wv;
-  if (k >= dp.npeaks || !dec_ok(dp.status)) return;
-  roi_window<false>(dp, k, threadIdx.x & 63);
-  if (roi_pairs(dp) && roi_overlaps(dp, k, s_list[wv], threadIdx.x & 63)) corrupt(dp.status);
 
 // An earlier window in a wave's list: its number (9 bits), and where its
 // corner lies from this one's, row and column + 1023 (11 bits each).
@@ -1925,6 +1924,81 @@ __device__ __forceinline__ bool roi_rect_differs(const RSZ_G uint32_t *pay, uint
   return bad;
 }
 
+// list: this wave's kRoiListed words.
+__device__ __forceinline__ bool roi_overlaps(const DecodePlan &dp, uint32_t k, uint32_t *list,
+                                             uint32_t lane) {
+  const uint32_t w = dp.w, ww = w * w;
+  const RSZ_G uint16_t *pk = gm((const uint16_t *)(dp.in + dp.off_peaks));
+  const int32_t h = (int32_t)(w / 2), H = (int32_t)dp.H, W = (int32_t)dp.W, iw = (int32_t)w;
+  const int32_t pa = pk[3 * k], r = (int32_t)pk[3 * k + 1] - h, c = (int32_t)pk[3 * k + 2] - h;
+  uint32_t n = 0, area = 0;   // the earlier windows that meet this one; of the shared rectangles
+  for (uint32_t b = 0; b < k; b += 64) {
+    const uint32_t o = min(b + lane, k - 1);
+    const int32_t opa = pk[3 * o];
+    const int32_t dr = (int32_t)pk[3 * o + 1] - h - r, dc = (int32_t)pk[3 * o + 2] - h - c;
+    const bool meet = b + lane < k && opa == pa && dr > -iw && dr < iw && dc > -iw && dc < iw;
+    const uint64_t m = __ballot(meet);
+    if (meet) {
+      list[n + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = roi_entry(o, dr, dc);
+      area += (uint32_t)((iw - abs(dr)) * (iw - abs(dc)));
+    }
+    n += (uint32_t)__builtin_popcountll(m);
+  }
+  if (n == 0) return false;
+  wave_sync();
+  const RSZ_G uint32_t *pay =
+      gm(dp.roi_coding ? dp.roi_payload : (const uint32_t *)(dp.in + dp.off_roi));
+  area = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(area), 63);
+  bool bad = false;
+  uint32_t t0 = (n - 1) & ~63u, x64 = list[min(t0 + lane, n - 1)];   // the list's last 64
+  if (area <= 2 * ww && t0 == 0) {
+    for (uint32_t t = 0; t < n; ++t)
+      bad |= roi_rect_differs(pay, k, (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)t), iw, r,
+                              c, H, W, lane);
+    return bad;
+  }
+  const RSZ_G uint32_t *mine = pay + (size_t)k * ww;
+  const int32_t du = (int32_t)(64 / w), dv = (int32_t)(64 % w);
+  int32_t u = (int32_t)(lane / w), v = (int32_t)lane - u * iw;   // element e of window k
+  for (uint32_t e0 = 0; e0 < ww; e0 += 64) {
+    const int32_t i = r + u, j = c + v;
+    bool open = u < iw && i >= 0 && i < H && j >= 0 && j < W;   // in the panel, not yet compared
+    uint32_t at = 0;
+    bool found = false;
+    for (uint32_t t = n; t > 0 && __ballot(open) != 0;) {
+      if (((t - 1) & ~63u) != t0) {
+        t0 = (t - 1) & ~63u;
+        x64 = list[min(t0 + lane, n - 1)];
+      }
+      for (; t > t0 && __ballot(open) != 0; --t) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)((t - 1) & 63));
+        const int32_t ou = u - ((int32_t)((x >> 11) & 2047u) - 1023);
+        const int32_t ov = v - ((int32_t)(x & 2047u) - 1023);
+        if (open && (uint32_t)ou < w && (uint32_t)ov < w) {
+          at = (x >> 22) * ww + (uint32_t)ou * w + (uint32_t)ov;
+          found = true;
+          open = false;
+        }
+      }
+    }
+    if (found) bad |= mine[e0 + lane] != pay[at];
+    u += du;
+    v += dv;
+    if (v >= iw) {
+      v -= iw;
+      ++u;
+    }
+  }
+  return bad;
+}
+
+__global__ __launch_bounds__(256) void k_dec_roi(DecBatch db) {
+  RSZ_DEC_FRAME(12);
+  __shared__ uint32_t s_list[4][kRoiListed];
+  const uint32_t wv = threadIdx.x >> 6, k = bid * 4 + wv;
+  if (k >= dp.npeaks || !dec_ok(dp.status)) return;
+  roi_window<false>(dp, k, threadIdx.x & 63);
+  if (roi_pairs(dp) && roi_overlaps(dp, k, s_list[wv], threadIdx.x & 63)) corrupt(dp.status);
 }
 __global__ __launch_bounds__(256) void k_dec_roi_check(DecBatch db) {
   RSZ_DEC_FRAME(13);
@@ -1946,24 +2020,16 @@ void decode_blocks(const DecodePlan &dp, uint32_t reps, BandSplit split, uint32_
     nb[4] = (dp.Hb * dp.Wb + cols - 1) / cols;
   }
   if (panel_fits(dp)) {
-    nb[9] = dp.P * split.rows;
+    nb[9] = dp.P * band_parts(dp, split.rows);
   } else {
     if (dp.dim == 1) {
-  area = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(area), 63);
-  bool bad = false;
-  uint32_t t0 = (n - 1) & ~63u, x64 = list[min(t0 + lane, n - 1)];   // the list's last 64
-  if (area <= 2 * ww && t0 == 0) {
-    for (uint32_t t = 0; t < n; ++t)
-      bad |= roi_rect_differs(pay, k, (uint32_t)__builtin_amdgcn_readlane((int)x64, (int)t), iw, r,
-                              c, H, W, lane);
-    return bad;
-  }
       nb[5] = (dp.P * dp.Hb + 4 * kDecRowsPerWave - 1) / (4 * kDecRowsPerWave);
       nb[6] = 1;
     } else if (dp.nbands > 1) {
       nb[7] = (uint32_t)(((uint64_t)dp.P * dp.nsegs * ((dp.Wb + 3) / 4) + 255) / 256);
     }
-    nb[8] = (uint32_t)(((uint64_t)dp.P * dp.nbands * split.rows * split.cols + 3) / 4);
+    nb[8] = (uint32_t)(
+        ((uint64_t)dp.P * dp.nbands * band_parts(dp, split.rows) * split.cols + 3) / 4);
   }
   if (dp.roi_coding) {
     const uint32_t wins = 4 * roi_wins(dp.w);
