@@ -1166,7 +1166,7 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
   const uint64_t h_vf = align_up((uint64_t)sizeof(VerifyFrame) * n, 256);
   const uint64_t h_vp = align_up(4ull * (n + 1), 256);
   const uint64_t head = h_dp + h_pre + h_vf + h_vp;
-  uint64_t total = head;
+  uint64_t total = head, blocks = 0;
   for (uint32_t f = 0; f < n; ++f) {
     DecodePlan &dp = dps[f];
     VerifyFrame &vf = vfs[f];
@@ -1206,8 +1206,6 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     decode_geometry(dp);
     region[f] = decode_ws_bytes(dp);
     total += region[f];
-    const uint32_t rows = std::min<uint32_t>((uint32_t)align_up(p->height, p->bin),
-                                             kVerifyRows / p->bin * p->bin);
     vf.x = d[f].frame;
     vf.y = frames_out ? frames_out[f] : nullptr;
     vf.peaks = (const int32_t *)d[f].peaks;
@@ -1219,12 +1217,20 @@ static int verify_plan(const PlanRecord &rec, uint32_t n, const rsz_frame_desc *
     vf.b = p->bin;
     vf.mode = p->bin_mode;
     vf.eb = p->eb;
-    vf.rows = rows;
     vf.cols = p->width <= kVerifyCols ? p->width : kVerifyCols / (32 * p->bin) * (32 * p->bin);
-    vf.chunks = (p->height + rows - 1) / rows;
     vf.across = (p->width + vf.cols - 1) / vf.cols;
     vf.valid = 1;
+    blocks += (uint64_t)p->panels * ((p->height + kVerifyRows - 1) / kVerifyRows) * vf.across;
   }
+  // blocks of more rows where panels are narrow and the blocks many: as many
+  // pixels as kVerifyRows rows of 256
+  const uint32_t most = (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, blocks / 2048));
+  for (VerifyFrame &vf : vfs)
+    if (vf.valid) {
+      const uint32_t r = kVerifyRows * std::min(most, std::max(1u, 256 / vf.W));
+      vf.rows = std::min<uint32_t>((uint32_t)align_up(vf.H, vf.b), r / vf.b * vf.b);
+      vf.chunks = (vf.H + vf.rows - 1) / vf.rows;
+    }
   if (need) *need = total;
   if (!ws) return RSZ_OK;
   if (!d_bad || (uintptr_t)ws % 256) return RSZ_ERR_ARG;

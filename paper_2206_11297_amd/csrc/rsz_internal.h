@@ -317,8 +317,8 @@ hipError_t launch_decompress(const DecBatch &db, const uint32_t *total, hipStrea
 // the frame it came from.
 constexpr uint32_t kVerifyMaskWords = 8192;   // a frame is verified if its widest bin row's
                                               // ROI bitmap takes no more words
-// Raw rows and columns of a workgroup's block (both in whole bins), and so 2048
-// words of bitmap at most.  Blocks across matter to wide panels: in blocks of
+// Raw rows and columns of a workgroup's block (both in whole bins; more rows
+// of narrow panels), and so 2048 words of bitmap at most.  Blocks across matter to wide panels: in blocks of
 // whole rows one of 1x16x65535 at b = 2 took 1016 us, now 72.
 constexpr uint32_t kVerifyRows = 32, kVerifyCols = 2048;
 constexpr uint32_t kVerifyOutlierBlocks = 16; // k_dec_outliers workgroups per frame
