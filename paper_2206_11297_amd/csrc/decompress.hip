@@ -355,9 +355,16 @@ __device__ __forceinline__ uint64_t rice_codes(const BitSrc &src, uint32_t &pos,
   return adv;
 }
 
+// Fewest bits of a slice (but for a chunk's only one): a start is found by the
+// lane before only once a slice holds a few codes, and where each held less
+// than one, as in chunks of few and long runs, the lanes found theirs one
+// after the other (10 frames of 16x512x1024 at b = 2, eb 5: 20 us, 40 in 64
+// slices whatever the length, 23, 34 and 48 with 64, 128 and 256 bits a slice).
+constexpr uint32_t kRunSlice = 32;
+
 // One wave per chunk.  Chunk c's codes occupy run bits [runoffs[c],
-// runoffs[c + 1]), cut into 64 slices and decoded as k_dec_chunks decodes its
-// own (self-synchronising starts); a scan of the Huffman bits that the lanes'
+// runoffs[c + 1]), cut into up to 64 slices and decoded as k_dec_chunks decodes
+// its own (self-synchronising starts); a scan of the Huffman bits that the lanes'
 // codes stand for places their one bits, which are ORed into the chunk's
 // words in LDS and leave as whole words (the two that the chunks beside may
 // share by atomics, on words that k_dec_tables cleared).  One thread a chunk,
@@ -408,8 +415,13 @@ __global__ __launch_bounds__(256) void k_dec_runs(DecBatch db) {
     for (uint32_t i = lane; i < nout; i += 64) s_out[wv][i] = 0u;
   wave_sync();
   const uint64_t len = rend - rs;
-  const uint32_t lim = lane == 63 ? rend : rs + (uint32_t)(len * (uint64_t)(lane + 1) / 64);
-  uint32_t from = rs + (uint32_t)(len * (uint64_t)lane / 64), pos = from;
+  const uint32_t slices = min(64u, max(1u, (rend - rs) / kRunSlice));
+  auto cut = [&](uint32_t i) {
+    if (slices == 64) return i == 64 ? rend : rs + (uint32_t)(len * i / 64);
+    return i >= slices ? rend : rs + (uint32_t)len * i / slices;   // (a short chunk)
+  };
+  const uint32_t lim = cut((uint32_t)lane + 1);
+  uint32_t from = cut((uint32_t)lane), pos = from;
   uint64_t adv = 0;
   bool converged = false, inv = false, last_ok = false;
   for (int round = 0; round <= 64 && !converged; ++round) {
