@@ -298,9 +298,12 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
   uint32_t *xp = kp + (nframes + 1);
   uint64_t tiles = 0, units = 0, npk_total = 0, chunks_done = 0, fixes = 0;
   bool all_vec = true, all_lines = true, all_wide = true;
-  uint64_t all_chunks = 0;
+  uint64_t all_chunks = 0, frame_bytes = 0;
   for (uint32_t f = 0; f < nframes; ++f)
-    if (valid[f]) all_chunks += gs[f].nchunks;
+    if (valid[f]) {
+      all_chunks += gs[f].nchunks;
+      frame_bytes += 4ull * ps[f]->panels * ps[f]->height * ps[f]->width;
+    }
   const uint32_t cpw = encode_cpw(all_chunks);
   for (uint32_t f = 0; f < nframes; ++f) {
     FramePlan &fp = fpl[f];
@@ -459,7 +462,7 @@ static int build_plan(uint32_t nframes, const rsz_frame_desc *d, uint64_t *res_b
   hp.bp.total_peaks = (uint32_t)npk_total;
   hp.bp.cpw = cpw;
   hp.bp.all_vec = all_vec ? 1u : 0u;
-  hp.bp.all_lines = all_lines ? 1u : 0u;
+  hp.bp.stream_lines = all_lines && frame_bytes > kCacheBytes ? 1u : 0u;
   hp.bp.all_wide = all_wide ? 1u : 0u;
   hp.bp.bin_waves = wpg;
   hp.bp.frames = (const FramePlan *)(ws + L.plans);

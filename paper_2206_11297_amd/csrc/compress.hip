@@ -1044,9 +1044,13 @@ __global__ __launch_bounds__(256) void k_bin(BatchPlan bp) {
 // the kernel holds its strips' loads and its sums in 128 registers without
 // spilling (five waves spill 23 registers, and measured 0.17 ms slower on
 // the 1000-frame CSPAD batch; six spill more).
-// NT: every frame's rows are whole lines (load_vec; 48 frames 8x512x1024 0.21
-// -> 0.19 ms, 64 of 16x512x1024 0.53 -> 0.51; with rows of 1552 bytes, whose
-// lines two strips or a row and the next share, 1.84 -> 1.92 ms).
+// NT: every frame's rows are whole lines and the frames more than the
+// memory-side cache holds (load_vec; 48 frames 8x512x1024 0.21 -> 0.19 ms, 64
+// of 16x512x1024 0.53 -> 0.51; with rows of 1552 bytes, whose lines two strips
+// or a row and the next share, 1.84 -> 1.92 ms). Frames that the cache holds
+// are read faster through it: 9 of 1x2048x2048 73 us, 82 by these loads (97
+// and 87 where the cache holds something else), 20 of 8x512x1024, 320 MiB, 84
+// and 82.
 template <int BB, int DIM, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bin_vec(
     BatchPlan bp) {
@@ -2982,12 +2986,12 @@ static hipError_t launch_bin(const BatchPlan &bp, uint32_t b, hipStream_t s) {
   switch (b) {
     case 1: RSZ_LAUNCH_B("k_bin", (k_bin<1, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp); break;
     case 2:
-      if (!DEBUG && DIM != 0 && bp.all_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
+      if (!DEBUG && DIM != 0 && bp.stream_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
       else if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<2, DIM, false>), grid, 64 * bp.bin_waves, s, bp);
       else RSZ_LAUNCH_B("k_bin", (k_bin<2, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp);
       break;
     case 4:
-      if (!DEBUG && DIM != 0 && bp.all_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
+      if (!DEBUG && DIM != 0 && bp.stream_lines) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM, DIM != 0>), grid, 64 * bp.bin_waves, s, bp);
       else if (!DEBUG && bp.all_vec) RSZ_LAUNCH_B("k_bin", (k_bin_vec<4, DIM, false>), grid, 64 * bp.bin_waves, s, bp);
       else RSZ_LAUNCH_B("k_bin", (k_bin<4, DEBUG, DIM>), grid, 64 * bp.bin_waves, s, bp);
       break;

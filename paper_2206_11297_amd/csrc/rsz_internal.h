@@ -121,6 +121,10 @@ __host__ __device__ __forceinline__ uint32_t fdiv(FastDiv f, uint32_t n) {
   return (uint32_t)((((uint64_t)n * f.m) >> 32) + n) >> f.l;
 }
 
+// The memory-side cache (256 MiB): frames of no more bytes may still be in it,
+// written by the copy or the kernel before.
+constexpr uint64_t kCacheBytes = 256ull << 20;
+
 // Per-frame mutable state in the workspace.
 struct FrameState {
   int32_t status;
@@ -215,7 +219,7 @@ struct BatchPlan {
   uint32_t total_tiles, total_units, total_peaks, total_chunks;
   uint32_t cpw;                  // chunks encoded by one k_encode workgroup
   uint32_t all_vec;              // every frame's rows load as float2/float4 (k_bin)
-  uint32_t all_lines;            // and are whole 128-byte lines
+  uint32_t stream_lines;         // and are whole 128-byte lines of frames that no cache holds
   uint32_t all_wide;             // every frame is at least a bin wide (k_bin_any)
   uint32_t bin_waves;            // waves per k_bin workgroup (1..kWaves)
   uint32_t total_fix;            // workgroups of k_lorenzo_dims (0: every frame is 2D)
