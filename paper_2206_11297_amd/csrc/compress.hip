@@ -2961,7 +2961,8 @@ hipError_t launch_debug_codes(const BatchPlan &bp, uint32_t nbins, uint16_t *out
   return hipGetLastError();
 }
 
-// `b`: the common bin factor of the batch, or 0 (mixed or not 1, 2, 4).
+// `b`: the common bin factor of the batch, 1 to 8, or 0 for a batch that mixes
+// them.
 template <bool DEBUG, int DIM>
 static hipError_t launch_bin(const BatchPlan &bp, uint32_t b, hipStream_t s) {
   if (bp.total_tiles == 0) return hipSuccess;

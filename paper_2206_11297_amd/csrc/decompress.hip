@@ -22,8 +22,10 @@
 //                   carry into each row.
 //   k_dec_cols      dimensions 2 and 3: the column sums above each band of
 //                   kDecTH bin rows.
-//   k_dec_pixels    one wave per band: column sums down the band, row sums
-//                   across it -> q, and every pixel float(q * 2eb).
+//   k_dec_pixels    one wave per band (in small batches several): column sums
+//                   down the band, row sums across it -> q, and every pixel
+//                   float(q * 2eb).  k_dec_panel: the same, a workgroup per
+//                   panel, where one covers it.
 //   k_dec_roi_decode  coded ROI: class tables, then per window its values
 //                   and their inverse prediction (k_dec_roi_unpred for
 //                   windows larger than LDS holds).
@@ -1027,7 +1029,7 @@ struct Band {
   __device__ __forceinline__ void load(const uint8_t *src, uint32_t Wb, uint32_t j0, int ns,
                                        uint32_t nr, int lane) {
     uint32_t z = 0;
-    // the strips in pairs, their loads in flight together
+    // a strip's loads, of all the rows, go out together
 #pragma unroll
     for (int s = 0; s < (NS ? NS : S); ++s) {
       if (!NS && s >= ns) continue;
