@@ -357,12 +357,13 @@ __device__ __forceinline__ uint64_t rice_codes(const BitSrc &src, uint32_t &pos,
   return adv;
 }
 
-// Fewest bits of a slice (but for a chunk's only one): a start is found by the
-// lane before only once a slice holds a few codes, and where each held less
-// than one, as in chunks of few and long runs, the lanes found theirs one
-// after the other (10 frames of 16x512x1024 at b = 2, eb 5: 20 us, 40 in 64
-// slices whatever the length, 23, 34 and 48 with 64, 128 and 256 bits a slice).
-constexpr uint32_t kRunSlice = 32;
+// Fewest bits of a slice (but for a chunk's only one), a few codes of parameter
+// k: a start is found by the lane before only once a slice holds some, and
+// where each held less than one, as in chunks of few and long runs, the lanes
+// found theirs one after the other (10 frames of 16x512x1024 at b = 2, eb 5: 21
+// us, 40 in 64 slices whatever the length; 32 bits for every k are too many for
+// short codes: 300 frames of 2x34x91 at b = 8, eb 0.5: 13 us against 25).
+__device__ __forceinline__ uint32_t run_slice(uint32_t k) { return 4 * (k + 2); }
 
 // One wave per chunk.  Chunk c's codes occupy run bits [runoffs[c],
 // runoffs[c + 1]), cut into up to 64 slices and decoded as k_dec_chunks decodes
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(256) void k_dec_runs(DecBatch db) {
     for (uint32_t i = lane; i < nout; i += 64) s_out[wv][i] = 0u;
   wave_sync();
   const uint64_t len = rend - rs;
-  const uint32_t slices = min(64u, max(1u, (rend - rs) / kRunSlice));
+  const uint32_t slices = min(64u, max(1u, (rend - rs) / run_slice(k)));
   auto cut = [&](uint32_t i) {
     if (slices == 64) return i == 64 ? rend : rs + (uint32_t)(len * i / 64);
     return i >= slices ? rend : rs + (uint32_t)len * i / slices;   // (a short chunk)

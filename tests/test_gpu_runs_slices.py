@@ -1,5 +1,5 @@
-"""The run decoder where a chunk's bits make few slices (32 bits each, 1 to 64
-of them): frames from no one bit to a few hundred a chunk, their runs of equal
+"""The run decoder where a chunk's bits make few slices (1 to 64, of a few codes
+each): frames from no one bit to a few hundred a chunk, their runs of equal
 and of very different lengths, bit for bit against the oracle, valid and with
 bits of the run section flipped."""
 import numpy as np
