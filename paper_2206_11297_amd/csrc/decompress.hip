@@ -2123,7 +2123,7 @@ uint32_t decode_chunk_reps(uint64_t all_chunks) {
 // rows down to one and then by columns, until there are kDecWaves (with two
 // and four times as many, waves read the bytes above them too often: 8 frames
 // of 32x185x388 at b = 2 take 18 us, 27 and 38).  The pixel kernel on one
-// frame of 1x2048x2048 at b = 5 79 -> 19 us, at b = 2 49 -> 34, of 32x185x388
+// frame of 1x2048x2048 at b = 5 79 -> 18 us, at b = 2 49 -> 34, of 32x185x388
 // 15 -> 10, of 1x40x30000 at b = 5 390 -> 25.
 constexpr uint64_t kDecWaves = 1024;
 BandSplit decode_split(uint64_t all_bands) {
